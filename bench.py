@@ -57,45 +57,40 @@ def byte_model(name: str, c: dict, plan: dict, R: int, K: int, G: int, flags: in
     if name == "ingest":
         # records in; runs of one context out (one word per run, a count per chunk)
         return 16.0 * n + 8.0 * plan.get("n_runs", 0) + 4.0 * (-(-n // 256))
-    if name.startswith("radix_") or name.startswith("ev_radix_"):
-        ev = name.startswith("ev_")
-        slots = plan["ev_slots"] if ev else plan["rec_slots"]
-        idx = {"ctx0": 0, "ctx1": 1, "ctx2": 2, "ctx3": 3, "ts0": 4, "ts1": 5, "ts2": 6, "ts3": 7,
-               "ts4": 8, "ts5": 9, "ts6": 10, "ts7": 11, "ctx0b": 12, "ctx1b": 13, "ctx2b": 14,
-               "ctx3b": 15}
-        if ev:
-            tail = name[len("ev_radix_"):]
-            slot = int(tail[2:]) if tail.startswith("ts") else (8 + int(tail[1:]) if tail.startswith("g") else 99)
-        else:
-            slot = idx[name[len("radix_"):]]
-        if slot >= 16 or not slots[slot]["active"]:
-            return 0.0
-        out_n = int(slots[slot]["n_out"])  # records, events, or runs of one context
-        elem = 12.0 + (4.0 if (wide and not ev) else 0.0)
-        src = int(slots[slot]["src"])
-        if src == 2:  # first pass: raw records / instances
-            return (16.0 * n if not ev else 32.0 * nb) + elem * out_n
-        return 2.0 * elem * out_n
     runs = plan.get("runs", 0)
-    if name == "runs_base":  # chunk run counts scanned (read twice, written once)
-        return 12.0 * (-(-n // 256)) if runs else 0.0
-    if name == "runs_compact":  # raw runs and counts in; run keys, ids and lengths out
-        return (12.0 * (-(-n // 256)) + 24.0 * plan["n_runs"]) if runs else 0.0
-    if name == "runs_pos":  # run ids and lengths in (twice), positions out
-        return 20.0 * plan["n_runs"] if runs else 0.0
+
+    def passes(slots, lo, hi, raw, elem):
+        """Sort passes that ran in slots lo..hi: each reads (a raw source the first time) and
+        writes its elements once."""
+        b = 0.0
+        for sl in slots[lo:hi]:
+            if sl["active"]:
+                b += (raw * float(sl["n_elems"]) if int(sl["src"]) == 2 else elem * float(sl["n_elems"]))
+                b += elem * float(sl["n_out"])
+        return b
+
+    elem = 12.0 + (4.0 if wide else 0.0)
+    if name == "ctx_sort":
+        # context passes over the records, or over runs: run counts and lists in, run keys, ids
+        # and lengths out, the passes, then ids, keys and lengths in and positions out
+        b = passes(plan["rec_slots"], 0, 4, 16.0, elem)
+        return b + (8.0 * (-(-n // 256)) + 24.0 * plan["n_runs"] + 20.0 * plan["n_runs"] if runs else 0.0)
+    if name == "full_sort":  # histograms, passes, tile sums
+        if not plan["unsorted"]:
+            return 0.0
+        first = [sl for sl in plan["rec_slots"][4:16] if sl["active"]]
+        raw = bool(first) and int(first[0]["src"]) == 2
+        return (16.0 * n if raw else 8.0 * nv) + passes(plan["rec_slots"], 4, 16, 16.0, elem) + elem * nv
+    if name == "ev_sort":  # histograms, passes, sweep
+        if plan["ev_merge"]:
+            return 0.0
+        return 32.0 * nb + passes(plan["ev_slots"], 0, 12, 16.0, 12.0) + 12.0 * nev
     if name == "runs_scatter":  # raw records in, packed keys and payloads out
         return (16.0 * n + 12.0 * nv) if runs else 0.0
     if name == "tile_sums":
-        # sorted keys and payloads: order check and per-tile depth maps (record radix path)
-        return 0.0 if runs else (12.0 + (4.0 if wide else 0.0)) * nv
-    if name == "runs_check":  # each run's count and position, the two keys where it meets the one before
-        return 24.0 * plan["n_runs"] if runs else 0.0
-    if name == "tile_sums_runs":  # sorted payloads (kind and context-start bits)
-        return 4.0 * nv if runs else 0.0
-    if name == "tile_sums_full":
-        return (12.0 + (4.0 if wide else 0.0)) * nv if plan["unsorted"] else 0.0
-    if name == "ts_hist":
-        return 8.0 * nv if plan["unsorted"] else 0.0
+        # sorted keys and payloads (order check and per-tile depth maps), or after the run scatter
+        # the payloads, and per run its count, its position and the two keys where it meets the one before
+        return (4.0 * nv + 24.0 * plan["n_runs"]) if runs else elem * nv
     ev_words = K > 0 and plan["rec_ts_bits"] + (max(G - 1, 0)).bit_length() + 5 <= 64
     if name == "match":
         # sorted keys (+ context words) in; instances and one event word per record out
@@ -114,14 +109,8 @@ def byte_model(name: str, c: dict, plan: dict, R: int, K: int, G: int, flags: in
         # the histogram keys are read from HBM once; the region slices of one
         # key range re-read them from the L2 of the XCD that holds them
         return 4.0 * nb if R > 167 else 0.0
-    if name == "ev_hist":
-        return 32.0 * nb
-    if name == "sweep":
-        return 0.0 if plan["ev_merge"] else 12.0 * nev
     if name == "init":
-        return 8.0 * (R * 142 + (-(-n // 4096)) * 256 + (-(-nv // 2048)) * 4 + (-(-n // 2048)) * 8)
-    if name == "ev_clear":
-        return 8.0 * (-(-2 * nb // 4096)) * 256
+        return 8.0 * (R * 142 + ((-(-n // 4096)) * 256 if n <= 1 << 25 else 0))
     return 0.0
 
 

@@ -51,14 +51,14 @@ size_t align_up(size_t v) { return (v + kAlign - 1) & ~(kAlign - 1); }
 
 // Workspace layout for n records.  Offsets only; the base is added in run.
 struct Layout {
-  size_t plan, rec_hist, rec_off, ev_hist, ev_off, tile_ctr;
-  size_t key[2], pay[2], ctxw[2], lb[2], tsum, carry, bsum, slb, mslb, tiles, tree;
-  size_t chunk_runs, run_base, run_cnt, run_pos, run_hist, scan_bsum;
+  size_t plan, rec_hist, ev_hist, tile_ctr;
+  size_t key[2], pay[2], ctxw[2], lb, tsum, carry, bsum, slb, mslb, tiles, tree;
+  size_t chunk_runs, run_base, run_cnt, run_pos, run_hist, scan_lb;
   size_t pop_ts, pop_reg, pushes, op_parent, op_sum;
   size_t inst, excl, hist_key, agg_part, ov_mask, ov_q;
   size_t push_pos, pop_pos, ctx_list, seg_run, seg_tile0, seg_samp0, part;
   size_t total;
-  uint64_t lb_words, tree_leaves, match_tiles, pool_cap, ctx_cap, tiles_cap, chunks, run_cap;
+  uint64_t lb_words, tree_leaves, match_tiles, pool_cap, ctx_cap, tiles_cap, chunks, run_cap, scan_words;
 };
 
 Layout make_layout(const argus_attr_config& c, uint64_t n, bool own_instances) {
@@ -72,10 +72,8 @@ Layout make_layout(const argus_attr_config& c, uint64_t n, bool own_instances) {
   const uint64_t nn = n ? n : 1;
   L.plan = take(sizeof(DevPlan));
   L.rec_hist = take(sizeof(uint32_t) * kDigitPositions * kRadixBins);
-  L.rec_off = take(sizeof(uint32_t) * kDigitPositions * kRadixBins);
   L.ev_hist = take(sizeof(uint32_t) * kDigitPositions * kRadixBins);
-  L.ev_off = take(sizeof(uint32_t) * kDigitPositions * kRadixBins);
-  L.tile_ctr = take(sizeof(uint32_t) * kCtrCount);
+  L.tile_ctr = take(sizeof(uint32_t) * kCtrWords);
   for (int b = 0; b < 2; ++b) {
     // key[1] first holds the chunks' run lists: 256 places per chunk
     L.key[b] = take(sizeof(uint64_t) * ceil_div(nn, kChunk) * kChunk);
@@ -84,7 +82,7 @@ Layout make_layout(const argus_attr_config& c, uint64_t n, bool own_instances) {
   }
   // The first event pass reads 2 * n_begin <= 2 * n slots.
   L.lb_words = ceil_div(2 * nn, kSortTile) * kRadixBins;
-  for (int b = 0; b < 2; ++b) L.lb[b] = take(sizeof(uint64_t) * L.lb_words);
+  L.lb = take(sizeof(uint64_t) * L.lb_words);
   L.match_tiles = ceil_div(nn, kMatchTile);
   L.tsum = take(sizeof(uint64_t) * L.match_tiles);
   L.carry = take(sizeof(TileCarry) * L.match_tiles);
@@ -97,7 +95,8 @@ Layout make_layout(const argus_attr_config& c, uint64_t n, bool own_instances) {
   L.run_cnt = take(sizeof(uint32_t) * L.run_cap);
   L.run_pos = take(sizeof(uint32_t) * L.run_cap);
   L.run_hist = take(sizeof(uint32_t) * 4 * kRadixBins);
-  L.scan_bsum = take(sizeof(uint64_t) * kMaxScanBlocks);
+  L.scan_words = ceil_div(L.chunks, kChunksPerTile) + ceil_div(L.run_cap, kSortTile);
+  L.scan_lb = take(sizeof(uint64_t) * L.scan_words);
   L.slb = take(sizeof(uint64_t) * 8 * ceil_div(nn, kSweepTile));
   L.tiles = take(sizeof(TileDesc) * L.match_tiles);
   uint64_t leaves = 1;
@@ -293,16 +292,14 @@ int enqueue_run(argus_attr* h, const argus_record* d_records, uint64_t n, char* 
   Work& w = a.w;
   w.plan = (DevPlan*)(base + L.plan);
   w.rec_hist = (uint32_t*)(base + L.rec_hist);
-  w.rec_off = (uint32_t*)(base + L.rec_off);
   w.ev_hist = (uint32_t*)(base + L.ev_hist);
-  w.ev_off = (uint32_t*)(base + L.ev_off);
   w.tile_ctr = (uint32_t*)(base + L.tile_ctr);
   for (int b = 0; b < 2; ++b) {
     w.key[b] = (uint64_t*)(base + L.key[b]);
     w.pay[b] = (uint32_t*)(base + L.pay[b]);
     w.ctxw[b] = (uint32_t*)(base + L.ctxw[b]);
-    w.lb[b] = (uint64_t*)(base + L.lb[b]);
   }
+  w.lb = (uint64_t*)(base + L.lb);
   w.tsum = (uint64_t*)(base + L.tsum);
   w.carry = (TileCarry*)(base + L.carry);
   w.bsum = (BlockSum*)(base + L.bsum);
@@ -311,7 +308,8 @@ int enqueue_run(argus_attr* h, const argus_record* d_records, uint64_t n, char* 
   w.run_cnt = (uint32_t*)(base + L.run_cnt);
   w.run_pos = (uint32_t*)(base + L.run_pos);
   w.run_hist = (uint32_t*)(base + L.run_hist);
-  w.scan_bsum = (uint64_t*)(base + L.scan_bsum);
+  w.scan_lb = (uint64_t*)(base + L.scan_lb);
+  w.scan_words = L.scan_words;
   w.chunks = L.chunks;
   w.run_cap = L.run_cap;
   w.slb = (uint64_t*)(base + L.slb);
@@ -393,44 +391,19 @@ int enqueue_run(argus_attr* h, const argus_record* d_records, uint64_t n, char* 
   if (!step("init", [&] { return launch_init(a, s); })) return ARGUS_E_HIP;
   if (n == 0) return ARGUS_OK;
   if (!step("ingest", [&] { return launch_ingest(a, s); })) return ARGUS_E_HIP;
-  if (!step("plan", [&] { return launch_plan(a, s); })) return ARGUS_E_HIP;
-  static const char* rnames[kSlots] = {
-      "radix_ctx0", "radix_ctx1", "radix_ctx2", "radix_ctx3", "radix_ts0", "radix_ts1",
-      "radix_ts2", "radix_ts3", "radix_ts4", "radix_ts5", "radix_ts6", "radix_ts7",
-      "radix_ctx0b", "radix_ctx1b", "radix_ctx2b", "radix_ctx3b"};
-  // context sort over runs (each launch returns at once on the radix path)
-  if (!step("runs_base", [&] { return launch_runs_base(a, s); })) return ARGUS_E_HIP;
-  if (!step("runs_compact", [&] { return launch_runs_compact(a, s); })) return ARGUS_E_HIP;
-  if (!step("runs_plan", [&] { return launch_runs_plan(a, s); })) return ARGUS_E_HIP;
-  for (int sl = 0; sl < kPhase2Slot; ++sl)
-    if (!step(rnames[sl], [&] { return launch_radix_pass(a, 0, sl, n, s); })) return ARGUS_E_HIP;
-  if (!step("runs_pos", [&] { return launch_runs_pos(a, s); })) return ARGUS_E_HIP;
+  // The sort by context, its tile sums, and the full sort (which returns at
+  // once when every context is in time order in the input).
+  if (!step("ctx_sort", [&] { return launch_ctx_sort(a, s); })) return ARGUS_E_HIP;
   if (!step("runs_scatter", [&] { return launch_runs_scatter(a, s); })) return ARGUS_E_HIP;
-  if (!step("tile_sums", [&] { return launch_tsum(a, 0, s); })) return ARGUS_E_HIP;
-  if (!step("runs_check", [&] { return launch_runs_check(a, s); })) return ARGUS_E_HIP;
-  if (!step("tile_sums_runs", [&] { return launch_tsum_codes(a, s); })) return ARGUS_E_HIP;
-  if (!step("ts_hist", [&] { return launch_ts_hist(a, s); })) return ARGUS_E_HIP;
-  if (!step("lb_clear", [&] { return launch_lb_clear(a, s); })) return ARGUS_E_HIP;
-  if (!step("plan2", [&] { return launch_plan2(a, s); })) return ARGUS_E_HIP;
-  for (int sl = kPhase2Slot; sl < kSlots; ++sl)
-    if (!step(rnames[sl], [&] { return launch_radix_pass(a, 0, sl, n, s); })) return ARGUS_E_HIP;
-  if (!step("tile_sums_full", [&] { return launch_tsum(a, 1, s); })) return ARGUS_E_HIP;
+  if (!step("tile_sums", [&] { return launch_tsum(a, s); })) return ARGUS_E_HIP;
+  if (!step("full_sort", [&] { return launch_full_sort(a, s); })) return ARGUS_E_HIP;
   if (!step("tile_scan", [&] { return launch_mscan(a, s); })) return ARGUS_E_HIP;
   if (!step("match", [&] { return launch_match(a, s); })) return ARGUS_E_HIP;
   if (!step("tree", [&] { return launch_tree(a, s); })) return ARGUS_E_HIP;
   if (!step("resolve", [&] { return launch_resolve(a, s); })) return ARGUS_E_HIP;
-  if (a.K > 0 && !step("merge_plan", [&] { return launch_mplan(a, s); })) return ARGUS_E_HIP;
   if (!step("agg", [&] { return launch_agg(a, s); })) return ARGUS_E_HIP;
   if (!step("hist", [&] { return launch_hist(a, s); })) return ARGUS_E_HIP;
   if (a.K > 0) {
-    static const char* enames[kSlots] = {
-        "ev_radix_ts0", "ev_radix_ts1", "ev_radix_ts2", "ev_radix_ts3", "ev_radix_ts4",
-        "ev_radix_ts5", "ev_radix_ts6", "ev_radix_ts7", "ev_radix_g0", "ev_radix_g1",
-        "ev_radix_g2", "ev_radix_g3", "ev_unused12", "ev_unused13", "ev_unused14", "ev_unused15"};
-    if (!step("ev_plan", [&] { return launch_ev_plan(a, s); })) return ARGUS_E_HIP;
-    if (!step("ev_clear", [&] { return launch_ev_clear(a, s); })) return ARGUS_E_HIP;
-    for (int sl = 0; sl < 12; ++sl)
-      if (!step(enames[sl], [&] { return launch_radix_pass(a, 1, sl, 2 * n, s); })) return ARGUS_E_HIP;
     // Merge passes (device-planned; a pass beyond the plan returns at once).
     // Bits are merged two per pass; the last pass is merged and swept by one
     // kernel; there is always at least one pass (a group of one context is a
@@ -446,7 +419,7 @@ int enqueue_run(argus_attr* h, const argus_record* d_records, uint64_t n, char* 
       if (r + 1 < rounds && !step(mnames[r][1], [&] { return launch_merge(a, r, s); })) return ARGUS_E_HIP;
     }
     if (!step("merge_sweep", [&] { return launch_merge_sweep(a, s); })) return ARGUS_E_HIP;
-    if (!step("sweep", [&] { return launch_sweep(a, s); })) return ARGUS_E_HIP;
+    if (!step("ev_sort", [&] { return launch_ev_sort(a, s); })) return ARGUS_E_HIP;
     if (!step("ov_final", [&] { return launch_ov_final(a, s); })) return ARGUS_E_HIP;
   }
   return ARGUS_OK;

@@ -14,8 +14,9 @@
 namespace argus {
 
 // ------------------------------------------------------------------ sizes
-constexpr int kSortThreads = 256;
-constexpr int kSortItems = 16;
+constexpr int kSortThreads = 512;
+constexpr int kSortItems = 8;
+constexpr int kSortWaves = kSortThreads / 64;
 constexpr int kSortTile = kSortThreads * kSortItems;  // 4096 elements
 constexpr int kRadixBins = 256;
 constexpr int kDigitPositions = 12;  // 4 context digits, then 8 timestamp digits
@@ -27,8 +28,8 @@ constexpr int kMatchThreads = 256;
 constexpr int kMatchItems = 8;
 constexpr int kMatchTile = kMatchThreads * kMatchItems;  // 2048 elements
 
-constexpr int kSweepThreads = 256;
-constexpr int kSweepItems = 8;
+constexpr int kSweepThreads = 512;
+constexpr int kSweepItems = 4;
 constexpr int kSweepTile = kSweepThreads * kSweepItems;  // 2048 events
 constexpr int kSweepSlots = 8;  // groups of one tile aggregated in LDS
 
@@ -126,7 +127,8 @@ struct DevPlan {
   uint32_t rec_final;    // buffer holding the sorted records
   uint32_t ev_final;     // buffer holding the sorted events
   uint32_t rec_active;   // active record passes so far (look-back parity)
-  uint32_t pad0;
+  uint32_t early;        // the ingest saw a context out of time order (or the full sort is forced):
+                         // no context sort, the full sort starts from the input
   uint64_t n_ev;         // valid overlap events
   uint64_t ev_slots;     // 2 * n_begin
   SlotPlan rs[kSlots];   // record sort
@@ -196,7 +198,7 @@ struct Fn {
 };
 
 // A run of matching tiles composed (one per block of the tile-sum pass).
-struct BlockSum {
+struct __align__(8) BlockSum {
   Fn f;
   uint32_t nb;  // BEGINs
   uint32_t nh;  // context starts
@@ -214,14 +216,12 @@ struct TileCarry {
 struct Work {
   DevPlan* plan;
   uint32_t* rec_hist;   // [12][256]
-  uint32_t* rec_off;    // [12][256]
   uint32_t* ev_hist;    // [12][256]
-  uint32_t* ev_off;     // [12][256]
-  uint32_t* tile_ctr;   // [64] dynamic tile counters (one per launch that needs one)
+  uint32_t* tile_ctr;   // [kCtrWords] phase and arrival counters (chain.h)
   uint64_t* key[2];
   uint32_t* pay[2];
   uint32_t* ctxw[2];
-  uint64_t* lb[2];      // radix look-back status, [tiles][256]
+  uint64_t* lb;         // radix look-back words, [tiles][256]
   uint64_t* tsum;       // matching tile sums, [tiles]
   TileCarry* carry;     // matching tile entering values, [tiles]
   BlockSum* bsum;       // [kMaxScanBlocks]
@@ -230,7 +230,8 @@ struct Work {
   uint32_t* run_cnt;    // [run_cap] valid records of each run
   uint32_t* run_pos;    // [run_cap] sorted position of each run's first valid record | starts its context << 31
   uint32_t* run_hist;   // [4][256] context-digit histograms over runs
-  uint64_t* scan_bsum;  // [kMaxScanBlocks] block sums of the run scans
+  uint64_t* scan_lb;    // look-back words of the run scans: tiles of chunks, then tiles of runs
+  uint64_t scan_words;
   uint64_t chunks;      // ceil(n / kChunk)
   uint64_t run_cap;     // runs the run path accepts
   uint64_t* slb;        // sweep look-back status, [tiles][8]
@@ -258,7 +259,7 @@ struct Work {
   uint32_t* part;       // [tiles_cap] merge tasks, 48 B each (k_merge.hip)
   uint64_t ctx_cap;
   uint64_t tiles_cap;
-  uint64_t lb_words;    // capacity of each lb array in words
+  uint64_t lb_words;    // capacity of lb in words
   uint64_t tree_leaves; // power of two >= max match tiles
   uint64_t match_tiles; // upper bound (from n_records)
   uint64_t pool_cap;
@@ -275,15 +276,34 @@ struct RunArgs {
   Work w;
 };
 
-// Tile counter slots.
-enum CtrSlot {
-  kCtrRec = 0,     // 16 record passes
-  kCtrEv = 16,     // 16 event passes
-  kCtrMatch = 32,
-  kCtrSweep = 33,
-  kCtrMerge = 34,  // 8 merge rounds
-  kCtrCount = 64
+// Phase counters (chain.h): kPhaseWords words each, zeroed by k_init.
+constexpr uint32_t kPhaseWords = 32;
+enum Phase {
+  kPhCompact = 0,  // k_ctx_sort: runs compacted,
+  kPhCtx = 1,      //   4 context passes,
+  kPhRunPos = 5,   //   run positions
+  kPhHist = 6,     // k_full_sort: digit histograms,
+  kPhFull = 7,     //   12 passes,
+  kPhTsum = 19,    //   tile sums
+  kPhEvHist = 20,  // k_ev_sort: digit histograms,
+  kPhEv = 21,      //   12 passes,
+  kPhSweep = 33,   //   sweep
+  kPhClear = 34,   // k_ctx_sort: look-back words cleared
+  kPhCount = 35
 };
+// Arrivals at the end of a kernel are counted in kArriveGroups groups of
+// blocks, then over the groups: about 10 ns per atomic on one word make 2048
+// arrivals on one counter 20 us.
+constexpr uint32_t kArriveGroups = 16;
+constexpr uint32_t kArriveWords = 16 * (kArriveGroups + 1);  // 64 bytes per counter
+enum Arrive { kArIngest = 0, kArTsum = 1, kArTree = 2, kArCount = 3 };
+constexpr uint32_t kCtrWords = kPhCount * kPhaseWords + kArCount * kArriveWords;
+
+// Up to this many records k_init clears the look-back words of the record
+// sorts (half a byte per record); beyond it they are cleared by the sort that
+// needs them (2^28 records sorted as runs use 2 of 128 MiB: 20 us less).
+constexpr uint64_t kInitClearMax = 1ull << 25;
+constexpr uint32_t kChunksPerTile = 1024;  // chunks per tile of k_ctx_sort's compaction
 
 // Run lists of the input chunks.  The ingest's waves take chunks g, g + W,
 // g + 2W, ... (W waves); each wave stages its chunks' lists and writes them
@@ -308,10 +328,17 @@ __host__ __device__ inline uint64_t chunk_slot(const ChunkWaves& cw, uint64_t c)
 constexpr uint32_t kChunkCountBits = 9;
 // run position word (by run id): first sorted position | starts its context << 31
 constexpr uint32_t kRunPosMask = 0x7FFFFFFFu;
-// the ingest's grid for n records (four waves per block)
+// The ingest's grid for n records (four waves per block): a chunk per wave
+// up to 256 blocks, so that short traces do not wait for four chunks in a
+// row, then four chunks per wave (each block ends with up to 1024 atomics on
+// the same histogram), up to 1024 blocks.
 __host__ __device__ inline uint32_t ingest_blocks(uint64_t n) {
-  uint64_t blocks = (n + 256 * 4 * 4 - 1) / (256 * 4 * 4);
-  if (blocks > 1024) blocks = 1024;
+  uint64_t blocks = (n + 256 * 4 - 1) / (256 * 4);
+  if (blocks > 256) {
+    blocks = (n + 256 * 4 * 4 - 1) / (256 * 4 * 4);
+    if (blocks < 256) blocks = 256;
+    if (blocks > 1024) blocks = 1024;
+  }
   return blocks < 1 ? 1u : (uint32_t)blocks;
 }
 
@@ -326,6 +353,12 @@ ARGUS_DEV uint64_t ld_agent(const uint64_t* p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 ARGUS_DEV void st_agent(uint64_t* p, uint64_t v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+ARGUS_DEV uint32_t ld_agent(const uint32_t* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+ARGUS_DEV void st_agent(uint32_t* p, uint32_t v) {
   __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 ARGUS_DEV void backoff() { __builtin_amdgcn_s_sleep(1); }
@@ -548,24 +581,14 @@ constexpr uint64_t kValMask = (1ull << 62) - 1;
 // Each returns hipSuccess or the launch error.
 hipError_t launch_init(const RunArgs& a, hipStream_t s);
 hipError_t launch_ingest(const RunArgs& a, hipStream_t s);
-hipError_t launch_plan(const RunArgs& a, hipStream_t s);
-hipError_t launch_radix_pass(const RunArgs& a, int which /*0 rec, 1 ev*/, int slot,
-                             uint64_t max_elems, hipStream_t s);
-hipError_t launch_tsum(const RunArgs& a, int mode, hipStream_t s);
-hipError_t launch_runs_base(const RunArgs& a, hipStream_t s);
-hipError_t launch_runs_compact(const RunArgs& a, hipStream_t s);
-hipError_t launch_runs_plan(const RunArgs& a, hipStream_t s);
-hipError_t launch_runs_pos(const RunArgs& a, hipStream_t s);
+hipError_t launch_ctx_sort(const RunArgs& a, hipStream_t s);
 hipError_t launch_runs_scatter(const RunArgs& a, hipStream_t s);
-hipError_t launch_lb_clear(const RunArgs& a, hipStream_t s);
+hipError_t launch_tsum(const RunArgs& a, hipStream_t s);
+hipError_t launch_full_sort(const RunArgs& a, hipStream_t s);
 hipError_t launch_mscan(const RunArgs& a, hipStream_t s);
-hipError_t launch_ts_hist(const RunArgs& a, hipStream_t s);
-hipError_t launch_plan2(const RunArgs& a, hipStream_t s);
 hipError_t launch_match(const RunArgs& a, hipStream_t s);
 hipError_t launch_tree(const RunArgs& a, hipStream_t s);
 hipError_t launch_resolve(const RunArgs& a, hipStream_t s);
-hipError_t launch_runs_check(const RunArgs& a, hipStream_t s);
-hipError_t launch_tsum_codes(const RunArgs& a, hipStream_t s);
 hipError_t launch_agg(const RunArgs& a, hipStream_t s);
 // Words of the per-block statistics buffer of k_agg for n records (0: none).
 uint64_t agg_part_words(uint64_t n, uint32_t R);
@@ -575,14 +598,11 @@ hipError_t launch_hist(const RunArgs& a, hipStream_t s);
 // into the region rows (k_agg.hip).
 hipError_t launch_hist_keys(const uint32_t* keys, const uint64_t* d_count, uint64_t count_max,
                             uint64_t* rstats, uint32_t R, hipStream_t s);
-hipError_t launch_ev_plan(const RunArgs& a, hipStream_t s);
-hipError_t launch_ev_clear(const RunArgs& a, hipStream_t s);
-hipError_t launch_mplan(const RunArgs& a, hipStream_t s);
 hipError_t launch_mseg(const RunArgs& a, int rounds, hipStream_t s);
 hipError_t launch_mpart(const RunArgs& a, int round, hipStream_t s);
 hipError_t launch_merge(const RunArgs& a, int round, hipStream_t s);
 hipError_t launch_merge_sweep(const RunArgs& a, hipStream_t s);
-hipError_t launch_sweep(const RunArgs& a, hipStream_t s);
+hipError_t launch_ev_sort(const RunArgs& a, hipStream_t s);
 hipError_t launch_ov_final(const RunArgs& a, hipStream_t s);
 
 // Number of blocks of `kernel` that fit on the device at once (all CUs at

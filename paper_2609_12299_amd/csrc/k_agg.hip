@@ -1,5 +1,4 @@
-// k_agg.hip -- per-region observed statistics and ambiguity counts, and the
-// planning of the overlap events.
+// k_agg.hip -- per-region observed statistics and ambiguity counts.
 //
 // Section 3.5 of the paper: a region's report holds measured durations and
 // makes ambiguous attributions visible.  Statistics are taken
@@ -46,11 +45,8 @@ struct AggArgs {
   uint32_t R;
   uint32_t lds_regions;  // R if statistics fit in LDS, else 0
   uint32_t hist_lds;     // histograms in LDS too
-  // overlap events (K > 0): digit histograms of the events' sort keys
   const uint8_t* region_class;
   uint32_t K, G, shift;
-  uint32_t* ev_hist;  // [12][256]
-  DevPlan* wplan;
 };
 
 template <typename T>
@@ -58,23 +54,6 @@ __device__ __forceinline__ T wsum(T v) {
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
   return v;
-}
-
-// Adds this wave's digits (lanes in `valid`) to an LDS histogram: one atomic
-// when every valid lane holds the same digit (high digits of nearby
-// timestamps, groups of one context), else one per lane (low digits, which
-// rarely collide).
-__device__ __forceinline__ void whist(uint32_t* hist, uint32_t d, bool valid) {
-  const uint64_t vm = __ballot(valid);
-  if (vm == 0) return;
-  const int first = __ffsll((long long)vm) - 1;
-  const uint32_t d0 = __shfl(d, first);
-  const uint64_t same = __ballot(valid && d == d0);
-  if (same == vm) {
-    if ((int)lane_id() == first) atomicAdd(&hist[d0], (uint32_t)__popcll(vm));
-    return;
-  }
-  if (valid) atomicAdd(&hist[d], 1u);
 }
 
 // Four waves per SIMD (two blocks per compute unit): the registers and the
@@ -94,7 +73,6 @@ __global__ __launch_bounds__(512, 4) void k_agg(AggArgs a) {
   uint32_t* s_mae = s_mab + RL;
   uint32_t* s_sn = s_mae + RL;
   uint32_t* s_hist = s_sn + RL;  // [RL][130] when hist_lds
-  uint32_t* s_evh = s_hist + (a.hist_lds ? RL * 130 : 0);  // [12][256] when K > 0
   constexpr uint32_t NT = 512;
   for (uint32_t r = threadIdx.x; r < RL; r += NT) {
     s_isum[r] = 0;
@@ -111,31 +89,14 @@ __global__ __launch_bounds__(512, 4) void k_agg(AggArgs a) {
   }
   if (a.hist_lds)
     for (uint32_t i = threadIdx.x; i < RL * 130; i += NT) s_hist[i] = 0;
-  // Events for the radix sort only: the merge path needs no histograms.
-  const bool evk = a.K && !a.plan->ev_merge;
-  if (evk)
-    for (uint32_t i = threadIdx.x; i < kDigitPositions * kRadixBins; i += NT) s_evh[i] = 0;
   __syncthreads();
 
   const uint64_t nb = a.plan->n_begin;
-  // Overlap-event digits that can vary: group digits below the width of
-  // G - 1, timestamp digits above which ts_min and ts_max differ.
-  uint32_t vary = 0;
-  if (evk) {
-    const uint64_t ts_lo = a.plan->rec.ts_min;
-    const uint64_t ts_hi = ts_lo + a.plan->rec.ts_mask;
-    const bool full_ts = a.plan->rec.ts_bits >= 64 || ts_hi < ts_lo;
-    for (int d = 0; d < 4; ++d)
-      if (d == 0 || ((uint64_t)(a.G - 1) >> (8 * d)) != 0) vary |= 1u << d;
-    for (int d = 0; d < 8; ++d)
-      if (full_ts || (ts_lo >> (8 * d)) != (ts_hi >> (8 * d))) vary |= 1u << (4 + d);
-  }
-  uint64_t n_m = 0, n_mm = 0, n_u = 0, n_sn = 0, n_ev = 0, n_skip = 0;
+  uint64_t n_m = 0, n_mm = 0, n_u = 0, n_sn = 0, n_skip = 0;
   unsigned long long* rs = (unsigned long long*)a.rstats;
   // Each wave takes 2 x 64 consecutive instances per step, with their loads
   // (and then the parents' regions) in flight together, and the next step's
-  // loads issued before this step's statistics; every lane of a wave
-  // iterates the same number of times (the event histograms use ballots).
+  // loads issued before this step's statistics.
   constexpr int B = 2;
   const uint32_t lane = threadIdx.x & 63;
   const uint64_t stride = (uint64_t)gridDim.x * NT * B;
@@ -212,8 +173,6 @@ __global__ __launch_bounds__(512, 4) void k_agg(AggArgs a) {
 #pragma unroll
     for (int j = 0; j < B; ++j) {
     const uint64_t id = wb + (uint64_t)j * 64 + lane;
-    bool ev = false;
-    uint64_t eg = 0, et0 = 0, et1 = 0;
     if (id < nb) {
     const argus_instance& x = xs[j];
     if (par[j] != x.parent) a.inst[id].parent = par[j];
@@ -230,15 +189,8 @@ __global__ __launch_bounds__(512, 4) void k_agg(AggArgs a) {
       if (a.K) {
         const uint32_t cls = rcl[j];
         if (cls < a.K) {
-          eg = a.shift >= 32 ? 0 : (x.ctx_key >> a.shift);
-          if (eg < a.G) {
-            ev = true;
-            et0 = x.t_begin;
-            et1 = x.t_end;
-            n_ev += 2;
-          } else {
-            n_skip++;
-          }
+          const uint32_t eg = a.shift >= 32 ? 0 : (x.ctx_key >> a.shift);
+          if (eg >= a.G) n_skip++;
         }
       }
       const bool sn = preg[j] == region;
@@ -285,21 +237,6 @@ __global__ __launch_bounds__(512, 4) void k_agg(AggArgs a) {
     }
     if (a.hist_key) a.hist_key[id] = hk;
     }
-    if (evk) {
-#pragma unroll
-      for (int d = 0; d < 4; ++d)
-        if ((vary >> d) & 1u) {
-          const uint32_t dg = (uint32_t)(eg >> (8 * d)) & 0xFFu;
-          whist(s_evh + d * kRadixBins, dg, ev);
-          whist(s_evh + d * kRadixBins, dg, ev);
-        }
-#pragma unroll
-      for (int d = 0; d < 8; ++d)
-        if ((vary >> (4 + d)) & 1u) {
-          whist(s_evh + (4 + d) * kRadixBins, (uint32_t)(et0 >> (8 * d)) & 0xFFu, ev);
-          whist(s_evh + (4 + d) * kRadixBins, (uint32_t)(et1 >> (8 * d)) & 0xFFu, ev);
-        }
-    }
   }  // j
   }
 
@@ -307,12 +244,8 @@ __global__ __launch_bounds__(512, 4) void k_agg(AggArgs a) {
   n_mm = wsum(n_mm);
   n_u = wsum(n_u);
   n_sn = wsum(n_sn);
-  n_ev = wsum(n_ev);
   n_skip = wsum(n_skip);
   __syncthreads();  // every wave's LDS adds are done
-  if (evk)
-    for (uint32_t i = threadIdx.x; i < kDigitPositions * kRadixBins; i += NT)
-      if (s_evh[i]) atomicAdd(&a.ev_hist[i], s_evh[i]);
   if (a.part) {
     // plain stores; k_agg_reduce combines the blocks (many blocks adding
     // into the same rows with atomics serialise on them)
@@ -360,27 +293,25 @@ __global__ __launch_bounds__(512, 4) void k_agg(AggArgs a) {
   // the counters, per block, through the start of the (now read) LDS area
   // (static LDS would keep two blocks from sharing a compute unit)
   __syncthreads();
-  uint64_t* s_red = (uint64_t*)smem;  // [8][6]
+  uint64_t* s_red = (uint64_t*)smem;  // [8][5]
   const int w = threadIdx.x >> 6;
   if ((threadIdx.x & 63) == 0) {
-    s_red[w * 6 + 0] = n_m;
-    s_red[w * 6 + 1] = n_mm;
-    s_red[w * 6 + 2] = n_u;
-    s_red[w * 6 + 3] = n_sn;
-    s_red[w * 6 + 4] = n_skip;
-    s_red[w * 6 + 5] = n_ev;
+    s_red[w * 5 + 0] = n_m;
+    s_red[w * 5 + 1] = n_mm;
+    s_red[w * 5 + 2] = n_u;
+    s_red[w * 5 + 3] = n_sn;
+    s_red[w * 5 + 4] = n_skip;
   }
   __syncthreads();
-  if (threadIdx.x < 6) {
+  if (threadIdx.x < 5) {
     uint64_t v = 0;
-    for (int q = 0; q < (int)(NT / 64); ++q) v += s_red[q * 6 + threadIdx.x];
+    for (int q = 0; q < (int)(NT / 64); ++q) v += s_red[q * 5 + threadIdx.x];
     const int idx = threadIdx.x == 0   ? ARGUS_C_N_MATCHED
                     : threadIdx.x == 1 ? ARGUS_C_N_MISMATCHED
                     : threadIdx.x == 2 ? ARGUS_C_N_UNCLOSED
                     : threadIdx.x == 3 ? ARGUS_C_N_SELF_NESTED
                                        : ARGUS_C_N_OVERLAP_SKIPPED;
-    if (v && threadIdx.x < 5) atomicAdd((unsigned long long*)&a.counters[idx], (unsigned long long)v);
-    if (v && threadIdx.x == 5 && evk) atomicAdd((unsigned long long*)&a.wplan->n_ev, (unsigned long long)v);
+    if (v) atomicAdd((unsigned long long*)&a.counters[idx], (unsigned long long)v);
   }
 }
 
@@ -409,7 +340,8 @@ uint64_t agg_part_words(uint64_t n, uint32_t R) {
   uint32_t rl, hl;
   size_t bytes;
   agg_sizes(R, &rl, &hl, &bytes);
-  if (!rl) return 0;
+  // few blocks add their rows directly: no second launch
+  if (!rl || agg_grid(n) <= 8) return 0;
   const uint64_t words = agg_grid(n) * kAggFields * rl;
   return words * sizeof(uint64_t) <= kAggPartBytes ? words : 0;
 }
@@ -449,8 +381,7 @@ hipError_t launch_agg(const RunArgs& a, hipStream_t s) {
   uint32_t rl, hl;
   size_t bytes;
   agg_sizes(a.R, &rl, &hl, &bytes);
-  if (a.K) bytes += sizeof(uint32_t) * kDigitPositions * kRadixBins;
-  if (bytes < 8 * 6 * sizeof(uint64_t)) bytes = 8 * 6 * sizeof(uint64_t);  // the counter sums at the end
+  if (bytes < 8 * 5 * sizeof(uint64_t)) bytes = 8 * 5 * sizeof(uint64_t);  // the counter sums at the end
   AggArgs g{};
   g.plan = a.w.plan;
   g.inst = a.w.inst;
@@ -468,8 +399,6 @@ hipError_t launch_agg(const RunArgs& a, hipStream_t s) {
   g.K = a.K;
   g.G = a.G;
   g.shift = a.shift;
-  g.ev_hist = a.w.ev_hist;
-  g.wplan = a.w.plan;
   g.part = a.w.agg_part;
   const uint64_t blocks = agg_grid(a.n);
   if (bytes > 64 * 1024)
@@ -578,98 +507,6 @@ hipError_t launch_hist(const RunArgs& a, hipStream_t s) {
   agg_sizes(a.R, &rl, &hl, &bytes);
   if (hl) return hipSuccess;
   return launch_hist_keys(a.w.hist_key, &a.w.plan->n_begin, a.n, a.out.d_region_stats, a.R, s);
-}
-
-// ------------------------------------------------------- overlap events
-
-struct EvPlanArgs {
-  DevPlan* plan;
-  const uint32_t* hist;
-  uint32_t* off;
-  uint32_t G;
-};
-
-__global__ __launch_bounds__(256) void k_ev_plan(EvPlanArgs a) {
-  __shared__ uint32_t s_scr[4];
-  __shared__ uint32_t s_active[kDigitPositions];
-  DevPlan* p = a.plan;
-  const int t = threadIdx.x;
-  if (p->ev_merge) return;  // events are merged, not sorted (all slots stay inactive)
-  for (int pos = 0; pos < kDigitPositions; ++pos) {
-    const uint32_t h = a.hist[pos * kRadixBins + t];
-    const int used = __syncthreads_count(h != 0);
-    uint32_t x = h;
-    const int lane = t & 63, w = t >> 6;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-      uint32_t y = __shfl_up(x, o);
-      if (lane >= o) x += y;
-    }
-    if (lane == 63) s_scr[w] = x;
-    __syncthreads();
-    uint32_t pre = 0;
-    for (int k = 0; k < w; ++k) pre += s_scr[k];
-    a.off[pos * kRadixBins + t] = pre + x - h;
-    if (t == 0) s_active[pos] = used > 1;
-    __syncthreads();
-  }
-  if (t != 0) return;
-  KeySpace k = p->rec;
-  k.ctx_min = 0;
-  k.ctx_bits = bit_width64(a.G > 0 ? a.G - 1 : 0);
-  k.wide = (k.ts_bits + k.ctx_bits > 64) ? 1u : 0u;
-  p->ev = k;
-  p->ev_slots = 2 * p->n_begin;
-  // LSD order: timestamp digits, then group digits.
-  uint32_t nact = 0;
-  for (int pos = 0; pos < kDigitPositions; ++pos) nact += s_active[pos];
-  uint32_t j = 0;
-  for (int sl = 0; sl < kSlots; ++sl) {
-    SlotPlan& sp = p->es[sl];
-    sp.active = 0;
-    if (sl >= 12) continue;
-    const uint32_t pos = sl < 8 ? (uint32_t)(4 + sl) : (uint32_t)(sl - 8);
-    sp.pos = pos;
-    const bool act = s_active[pos] || (nact == 0 && sl == 0 && p->n_ev > 0);
-    if (!act) continue;
-    sp.active = 1;
-    sp.src = j == 0 ? 2u : ((j - 1) & 1u);
-    sp.dst = j & 1u;
-    sp.lb = j & 1u;
-    sp.n_elems = j == 0 ? p->ev_slots : p->n_ev;
-    sp.n_out = (uint32_t)p->n_ev;
-    sp.tiles = ceil_div(sp.n_elems, kSortTile);
-    p->ev_final = sp.dst;
-    ++j;
-  }
-}
-
-hipError_t launch_ev_plan(const RunArgs& a, hipStream_t s) {
-  EvPlanArgs e{a.w.plan, a.w.ev_hist, a.w.ev_off, a.G};
-  hipLaunchKernelGGL(k_ev_plan, dim3(1), dim3(256), 0, s, e);
-  return hipGetLastError();
-}
-
-struct EvClearArgs {
-  const DevPlan* plan;
-  uint64_t* lb0;
-};
-
-// Clears the look-back status the first event pass uses.
-__global__ __launch_bounds__(256) void k_ev_clear(EvClearArgs a) {
-  if (a.plan->ev_merge) return;
-  const uint64_t words = ceil_div(a.plan->ev_slots, kSortTile) * kRadixBins;
-  const uint64_t stride = (uint64_t)gridDim.x * 256;
-  for (uint64_t i = (uint64_t)blockIdx.x * 256 + threadIdx.x; i < words; i += stride) a.lb0[i] = 0;
-}
-
-hipError_t launch_ev_clear(const RunArgs& a, hipStream_t s) {
-  EvClearArgs e{a.w.plan, a.w.lb[0]};
-  uint64_t blocks = ceil_div(ceil_div(2 * (a.n ? a.n : 1), kSortTile) * kRadixBins, 256 * 4);
-  if (blocks > 2048) blocks = 2048;
-  if (blocks < 1) blocks = 1;
-  hipLaunchKernelGGL(k_ev_clear, dim3((uint32_t)blocks), dim3(256), 0, s, e);
-  return hipGetLastError();
 }
 
 }  // namespace argus

@@ -26,7 +26,7 @@
 // duration to its own slot and takes it off its parent's.  Instances of the
 // tile accumulate in LDS; what goes to instances open when the tile starts
 // is kept per enclosing level for k_resolve.
-#include "internal.h"
+#include "tile_tree.h"
 
 namespace argus {
 
@@ -44,6 +44,7 @@ constexpr int kLeafStride = 10;  // uint2 slots per node
 __device__ __forceinline__ uint32_t leaf_slot(uint32_t p) { return (p >> 3) * kLeafStride + (p & 7u); }
 constexpr uint32_t kNoHit = 0xFFFFFFFFu;
 static_assert(kMatchTile == 2048, "tree levels assume 2048 leaves");
+static_assert(sizeof(uint2) * kMatchTile / 8 * kLeafStride >= 2 * sizeof(int64_t) * kTreeSub, "tile tree in the leaves' LDS");
 
 // Last j < lim of the 8 siblings at g whose value is <= v, or -1.
 __device__ __forceinline__ int last_le8(const uint32_t* g, uint32_t lim, uint32_t v) {
@@ -108,7 +109,10 @@ struct MatchArgs {
   uint64_t* op_sum;
   uint64_t* counters;
   uint64_t* rstats;
-  uint32_t* tile_ctr;
+  uint32_t* ctrs;
+  int64_t* tree;
+  uint64_t tree_leaves;
+  uint32_t tree_here;  // few tiles: the last block builds the tile tree
   // overlap events in sorted-record order (merge path)
   uint64_t* ev[2];
   uint32_t K, G, shift, R;
@@ -690,6 +694,7 @@ __global__ __launch_bounds__(kMatchThreads, 3) void k_match(MatchArgs a) {
     d.n_op = n_op;
     d.pad = 0;
     a.tiles[tile] = d;
+    st_agent((uint64_t*)&a.tree[a.tree_leaves + tile], (uint64_t)d.key);
     // every thread has read this tile's scalars: reset them for the next
     // (the counts and the merge bits add up over the block's tiles)
     s_first = kMatchTile;
@@ -706,6 +711,12 @@ __global__ __launch_bounds__(kMatchThreads, 3) void k_match(MatchArgs a) {
     if (s_heads) atomicAdd(&c[ARGUS_C_N_CTX], (unsigned long long)s_heads);
     if (s_maxlvl) atomicMax(&c[ARGUS_C_MAX_LEVEL], (unsigned long long)s_maxlvl);
     if (s_orph) atomicAdd(&c[ARGUS_C_N_ORPHAN_END], (unsigned long long)s_orph);
+  }
+  // few tiles: the last block to finish builds the tree over them
+  if (a.tree_here) {
+    const uint32_t active = gridDim.x < n_tiles ? gridDim.x : (uint32_t)n_tiles;
+    if (last_arrival(a.ctrs, kArTree, active, &s_sin))
+      tree_subtree(a.tree, (uint32_t)a.tree_leaves, 0, 1, n_tiles, (int64_t*)s_leaf);
   }
 }
 
@@ -737,7 +748,10 @@ hipError_t launch_match(const RunArgs& a, hipStream_t s) {
   m.op_sum = a.w.op_sum;
   m.counters = a.out.d_counters;
   m.rstats = a.out.d_region_stats;
-  m.tile_ctr = a.w.tile_ctr;
+  m.ctrs = a.w.tile_ctr;
+  m.tree = a.w.tree;
+  m.tree_leaves = a.w.tree_leaves;
+  m.tree_here = a.w.tree_leaves <= kTreeSub ? 1u : 0u;
   uint64_t blocks = a.w.match_tiles;
   const uint64_t resident = persistent_blocks((const void*)k_match<false>, kMatchThreads);
   if (blocks > resident) blocks = resident;

@@ -37,25 +37,38 @@ constexpr uint32_t kNoSplit = 0xFFFFFFFFu;
 
 // ------------------------------------------------------------------ plan
 
-struct MPlanArgs {
+struct MSegArgs {
   DevPlan* plan;
   const uint2* ctx_list;
-  const uint64_t* counters;
+  uint4* seg_run;
+  uint32_t* seg_tile0;
+  uint32_t* seg_samp0;
+  uint64_t* counters;
+  uint64_t stride;  // per-pass stride of the segment arrays
   uint32_t K, G, shift;
   uint32_t force_radix;
   uint32_t max_bits;
   uint64_t ctx_cap;
 };
 
-// Chooses between merging and the event radix sort, and plans the passes.
-// Merging applies when the event word (group, timestamp offset, code) fits
-// 64 bits, the context list is complete, and the bits to merge are few
-// enough.
-__global__ __launch_bounds__(64) void k_mplan(MPlanArgs a) {
-  if (threadIdx.x != 0) return;
-  DevPlan* p = a.plan;
-  p->ev_merge = 0;
-  if (a.K == 0 || a.force_radix) return;
+// What every pass needs of the plan, and the pass of this block.
+struct MergePlan {
+  uint32_t use;     // 1: merge (else the event radix sort)
+  uint32_t rounds;
+  uint32_t nctx;    // contexts of groups < G
+  uint64_t end;     // sorted position where groups >= G start (or n_valid)
+  MergeRound mr;
+  uint32_t buf;     // buffer after the last pass
+};
+
+// Chooses between merging and the event radix sort, and plans the passes
+// (by one thread; every block of k_mseg does it for itself).  Merging applies
+// when the event word (group, timestamp offset, code) fits 64 bits, the
+// context list is complete, and the bits to merge are few enough.
+__device__ __forceinline__ void merge_plan(const MSegArgs& a, uint32_t round, MergePlan& m) {
+  const DevPlan* p = a.plan;
+  m.use = 0;
+  if (a.force_radix) return;
   const KeySpace ks = p->rec;
   const uint32_t g_bits = a.G > 1 ? bit_width64(a.G - 1) : 0u;
   if (ks.ts_bits + g_bits + kEvCodeBits > 64) return;
@@ -68,59 +81,40 @@ __global__ __launch_bounds__(64) void k_mplan(MPlanArgs a) {
   // more, two bits sharing a pass).
   const uint32_t radix_passes = (g_bits + ks.ts_bits + 7) / 8;
   if (bits > a.max_bits || bits > 2 * radix_passes) return;
-  // contexts of groups < G form a prefix of the (sorted) context list
+  // contexts of groups < G form a prefix of the (sorted) context list,
+  // nearly always all of it
+  auto below = [&](uint64_t i) {
+    const uint32_t c = a.ctx_list[i].x;
+    return (a.shift >= 32 ? 0u : (c >> a.shift)) < a.G;
+  };
   uint64_t lo = 0, hi = n_ctx;
+  if (n_ctx && below(n_ctx - 1)) lo = n_ctx;
   while (lo < hi) {
     const uint64_t mid = (lo + hi) / 2;
-    const uint32_t c = a.ctx_list[mid].x;
-    const uint64_t g = a.shift >= 32 ? 0 : (c >> a.shift);
-    if (g < a.G) lo = mid + 1;
+    if (below(mid)) lo = mid + 1;
     else hi = mid;
   }
-  p->m_nctx = (uint32_t)lo;
-  p->m_end = lo < n_ctx ? a.ctx_list[lo].y : p->n_valid;
+  m.nctx = (uint32_t)lo;
+  m.end = lo < n_ctx ? a.ctx_list[lo].y : p->n_valid;
   // No bit to merge: every group is one context, already in time order; one
   // pass that merges nothing takes each group as a run of its own.
-  p->m_rounds = bits ? (bits + 1) / 2 : 1u;
-  uint32_t buf = p->rec_final ^ 1u, r = 0, pending = kNoBit;
-  auto emit = [&](uint32_t b, uint32_t b2) {
-    MergeRound& m = p->mr[r++];
-    m.bit = b;
-    m.bit2 = b2;
-    m.src = buf;
-    m.dst = buf ^ 1u;
-    m.n_segs = 0;
-    m.n_tiles = 0;
-    buf ^= 1u;
-  };
-  for (uint32_t b = 0; b < 32; ++b) {
-    if (!((need >> b) & 1u)) continue;
-    if (pending == kNoBit) {
-      pending = b;
-    } else {
-      emit(pending, b);
-      pending = kNoBit;
-    }
+  m.rounds = bits ? (bits + 1) / 2 : 1u;
+  m.buf = (p->rec_final ^ 1u) ^ (m.rounds & 1u);
+  m.mr.bit = kSegByGroup;
+  m.mr.bit2 = kNoBit;
+  m.mr.src = (p->rec_final ^ 1u) ^ (round & 1u);
+  m.mr.dst = m.mr.src ^ 1u;
+  m.mr.n_segs = 0;
+  m.mr.n_tiles = 0;
+  // the pass's bits: the (2 round)-th set bit of `need` and the one after it
+  uint32_t rest = need;
+  for (uint32_t r = 0; r < 2 * round; ++r) rest &= rest - 1;
+  if (rest) {
+    m.mr.bit = (uint32_t)__ffs((int)rest) - 1u;
+    rest &= rest - 1;
+    if (rest) m.mr.bit2 = (uint32_t)__ffs((int)rest) - 1u;
   }
-  if (pending != kNoBit) emit(pending, kNoBit);
-  if (bits == 0) emit(kSegByGroup, kNoBit);
-  p->ev_final = buf;
-  p->n_ev = p->m_end;
-  KeySpace ek = ks;
-  ek.ctx_min = 0;
-  ek.ctx_bits = g_bits;
-  ek.wide = 0;
-  p->ev = ek;
-  p->ev_merge = 1;
-}
-
-hipError_t launch_mplan(const RunArgs& a, hipStream_t s) {
-  MPlanArgs m{a.w.plan, a.w.ctx_list, a.out.d_counters, a.K, a.G, a.shift,
-              (a.flags & ARGUS_FORCE_EVENT_SORT) ? 1u : 0u,
-              a.shift < (uint32_t)kMaxMergeBits ? a.shift : (uint32_t)kMaxMergeBits,
-              a.w.ctx_cap};
-  hipLaunchKernelGGL(k_mplan, dim3(1), dim3(64), 0, s, m);
-  return hipGetLastError();
+  m.use = 1;
 }
 
 // -------------------------------------------------------------- segments
@@ -149,17 +143,6 @@ __device__ __forceinline__ uint32_t block_incl_scan1024(uint32_t v, uint32_t* s_
   return pre + x;
 }
 
-struct MSegArgs {
-  DevPlan* plan;
-  const uint2* ctx_list;
-  uint4* seg_run;
-  uint32_t* seg_tile0;
-  uint32_t* seg_samp0;
-  uint64_t* counters;
-  uint64_t stride;  // per-pass stride of the segment arrays
-  uint32_t shift;
-};
-
 // Samples of a run of len events: every kSampStride-th, from its first.
 __device__ __forceinline__ uint32_t run_samples(uint32_t len) {
   return (len + kSampStride - 1) / kSampStride;
@@ -177,18 +160,35 @@ __device__ __forceinline__ uint32_t run_samples(uint32_t len) {
 __global__ __launch_bounds__(1024) void k_mseg(MSegArgs a) {
   DevPlan* p = a.plan;
   const int round = blockIdx.x;
-  if (!p->ev_merge || (uint32_t)round >= p->m_rounds) return;
+  __shared__ MergePlan s_plan;
+  if (threadIdx.x == 0) merge_plan(a, (uint32_t)round, s_plan);
+  __syncthreads();
+  if (!s_plan.use) return;
+  if (round == 0 && threadIdx.x == 0) {
+    p->m_nctx = s_plan.nctx;
+    p->m_end = s_plan.end;
+    p->m_rounds = s_plan.rounds;
+    p->ev_final = s_plan.buf;
+    p->n_ev = s_plan.end;
+    KeySpace ek = p->rec;
+    ek.ctx_min = 0;
+    ek.ctx_bits = a.G > 1 ? bit_width64(a.G - 1) : 0u;
+    ek.wide = 0;
+    p->ev = ek;
+    p->ev_merge = 1;
+  }
+  if ((uint32_t)round >= s_plan.rounds) return;
   const uint64_t off = (uint64_t)round * a.stride;
   uint4* seg_run = a.seg_run + off;
   uint32_t* seg_tile0 = a.seg_tile0 + off;
   uint32_t* seg_samp0 = a.seg_samp0 + off;
   __shared__ uint32_t s_w[16];
-  const MergeRound mr = p->mr[round];
+  const MergeRound mr = s_plan.mr;
   const bool by_group = mr.bit == kSegByGroup;
   const bool four = !by_group && mr.bit2 != kNoBit;
   const uint32_t top = four ? mr.bit2 : mr.bit;
-  const uint32_t nc = p->m_nctx;
-  const uint32_t end = (uint32_t)p->m_end;
+  const uint32_t nc = s_plan.nctx;
+  const uint32_t end = (uint32_t)s_plan.end;
   const uint32_t t = threadIdx.x;
   // segment key: ctx >> (top + 1), or the group for a pass that merges nothing
   auto hi_of = [&](uint32_t c) -> uint32_t {
@@ -302,14 +302,18 @@ __global__ __launch_bounds__(1024) void k_mseg(MSegArgs a) {
   if (t == 0) {
     seg_tile0[n_segs] = carry;
     seg_samp0[n_segs] = carry_s;
-    p->mr[round].n_segs = n_segs;
-    p->mr[round].n_tiles = carry;
+    MergeRound m = mr;
+    m.n_segs = n_segs;
+    m.n_tiles = carry;
+    p->mr[round] = m;
   }
 }
 
 hipError_t launch_mseg(const RunArgs& a, int rounds, hipStream_t s) {
   MSegArgs m{a.w.plan, a.w.ctx_list, a.w.seg_run, a.w.seg_tile0, a.w.seg_samp0,
-             a.out.d_counters, a.w.ctx_cap + 1, a.shift};
+             a.out.d_counters, a.w.ctx_cap + 1, a.K, a.G, a.shift,
+             (a.flags & ARGUS_FORCE_EVENT_SORT) ? 1u : 0u,
+             a.shift < (uint32_t)kMaxMergeBits ? a.shift : (uint32_t)kMaxMergeBits, a.w.ctx_cap};
   hipLaunchKernelGGL(k_mseg, dim3((uint32_t)(rounds > 0 ? rounds : 1)), dim3(1024), 0, s, m);
   return hipGetLastError();
 }

@@ -11,12 +11,13 @@
 // instances are put in (group, time) order beforehand, either by merging the
 // per-context runs of the sorted records (k_merge.hip, whose last round also
 // sweeps) or, when merging does not apply, by a radix sort of (group, time)
-// keys with a class payload (k_radix).  This kernel sweeps the radix-sorted
-// events: it scans the per-class active counts c (segmented by group,
+// keys with a class payload.  k_ev_sort is that sort and the sweep of its
+// events in one persistent kernel (chain.h): the sweep scans the per-class active counts c (segmented by group,
 // decoupled look-back across tiles) and, for each gap between consecutive
 // events of a group, adds gap * [c_A > 0 and c_B > 0] to U and gap * c_A *
 // c_B (or gap * c_A (c_A - 1) / 2 for A == B) to Q.  Equal times give zero
 // gaps, so the order among ties does not matter.
+#include "radix_tile.h"
 #include "sweep_common.h"
 
 namespace argus {
@@ -27,42 +28,41 @@ struct Counts {
 };
 
 struct SweepArgs {
-  const DevPlan* plan;
-  const uint64_t* key[2];
-  const uint32_t* pay[2];
-  const uint32_t* ctxw[2];
-  uint64_t* slb;
+  RadixArgs r;
+  uint32_t* hist;  // [12][256]: key digits, then raw group digits (zero on entry)
+  uint64_t* slb;   // sweep look-back words, 8 per tile
   uint64_t* ov_u;  // [G][36]
   uint64_t* ov_q;  // [G][36]
-  uint32_t K;
-  uint32_t G;
-  uint32_t* tile_ctr;
-  uint64_t* counters;
 };
 
 template <int KM>
-__global__ __launch_bounds__(kSweepThreads) void k_sweep(SweepArgs a) {
+struct SweepShared {
+  static constexpr int NP = KM * (KM + 1) / 2;
+  uint64_t u[kSweepSlots][NP];
+  uint64_t q[kSweepSlots][NP];
+  int32_t wd[kSweepThreads / 64][KM];
+  uint32_t wr[kSweepThreads / 64];
+  int32_t cin[KM];
+  uint32_t g0;
+};
+
+// One tile of 2048 sorted events.
+template <int KM>
+__device__ __forceinline__ void sweep_tile(const SweepArgs& a, SweepShared<KM>& s, const KeySpace& ks,
+                                           uint64_t n, uint32_t buf, uint64_t tile) {
   constexpr int NP = KM * (KM + 1) / 2;
   constexpr int IT = kSweepItems;
-  const DevPlan* P = a.plan;
-  if (P->ev_merge) return;  // merged events are swept by k_merge_sweep
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  __shared__ uint32_t s_tile;
-  __shared__ uint64_t s_u[kSweepSlots][NP];
-  __shared__ uint64_t s_q[kSweepSlots][NP];
-  __shared__ int32_t s_wd[4][KM];
-  __shared__ uint32_t s_wr[4];
-  __shared__ int32_t s_cin[KM];
-  __shared__ uint32_t s_g0;
-
-  const uint64_t n = P->n_ev;
-  const uint64_t tiles = ceil_div(n, kSweepTile);
-  const KeySpace ks = P->ev;
+  auto& s_u = s.u;
+  auto& s_q = s.q;
+  auto& s_wd = s.wd;
+  auto& s_wr = s.wr;
+  auto& s_cin = s.cin;
+  uint32_t& s_g0 = s.g0;
   const bool wide = ks.wide != 0;
-  const uint32_t buf = P->ev_final;
-  const uint64_t* gk = a.key[buf];
-  const uint32_t* gp = a.pay[buf];
-  const uint32_t* gc = a.ctxw[buf];
+  const uint64_t* gk = a.r.key[buf];
+  const uint32_t* gp = a.r.pay[buf];
+  const uint32_t* gc = a.r.ctxw[buf];
   constexpr uint32_t kNoGroup = 0xFFFFFFFFu;
   // (group, time, class | is_end << 8) of event i; class 0xFF changes no count
   auto decode = [&](uint64_t k, uint32_t pay, uint32_t cw, uint32_t* g, uint64_t* t,
@@ -74,21 +74,16 @@ __global__ __launch_bounds__(kSweepThreads) void k_sweep(SweepArgs a) {
   auto load_one = [&](uint64_t i, uint32_t* g, uint64_t* t, uint32_t* py) {
     decode(gk[i], gp[i], wide ? gc[i] : 0u, g, t, py);
   };
-
-  for (;;) {
-  if (tid == 0) s_tile = atomicAdd(&a.tile_ctr[kCtrSweep], 1u);
   for (int i = tid; i < kSweepSlots * NP; i += kSweepThreads) {
     (&s_u[0][0])[i] = 0;
     (&s_q[0][0])[i] = 0;
   }
   __syncthreads();
-  const uint64_t tile = s_tile;
-  if (tile >= tiles) break;
   const uint64_t base = tile * kSweepTile;
   const uint32_t cnt = n - base < (uint64_t)kSweepTile ? (uint32_t)(n - base) : (uint32_t)kSweepTile;
   const uint32_t p0 = (uint32_t)tid * IT;
 
-  // ---- this thread's 8 consecutive events, the one before and the one after
+  // ---- this thread's consecutive events, the one before and the one after
   uint32_t g[IT], py[IT];
   uint64_t t[IT];
   if (p0 + IT <= cnt && !wide) {
@@ -209,7 +204,7 @@ __global__ __launch_bounds__(kSweepThreads) void k_sweep(SweepArgs a) {
     int32_t td[KM];
 #pragma unroll
     for (int k = 0; k < KM; ++k) td[k] = 0;
-    for (int qq = 0; qq < 4; ++qq) {
+    for (int qq = 0; qq < kSweepThreads / 64; ++qq) {
       if (s_wr[qq]) {
         tr = 1;
 #pragma unroll
@@ -302,7 +297,7 @@ __global__ __launch_bounds__(kSweepThreads) void k_sweep(SweepArgs a) {
         top -= kk;
         if (kk == 0) {
           if (++spins > kMaxSpins) {
-            if (lane == 0) flag_internal_error(a.counters, 128);
+            if (lane == 0) flag_internal_error(a.r.counters, 128);
             break;
           }
           backoff();
@@ -332,10 +327,10 @@ __global__ __launch_bounds__(kSweepThreads) void k_sweep(SweepArgs a) {
     q[k] = 0;
   }
   uint32_t qg = g[0] != kNoGroup ? g[0] : g0;
-  const uint32_t K = a.K;
+  const uint32_t K = a.r.K, G = a.r.G;
   auto flush = [&](uint32_t gg) {
     const uint32_t slot = gg - g0;
-    if (gg >= a.G) return;
+    if (gg >= G) return;
 #pragma unroll
     for (int k = 0; k < NP; ++k) {
       if (u[k]) {
@@ -397,40 +392,122 @@ __global__ __launch_bounds__(kSweepThreads) void k_sweep(SweepArgs a) {
   for (uint32_t i = tid; i < (uint32_t)(kSweepSlots * NP); i += kSweepThreads) {
     const uint32_t slot = i / NP, k = i % NP;
     const uint64_t gg = (uint64_t)g0 + slot;
-    if (gg >= a.G) continue;
+    if (gg >= G) continue;
     if (s_u[slot][k]) atomicAdd((unsigned long long*)&a.ov_u[gg * kSweepQWords + k], (unsigned long long)s_u[slot][k]);
     if (s_q[slot][k]) atomicAdd((unsigned long long*)&a.ov_q[gg * kSweepQWords + k], (unsigned long long)s_q[slot][k]);
   }
   __syncthreads();
-  }  // tiles
 }
 
-hipError_t launch_sweep(const RunArgs& a, hipStream_t s) {
-  SweepArgs sa{};
-  sa.plan = a.w.plan;
-  for (int b = 0; b < 2; ++b) {
-    sa.key[b] = a.w.key[b];
-    sa.pay[b] = a.w.pay[b];
-    sa.ctxw[b] = a.w.ctxw[b];
+// Where the events cannot be merged (decided by k_mseg): their digit
+// histograms and number, a radix sort on (group, time offset), the sweep.
+// Event slot e is the begin (even) or end (odd) of instance e / 2.
+template <int KM>
+__global__ __launch_bounds__(kSortThreads) void k_ev_sort(SweepArgs a) {
+  static_assert(kSortThreads == kSweepThreads && kSortTile == 2 * kSweepTile, "one block shape");
+  DevPlan* p = a.r.plan;
+  if (p->ev_merge) return;  // merged events are swept by k_merge_sweep
+  __shared__ RadixShared s;
+  static_assert(sizeof(SweepShared<KM>) <= sizeof(s.key), "the sweep shares the stage");
+  SweepShared<KM>& sw = *reinterpret_cast<SweepShared<KM>*>(s.key);
+  __shared__ unsigned long long s_nev;
+  const uint32_t tid = threadIdx.x;
+  KeySpace ks = p->rec;
+  ks.ctx_min = 0;
+  ks.ctx_bits = a.r.G > 1 ? bit_width64(a.r.G - 1) : 0u;
+  const bool wide = ks.ts_bits + ks.ctx_bits > 64;
+  ks.wide = wide ? 1u : 0u;
+  const uint64_t slots = 2 * p->n_begin;
+  const uint32_t nd = ((wide ? ks.ts_bits : ks.ts_bits + ks.ctx_bits) + 7) / 8;
+  {
+    uint32_t* s_hist = s.pay;  // [12][256]
+    for (uint32_t i = tid; i < 12 * kRadixBins; i += kSortThreads) s_hist[i] = 0;
+    if (tid == 0) s_nev = 0;
+    const uint32_t tiles = (uint32_t)ceil_div(slots, kSortTile);
+    // sweep look-back words: at most one event per record
+    const uint64_t slb_words = 8 * ceil_div(p->n_records, kSweepTile);
+    uint32_t* ctr = phase_ctr(a.r.ctrs, kPhEvHist);
+    uint32_t mine = 0;
+    for (;;) {
+      const uint32_t t = phase_take(ctr, &s.ticket);
+      if (t >= tiles) break;
+      // the look-back words of the sort tile and of its two sweep tiles
+      if (tid < (uint32_t)kRadixBins) st_agent(&a.r.lb[(uint64_t)t * kRadixBins + tid], 0ull);
+      if (tid < 16 && 16ull * t + tid < slb_words) st_agent(&a.slb[16ull * t + tid], 0ull);
+      uint32_t n_ev = 0;
+      for (int r = 0; r < kSortItems; ++r) {
+        const uint64_t e = (uint64_t)t * kSortTile + (uint32_t)r * kSortThreads + tid;
+        if (e >= slots) continue;
+        const argus_instance x = a.r.inst[e >> 1];
+        const uint64_t g = a.r.shift >= 32 ? 0 : (x.ctx_key >> a.r.shift);
+        if (x.region_id != x.end_region_id || a.r.region_class[x.region_id] >= a.r.K || g >= a.r.G) continue;
+        ++n_ev;
+        const uint64_t t_off = ((e & 1) ? x.t_end : x.t_begin) - ks.ts_min;
+        const uint64_t k = wide ? t_off : ((ks.ts_bits >= 64 ? 0 : (g << ks.ts_bits)) | t_off);
+        for (uint32_t d = 0; d < nd; ++d) atomicAdd(&s_hist[d * kRadixBins + ((uint32_t)(k >> (8 * d)) & 0xFFu)], 1u);
+        if (wide)
+          for (uint32_t d = 0; d < 4; ++d) atomicAdd(&s_hist[(8 + d) * kRadixBins + ((uint32_t)(g >> (8 * d)) & 0xFFu)], 1u);
+      }
+      if (n_ev) atomicAdd(&s_nev, (unsigned long long)n_ev);
+      ++mine;
+    }
+    if (!mine) return;  // the blocks with a tile are as many as any later phase has tiles
+    __syncthreads();
+    for (uint32_t i = tid; i < 12 * kRadixBins; i += kSortThreads)
+      if (s_hist[i]) atomicAdd(&a.hist[i], s_hist[i]);
+    if (tid == 0 && s_nev) atomicAdd((unsigned long long*)&p->n_ev, s_nev);
+    phase_done(ctr, mine, &s.ticket);
+    phase_wait(ctr, tiles, a.r.counters);
   }
+  const uint64_t n_ev = ld_agent(&p->n_ev);
+  uint32_t act = digits_varying<12>(a.hist, 12);
+  if (!act) act = nd ? 1u : 1u << 8;  // one pass packs the events
+  uint32_t src = 2u;
+  for (uint32_t d = 0; d < 12; ++d) {
+    if (!((act >> d) & 1u)) continue;
+    RadixPass ps;
+    ps.src = src;
+    ps.dst = src == 2 ? 0u : src ^ 1u;
+    ps.mode = d < 8 ? kDigKey : kDigCtx;
+    ps.shift = 8 * (d & 7u);
+    ps.tag = 17 + d;
+    ps.n_out = (uint32_t)n_ev;
+    ps.n_elems = src == 2 ? slots : n_ev;
+    radix_offsets(s, a.hist + d * kRadixBins);
+    bool fin;
+    const uint32_t mine = radix_phase<2>(a.r, s, ks, ps, kPhEv + d, false, &fin);
+    src = ps.dst;
+    if (fin && tid == 0) {
+      note_slot(p->es[d], d < 8 ? 4 + d : d - 8, ps);
+      p->ev_slots = slots;
+      p->ev = ks;
+    }
+    if (!mine) return;
+  }
+  // the sweep reads with plain loads: what this XCD's caches hold of the
+  // buffers is dropped first
+  if (tid < 64) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+  __syncthreads();
+  const uint32_t tiles = (uint32_t)ceil_div(n_ev, kSweepTile);
+  uint32_t* ctr = phase_ctr(a.r.ctrs, kPhSweep);
+  for (;;) {
+    const uint32_t t = phase_take(ctr, &s.ticket);
+    if (t >= tiles) break;
+    sweep_tile<KM>(a, sw, ks, n_ev, src, t);
+    if (t + 1 == tiles && tid == 0) p->ev_final = src;
+  }
+}
+
+hipError_t launch_ev_sort(const RunArgs& a, hipStream_t s) {
+  SweepArgs sa{};
+  sa.r = radix_args(a);
+  sa.hist = a.w.ev_hist;
   sa.slb = a.w.slb;
   sa.ov_u = a.w.ov_mask;
   sa.ov_q = a.w.ov_q;
-  sa.K = a.K;
-  sa.G = a.G;
-  sa.tile_ctr = a.w.tile_ctr;
-  sa.counters = a.out.d_counters;
-  uint64_t blocks = ceil_div(a.n ? a.n : 1, kSweepTile);
-  const void* kern = a.K <= 2 ? (const void*)k_sweep<2> : a.K <= 4 ? (const void*)k_sweep<4> : (const void*)k_sweep<8>;
-  const uint64_t resident = persistent_blocks(kern, kSweepThreads);
-  if (blocks > resident) blocks = resident;
-  if (a.K <= 2)
-    hipLaunchKernelGGL(k_sweep<2>, dim3((uint32_t)blocks), dim3(kSweepThreads), 0, s, sa);
-  else if (a.K <= 4)
-    hipLaunchKernelGGL(k_sweep<4>, dim3((uint32_t)blocks), dim3(kSweepThreads), 0, s, sa);
-  else
-    hipLaunchKernelGGL(k_sweep<8>, dim3((uint32_t)blocks), dim3(kSweepThreads), 0, s, sa);
-  return hipGetLastError();
+  const void* kern = a.K <= 2 ? (const void*)k_ev_sort<2> : a.K <= 4 ? (const void*)k_ev_sort<4> : (const void*)k_ev_sort<8>;
+  void* args[] = {&sa};
+  return hipLaunchKernel(kern, dim3(sort_blocks(kern, 2 * a.n)), dim3(kSortThreads), args, 0, s);
 }
 
 // ------------------------------------------------------------- finalise

@@ -1,338 +1,424 @@
-// k_radix.hip -- one stable LSD radix pass over 8-bit digits.
-//
-// Stable sorting is how the records of every execution context are put in
-// execution order before the per-context stack is replayed (the paper's
-// Section 3.2 keeps a stack of open regions for each warp); the same
-// pass orders the overlap events by (group, time).
-//
-// One pass, per tile of 4096 elements (4 waves x 16 rounds x 64 lanes):
-//   * rank: each wave finds, with eight ballots, the lanes holding the same
-//     digit and counts them in per-wave LDS digit counters (stable order is
-//     wave, round, lane = element order);
-//   * the tile's 256 digit counts are published for decoupled look-back
-//     (Merrill & Garland 2016) with tile ids taken in launch order from an
-//     atomic counter, so every predecessor tile is already running;
-//   * elements are staged in LDS in digit order and written out so that a
-//     run of equal digits goes to consecutive addresses.
-// The first pass of a sort reads its raw source (records or instances),
-// drops invalid elements (they are never written) and packs the key.
-#include "internal.h"
+// k_radix.hip -- the sorts of the records: by context, and (when some
+// context is out of time order in the input) by context and time.  Each
+// sort is one persistent kernel whose passes are phases (chain.h).
+#include "radix_tile.h"
+#include "tile_sums.h"
 
 namespace argus {
 
-struct RadixArgs {
-  const DevPlan* plan;
-  int which;  // 0: records, 1: overlap events
-  int slot;
-  const uint4* rec;
-  const argus_instance* inst;
-  const uint8_t* region_class;
-  uint32_t R, K, G, shift;
-  uint64_t* key[2];
-  uint32_t* pay[2];
-  uint32_t* ctxw[2];
-  uint64_t* lb[2];
-  const uint32_t* off;  // [12][256] exclusive digit offsets
-  uint32_t* tile_ctr;
-  uint64_t* counters;
+// Adds this wave's digits (lanes in `valid`) to an LDS histogram: one atomic
+// when every valid lane holds the same digit, else one per lane.
+__device__ __forceinline__ void hist_digit(uint32_t* hist, uint32_t d, bool valid) {
+  const uint64_t vm = __ballot(valid);
+  if (vm == 0) return;
+  const uint32_t first = (uint32_t)__builtin_ctzll(vm);
+  const uint32_t d0 = (uint32_t)__builtin_amdgcn_readlane((int)d, (int)first);
+  if (__ballot(valid && d == d0) == vm) {
+    if (lane_id() == first) atomicAdd(&hist[d0], (uint32_t)__popcll(vm));
+  } else if (valid) {
+    atomicAdd(&hist[d], 1u);
+  }
+}
+
+// ------------------------------------------------- context sort over runs
+//
+// When the input holds long runs of one context (trace buffers written per
+// warp, interleaved in chunks), a stable sort of the records by context is:
+// the runs sorted stably by context (a radix sort over runs, not records),
+// each run's first position an exclusive scan of the run lengths in that
+// order, and every record written to its run's position plus its rank among
+// the run's valid records (k_runs_scatter).  Within a context, runs and the
+// records of a run keep input order, so the result equals the record radix
+// sort's.
+
+struct CtxSortArgs {
+  RadixArgs r;
+  const uint32_t* rec_hist;    // raw context digits over records
+  // runs
+  const uint64_t* runs_raw;
+  const uint32_t* chunk_runs;
+  uint32_t* run_base;
+  uint32_t* run_cnt;
+  uint32_t* run_pos;
+  uint32_t* run_hist;  // [4][256]
+  uint64_t* scan0;     // look-back words over tiles of chunks
+  uint64_t* scan1;     // ... over tiles of sorted runs
+  ChunkWaves cw;
 };
 
-__device__ __forceinline__ uint32_t digit_of(uint32_t pos, uint64_t raw_ctx, uint64_t raw_ts) {
-  return pos < 4 ? (uint32_t)(raw_ctx >> (8 * pos)) & 0xFFu
-                 : (uint32_t)(raw_ts >> (8 * (pos - 4))) & 0xFFu;
-}
-
-// WHICH (records / events) and SLOT are template parameters so that every
-// pass of a sort is a distinct kernel in profiles.
-template <int WHICH, int SLOT>
-__global__ __launch_bounds__(kSortThreads) void k_radix_pass(RadixArgs a) {
-  const SlotPlan sp = WHICH ? a.plan->es[SLOT] : a.plan->rs[SLOT];
-  if (!sp.active) return;
-  const KeySpace ks = WHICH ? a.plan->ev : a.plan->rec;
-
-  __shared__ uint32_t s_tile;
-  __shared__ uint32_t s_wave[4][kRadixBins];  // per-wave counts, then wave prefixes
-  __shared__ uint32_t s_start[kRadixBins];    // tile-local start of each digit
-  __shared__ uint32_t s_gbase[kRadixBins];    // global start of this tile's digit run
-  __shared__ uint32_t s_scr[4];
-  __shared__ uint32_t s_total;
-  __shared__ uint64_t s_key[kSortTile];
-  __shared__ uint32_t s_pay[kSortTile];
-  __shared__ uint32_t s_cw[kSortTile];
-  __shared__ uint8_t s_dig[kSortTile];
-
-  const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63;
-  // Persistent blocks: tiles are taken in order from an atomic counter, so a
-  // tile's predecessors always belong to blocks that are already running.
-  for (;;) {
-  if (tid == 0) s_tile = atomicAdd(&a.tile_ctr[(WHICH ? kCtrEv : kCtrRec) + SLOT], 1u);
-  for (int i = tid; i < 4 * kRadixBins; i += kSortThreads) (&s_wave[0][0])[i] = 0;
-  __syncthreads();
-  const uint64_t tile = s_tile;
-  if (tile >= sp.tiles) break;
-
-  const uint64_t base = tile * kSortTile;
-  const uint64_t left = sp.n_elems - base;
-  const uint32_t cnt = left < (uint64_t)kSortTile ? (uint32_t)left : (uint32_t)kSortTile;
-  const bool wide = ks.wide != 0;
-  const uint32_t pos = sp.pos;
-
-  uint64_t key[kSortItems];
-  uint32_t pay[kSortItems], cw[kSortItems], dig[kSortItems], rank[kSortItems];
-
-  // Loads first, all of them unconditional (an index past the tile's end is
-  // clamped to its last element, whose digit is then discarded), so that
-  // every load of the tile is in flight before the first one is used.
-  auto elem = [&](int r) -> uint32_t {
-    return (uint32_t)w * (kSortItems * 64) + (uint32_t)r * 64 + lane;
-  };
-  auto clamp = [&](uint32_t el) -> uint64_t { return base + (el < cnt ? el : cnt - 1); };
-  if (sp.src < 2) {
-    const uint64_t* ksrc = sp.src ? a.key[1] : a.key[0];
-    const uint32_t* psrc = sp.src ? a.pay[1] : a.pay[0];
-    const uint32_t* csrc = sp.src ? a.ctxw[1] : a.ctxw[0];
+// Tile of 1024 chunks: each chunk's first run index (a scan of the chunks'
+// run counts), then the runs of the chunks in input order as sort elements
+// (key: context offset << ts_bits, payload: run id), their lengths, and the
+// context-digit histograms over runs.  A run without valid records sorts as
+// the lowest context.
+__device__ __forceinline__ void runs_compact_tile(const CtxSortArgs& a, RadixShared& s, uint32_t* s_hist,
+                                                  const KeySpace& ks, uint64_t chunks, uint32_t tile) {
+  const uint32_t tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  constexpr int kPer = kChunksPerTile / kSortThreads;
+  const uint64_t c0 = (uint64_t)tile * kChunksPerTile + kPer * tid;
+  uint32_t word[kPer], cnt[kPer], sum = 0;
 #pragma unroll
-    for (int r = 0; r < kSortItems; ++r) {
-      const uint64_t e = clamp(elem(r));
-      key[r] = ksrc[e];
-      pay[r] = psrc[e];
-      cw[r] = wide ? csrc[e] : 0u;
-    }
+  for (int q = 0; q < kPer; ++q) word[q] = c0 + q < chunks ? a.chunk_runs[chunk_slot(a.cw, c0 + q)] : 0u;
 #pragma unroll
-    for (int r = 0; r < kSortItems; ++r) {
-      uint64_t ctx_rel, ts_off;
-      if (wide) {
-        ctx_rel = cw[r];
-        ts_off = key[r];
-      } else {
-        ctx_rel = ks.ts_bits >= 64 ? 0 : (key[r] >> ks.ts_bits);
-        ts_off = key[r] & ks.ts_mask;
-      }
-      dig[r] = elem(r) < cnt ? digit_of(pos, ks.ctx_min + ctx_rel, ks.ts_min + ts_off) : 256u;
-    }
-  } else if (WHICH == 0) {
-    uint4 rr[kSortItems];
-#pragma unroll
-    for (int r = 0; r < kSortItems; ++r) rr[r] = a.rec[clamp(elem(r))];
-#pragma unroll
-    for (int r = 0; r < kSortItems; ++r) {
-      // branch-free, so that the whole 16-byte record is loaded up front
-      const uint64_t ts = (uint64_t)rr[r].x | ((uint64_t)rr[r].y << 32);
-      const uint32_t ctx = rr[r].z;
-      const uint32_t region = rr[r].w & 0xFFFFu;
-      const uint32_t kind = (rr[r].w >> 16) & 0xFFu;
-      const bool ok = elem(r) < cnt && (kind == 1 || kind == 2) && region < a.R;
-      const uint64_t ts_off = ts - ks.ts_min;
-      const uint64_t ctx_rel = (uint64_t)ctx - ks.ctx_min;
-      const uint64_t k = wide ? ts_off : ((ks.ts_bits >= 64 ? 0 : (ctx_rel << ks.ts_bits)) | ts_off);
-      key[r] = ok ? k : 0;
-      cw[r] = ok ? (uint32_t)ctx_rel : 0u;
-      const uint32_t cls = ok && swept_ctx(ctx, a.K, a.G, a.shift) ? a.region_class[region] : 0xFFu;
-      pay[r] = ok ? pack_payload(region, kind, cls) : 0u;
-      dig[r] = ok ? digit_of(pos, ctx, ts) : 256u;  // 256: invalid (never written)
-    }
-  } else {
-    // Overlap events: element e is the begin (even) or end (odd) of instance
-    // e / 2; only matched, classified instances of a group < G.
-    uint64_t tv[kSortItems];
-    uint32_t cv[kSortItems], rv[kSortItems], cl[kSortItems];
-#pragma unroll
-    for (int r = 0; r < kSortItems; ++r) {
-      const uint64_t e = clamp(elem(r));
-      const argus_instance* ip = a.inst + (e >> 1);
-      tv[r] = (e & 1) ? ip->t_end : ip->t_begin;
-      cv[r] = ip->ctx_key;
-      rv[r] = *(const uint32_t*)&ip->region_id;  // region | end_region << 16
-    }
-#pragma unroll
-    for (int r = 0; r < kSortItems; ++r) cl[r] = a.region_class[rv[r] & 0xFFFFu];
-#pragma unroll
-    for (int r = 0; r < kSortItems; ++r) {
-      uint32_t d = 256;
-      const uint32_t el = elem(r);
-      const uint32_t is_end = (uint32_t)((base + el) & 1);
-      const uint32_t region = rv[r] & 0xFFFFu, eregion = rv[r] >> 16;
-      const uint64_t g = a.shift >= 32 ? 0 : (cv[r] >> a.shift);
-      key[r] = 0;
-      pay[r] = 0;
-      cw[r] = 0;
-      if (el < cnt && region == eregion && cl[r] < a.K && g < a.G) {
-        const uint64_t ts_off = tv[r] - ks.ts_min;
-        key[r] = wide ? ts_off : ((ks.ts_bits >= 64 ? 0 : (g << ks.ts_bits)) | ts_off);
-        cw[r] = (uint32_t)g;
-        pay[r] = cl[r] | (is_end << 8);
-        d = digit_of(pos, g, tv[r]);
-      }
-      dig[r] = d;
-    }
+  for (int q = 0; q < kPer; ++q) {
+    cnt[q] = word[q] & ((1u << kChunkCountBits) - 1u);
+    sum += cnt[q];
   }
-  // Rank among this wave's elements with the same digit (stable order is
-  // wave, round, lane).  All loads above are already in flight.
+  uint32_t total;
+  uint32_t pre = sort_excl_scan(sum, s.scr, &total);
+  // per chunk of the tile: first run in the tile, place of its list
+  uint32_t* s_first = s.cw;
+  uint64_t* s_list = s.key;
 #pragma unroll
-  for (int r = 0; r < kSortItems; ++r) {
-    const uint32_t d = dig[r];
-    const bool part = d < 256;
-    const uint64_t vm = __ballot(part);
-    uint64_t peers = vm;
-#pragma unroll
-    for (int b = 0; b < 8; ++b) {
-      const uint32_t bit = (d >> b) & 1u;
-      const uint64_t m = __ballot(bit);
-      peers &= bit ? m : ~m;
-    }
-    uint32_t rk = 0;
-    if (part) {
-      const uint32_t before = (uint32_t)__popcll(peers & lanemask_lt());
-      const uint32_t old = s_wave[w][d];
-      rk = old + before;
-      __builtin_amdgcn_wave_barrier();
-      if ((peers >> lane) == 1ull) s_wave[w][d] = old + (uint32_t)__popcll(peers);
-    }
-    __builtin_amdgcn_wave_barrier();
-    rank[r] = rk;
+  for (int q = 0; q < kPer; ++q) {
+    s_first[kPer * tid + q] = pre;
+    s_list[kPer * tid + q] = wave_slot0(a.cw, (c0 + q) % a.cw.W) * kChunk + (word[q] >> kChunkCountBits);
+    pre += cnt[q];
+  }
+  if (w == 0) {
+    const uint32_t ex = (uint32_t)scan_lookback(a.scan0, tile, total, a.r.counters);
+    if (lane == 0) s.total = ex;
   }
   __syncthreads();
-
-  // Digit totals of the tile, per-wave prefixes and tile-local starts.
-  const int dgt = tid;
-  uint32_t c0 = s_wave[0][dgt], c1 = s_wave[1][dgt], c2 = s_wave[2][dgt], c3 = s_wave[3][dgt];
-  const uint32_t tot = c0 + c1 + c2 + c3;
-  uint32_t lane_total;
-  {
-    uint32_t x = tot;
+  const uint32_t r0 = s.total;  // runs before the tile
 #pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-      uint32_t y = __shfl_up(x, o);
-      if (lane >= o) x += y;
-    }
-    if (lane == 63) s_scr[w] = x;
-    __syncthreads();
-    uint32_t pre = 0, all = 0;
-    for (int k = 0; k < 4; ++k) {
-      if (k < w) pre += s_scr[k];
-      all += s_scr[k];
-    }
-    s_start[dgt] = pre + x - tot;
-    lane_total = all;
+  for (int q = 0; q < kPer; ++q) {
+    const uint32_t c = (uint32_t)q * kSortThreads + tid;
+    if ((uint64_t)tile * kChunksPerTile + c < chunks) a.run_base[(uint64_t)tile * kChunksPerTile + c] = r0 + s_first[c];
   }
-  s_wave[0][dgt] = 0;
-  s_wave[1][dgt] = c0;
-  s_wave[2][dgt] = c0 + c1;
-  s_wave[3][dgt] = c0 + c1 + c2;
-  if (tid == 0) s_total = lane_total;
-
-  // Decoupled look-back on the count of this digit in earlier tiles.
-  uint64_t* lb = a.lb[sp.lb];
-  uint64_t excl = 0;
-  if (tile == 0) {
-    st_agent(&lb[dgt], kFlagIncl | tot);
-  } else {
-    st_agent(&lb[tile * kRadixBins + dgt], kFlagAgg | tot);
-    // Four predecessors per round trip; consume them nearest first.
-    int64_t tt = (int64_t)tile - 1;
-    uint32_t spins = 0;
-    bool done = false;
-    while (!done && tt >= 0) {
-      uint64_t v[4];
-#pragma unroll
-      for (int q = 0; q < 4; ++q)
-        v[q] = tt - q >= 0 ? ld_agent(&lb[(uint64_t)(tt - q) * kRadixBins + dgt]) : kFlagIncl;
-      int used = 0;
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        if (done || used != q) break;
-        const uint64_t f = v[q] & ~kValMask;
-        if (f == 0) break;  // not published yet: reload from here
-        excl += v[q] & kValMask;
-        ++used;
-        if (f == kFlagIncl) done = true;
-      }
-      tt -= used;
-      if (used == 0) {
-        if (++spins > kMaxSpins) {
-          flag_internal_error(a.counters, 1);
-          break;
-        }
-        backoff();
-      }
-    }
-    st_agent(&lb[tile * kRadixBins + dgt], kFlagIncl | (excl + tot));
-  }
-  s_gbase[dgt] = a.off[pos * kRadixBins + dgt] + (uint32_t)excl;
-  // The other status array is the one the next pass uses: clear our slots.
-  a.lb[sp.lb ^ 1u][tile * kRadixBins + dgt] = 0;
-  __syncthreads();
-
-  // Stage in LDS in digit order.
-#pragma unroll
-  for (int r = 0; r < kSortItems; ++r) {
-    const uint32_t d = dig[r];
-    if (d < 256) {
-      const uint32_t lp = s_start[d] + s_wave[w][d] + rank[r];
-      s_key[lp] = key[r];
-      s_pay[lp] = pay[r];
-      s_cw[lp] = cw[r];
-      s_dig[lp] = (uint8_t)d;
-    }
-  }
-  __syncthreads();
-
-  // Write out: consecutive staged elements of one digit go to consecutive
-  // global positions.
-  const uint32_t total = s_total;
-  uint64_t* kd = a.key[sp.dst];
-  uint32_t* pd = a.pay[sp.dst];
-  uint32_t* cd = a.ctxw[sp.dst];
-  const uint32_t n_out = sp.n_out;
+  // consecutive threads take consecutive runs (the chunk of each by a search
+  // over the tile's chunks): whole lines are written at once
   for (uint32_t i = tid; i < total; i += kSortThreads) {
-    const uint32_t d = s_dig[i];
-    const uint32_t gp = s_gbase[d] + (i - s_start[d]);
-    if (gp >= n_out) {
-      flag_internal_error(a.counters, 2);
-      continue;
+    uint32_t lo = 0, hi = kChunksPerTile;  // the last chunk whose first run is <= i
+#pragma unroll
+    for (int b = 0; b < 10; ++b) {
+      const uint32_t mid = (lo + hi) >> 1;
+      if (s_first[mid] <= i) lo = mid;
+      else hi = mid;
     }
-    kd[gp] = s_key[i];
-    pd[gp] = s_pay[i];
-    if (wide) cd[gp] = s_cw[i];
+    const uint64_t v = a.runs_raw[s_list[lo] + (i - s_first[lo])];
+    const uint32_t n = (uint32_t)(v >> 32);
+    const uint64_t rel = n ? (uint64_t)((uint32_t)v - (uint32_t)ks.ctx_min) : 0ull;
+    const uint32_t rid = r0 + i;
+    st_agent(&a.r.key[0][rid], ks.ts_bits >= 64 ? 0ull : (rel << ks.ts_bits));
+    st_agent(&a.r.pay[0][rid], rid);
+    st_agent(&a.run_cnt[rid], n);
+    const uint32_t ctx = (uint32_t)(ks.ctx_min + rel);
+#pragma unroll
+    for (int d = 0; d < 4; ++d) atomicAdd(&s_hist[d * kRadixBins + ((ctx >> (8 * d)) & 0xFFu)], 1u);
   }
-  __syncthreads();
-  }  // tiles
 }
 
-hipError_t launch_radix_pass(const RunArgs& a, int which, int slot, uint64_t max_elems,
-                             hipStream_t s) {
-  RadixArgs ra{};
-  ra.plan = a.w.plan;
-  ra.which = which;
-  ra.slot = slot;
-  ra.rec = (const uint4*)a.rec;
-  ra.inst = a.w.inst;
-  ra.region_class = a.region_class;
-  ra.R = a.R;
-  ra.K = a.K;
-  ra.G = a.G;
-  ra.shift = a.shift;
-  for (int b = 0; b < 2; ++b) {
-    ra.key[b] = a.w.key[b];
-    ra.pay[b] = a.w.pay[b];
-    ra.ctxw[b] = a.w.ctxw[b];
-    ra.lb[b] = a.w.lb[b];
+// Tile of 4096 sorted runs: each run's first sorted record position (a scan
+// of the run lengths in sorted order), and whether it starts its context: it
+// does if it has valid records and the previous run has another context;
+// runs without valid records sort as context offset 0, so the runs of
+// offset 0 start it only at position 0.
+__device__ __forceinline__ void runs_pos_tile(const CtxSortArgs& a, RadixShared& s, const KeySpace& ks,
+                                              uint64_t n_runs, uint32_t buf, uint32_t tile) {
+  const uint32_t tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const uint32_t* ids = a.r.pay[buf];
+  const uint64_t* keys = a.r.key[buf];
+  const uint64_t base = (uint64_t)tile * kSortTile;
+  constexpr int kPer = kSortItems;
+  const uint32_t cnt = n_runs - base < (uint64_t)kSortTile ? (uint32_t)(n_runs - base) : (uint32_t)kSortTile;
+  auto ctx_of = [&](uint64_t k) -> uint32_t { return ks.ts_bits >= 64 ? 0u : (uint32_t)(k >> ks.ts_bits); };
+  // loaded in rows of 512 consecutive runs; the lengths through LDS, where
+  // each thread scans 8 consecutive ones (a pad word after every 8)
+  uint32_t* const s_len = (uint32_t*)s.key;
+  uint32_t* const s_cx = s.pay;
+  auto slot = [](uint32_t i) { return i + (i >> 3); };
+  uint32_t id[kPer], len[kPer], cx[kPer];
+#pragma unroll
+  for (int q = 0; q < kPer; ++q) {
+    const uint32_t i = (uint32_t)q * kSortThreads + tid;
+    const uint64_t e = base + (i < cnt ? i : cnt - 1);
+    id[q] = ld_agent(&ids[e]);
+    cx[q] = ctx_of(ld_agent(&keys[e]));
   }
-  ra.off = which ? a.w.ev_off : a.w.rec_off;
-  ra.tile_ctr = a.w.tile_ctr;
-  ra.counters = a.out.d_counters;
-  uint64_t blocks = ceil_div(max_elems ? max_elems : 1, kSortTile);
-  const uint64_t resident = persistent_blocks((const void*)k_radix_pass<0, 0>, kSortThreads);
-  if (blocks > resident) blocks = resident;
-  using K = void (*)(RadixArgs);
-#define ARGUS_SLOTS(W) \
-  k_radix_pass<W, 0>, k_radix_pass<W, 1>, k_radix_pass<W, 2>, k_radix_pass<W, 3>, \
-  k_radix_pass<W, 4>, k_radix_pass<W, 5>, k_radix_pass<W, 6>, k_radix_pass<W, 7>, \
-  k_radix_pass<W, 8>, k_radix_pass<W, 9>, k_radix_pass<W, 10>, k_radix_pass<W, 11>, \
-  k_radix_pass<W, 12>, k_radix_pass<W, 13>, k_radix_pass<W, 14>, k_radix_pass<W, 15>
-  static const K table[2][kSlots] = {{ARGUS_SLOTS(0)}, {ARGUS_SLOTS(1)}};
-#undef ARGUS_SLOTS
-  hipLaunchKernelGGL(table[which][slot], dim3((uint32_t)blocks), dim3(kSortThreads), 0, s, ra);
+  const uint32_t prev0 = base > 0 ? ctx_of(ld_agent(&keys[base - 1])) : 0xFFFFFFFFu;
+#pragma unroll
+  for (int q = 0; q < kPer; ++q) len[q] = ld_agent(&a.run_cnt[id[q]]);
+#pragma unroll
+  for (int q = 0; q < kPer; ++q) {
+    const uint32_t i = (uint32_t)q * kSortThreads + tid;
+    if (i >= cnt) len[q] = 0;
+    s_len[slot(i)] = len[q];
+    s_cx[i] = cx[q];
+  }
+  __syncthreads();
+  uint32_t v[kPer], sum = 0;
+#pragma unroll
+  for (int q = 0; q < kPer; ++q) {
+    v[q] = s_len[slot((uint32_t)kPer * tid + q)];
+    sum += v[q];
+  }
+  uint32_t total;
+  uint32_t pre = sort_excl_scan(sum, s.scr, &total);
+  if (w == 0) {
+    const uint32_t ex = (uint32_t)scan_lookback(a.scan1, tile, total, a.r.counters);
+    if (lane == 0) s.total = ex;
+  }
+  __syncthreads();
+  pre += s.total;
+#pragma unroll
+  for (int q = 0; q < kPer; ++q) {
+    s_len[slot((uint32_t)kPer * tid + q)] = pre;
+    pre += v[q];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < kPer; ++q) {
+    const uint32_t i = (uint32_t)q * kSortThreads + tid;
+    if (i >= cnt) continue;
+    const uint32_t pos = s_len[slot(i)], prev = i > 0 ? s_cx[i - 1] : prev0;
+    const bool head = len[q] > 0 && (cx[q] == 0 ? pos == 0 : prev != cx[q]);
+    a.run_pos[id[q]] = pos | ((head ? 1u : 0u) << 31);
+  }
+}
+
+// The sort by context.  With long runs of one context in the input: the runs
+// compacted, sorted and placed (k_runs_scatter then writes the records);
+// else radix passes over the records' varying context digits.  Stable, so
+// that contexts already in time order in the input are then sorted.  Nothing
+// to do when the ingest has seen a context out of time order: k_full_sort
+// starts from the input.
+__global__ __launch_bounds__(kSortThreads, 4) void k_ctx_sort(CtxSortArgs a) {
+  DevPlan* p = a.r.plan;
+  if (p->early) return;
+  __shared__ RadixShared s;
+  const KeySpace ks = p->rec;
+  const bool runs = p->runs != 0;
+  const uint64_t n_valid = p->n_valid, n_records = p->n_records, n_runs = p->n_runs;
+  const uint32_t tid = threadIdx.x;
+  if (runs) {
+    uint32_t* s_hist = s.pay;  // [4][256]
+    for (uint32_t i = tid; i < 4 * kRadixBins; i += kSortThreads) s_hist[i] = 0;
+    const uint64_t chunks = ceil_div(n_records, kChunk);
+    const uint32_t tiles = (uint32_t)ceil_div(chunks, kChunksPerTile);
+    uint32_t* ctr = phase_ctr(a.r.ctrs, kPhCompact);
+    uint32_t mine = 0;
+    for (;;) {
+      const uint32_t t = phase_take(ctr, &s.ticket);
+      if (t >= tiles) break;
+      runs_compact_tile(a, s, s_hist, ks, chunks, t);
+      if (a.r.clear_lb) {  // this tile's share of the rows that the run passes use
+        const uint64_t rows = ceil_div(n_runs, kSortTile);
+        clear_rows(a.r.lb, rows * t / tiles, rows * (t + 1) / tiles);
+      }
+      ++mine;
+    }
+    for (uint32_t i = tid; mine && i < 4 * kRadixBins; i += kSortThreads) {
+      const uint32_t h = s_hist[i];
+      if (h) atomicAdd(&a.run_hist[i], h);
+    }
+    // later phases may have more tiles than this one (up to 32 runs a chunk):
+    // a block without a tile here stays
+    if (mine) phase_done(ctr, mine, &s.ticket);
+    phase_wait(ctr, tiles, a.r.counters);
+  } else if (a.r.clear_lb) {
+    const uint64_t rows = ceil_div(n_records, kSortTile);
+    const uint32_t tiles = (uint32_t)ceil_div(rows, 64);
+    uint32_t* ctr = phase_ctr(a.r.ctrs, kPhClear);
+    uint32_t mine = 0;
+    for (;;) {
+      const uint32_t t = phase_take(ctr, &s.ticket);
+      if (t >= tiles) break;
+      clear_rows(a.r.lb, 64ull * t, 64ull * t + 64 < rows ? 64ull * t + 64 : rows);
+      ++mine;
+    }
+    if (mine) phase_done(ctr, mine, &s.ticket);
+    phase_wait(ctr, tiles, a.r.counters);
+  }
+  const uint32_t* hist = runs ? a.run_hist : a.rec_hist;
+  uint32_t act = digits_varying<4>(hist, 4);
+  if (!runs && !act) act = 1;  // one pass packs the records
+  uint32_t src = runs ? 0u : 2u, ran = 0;
+  for (uint32_t pos = 0; pos < 4; ++pos) {
+    if (!((act >> pos) & 1u)) continue;
+    RadixPass ps;
+    ps.src = src;
+    ps.dst = src == 2 ? 0u : src ^ 1u;
+    ps.mode = kDigCtx;
+    ps.shift = 8 * pos;
+    ps.tag = 1 + pos;
+    ps.n_out = (uint32_t)(runs ? n_runs : n_valid);
+    ps.n_elems = runs ? n_runs : src == 2 ? n_records : n_valid;
+    radix_offsets(s, hist + pos * kRadixBins);
+    const bool last = !runs && (act >> (pos + 1)) == 0;
+    bool fin;
+    const uint32_t mine = radix_phase<1>(a.r, s, ks, ps, kPhCtx + pos, last, &fin);
+    src = ps.dst;
+    ++ran;
+    if (fin && tid == 0) {
+      note_slot(p->rs[pos], pos, ps);
+      p->rec_active = ran;
+      if (!runs) p->rec_final = ps.dst;  // over runs: the scatter writes buffer 0
+    }
+    if (!mine) return;
+  }
+  if (runs) {
+    uint32_t* ctr = phase_ctr(a.r.ctrs, kPhRunPos);
+    const uint32_t tiles = (uint32_t)ceil_div(n_runs, kSortTile);
+    for (;;) {
+      const uint32_t t = phase_take(ctr, &s.ticket);
+      if (t >= tiles) break;
+      runs_pos_tile(a, s, ks, n_runs, src, t);
+    }
+  }
+}
+
+hipError_t launch_ctx_sort(const RunArgs& a, hipStream_t s) {
+  CtxSortArgs c{};
+  c.r = radix_args(a);
+  c.rec_hist = a.w.rec_hist;
+  c.runs_raw = a.w.key[1];
+  c.chunk_runs = a.w.chunk_runs;
+  c.run_base = a.w.run_base;
+  c.run_cnt = a.w.run_cnt;
+  c.run_pos = a.w.run_pos;
+  c.run_hist = a.w.run_hist;
+  c.scan0 = a.w.scan_lb;
+  c.scan1 = a.w.scan_lb + ceil_div(a.w.chunks, kChunksPerTile);
+  c.cw = chunk_waves(a.w.chunks, ingest_blocks(a.n) * 4);
+  hipLaunchKernelGGL(k_ctx_sort, dim3(sort_blocks((const void*)k_ctx_sort, a.n)), dim3(kSortThreads), 0, s, c);
+  return hipGetLastError();
+}
+
+// ------------------------------------------------------------- full sort
+
+struct FullSortArgs {
+  RadixArgs r;
+  uint32_t* hist;            // [8][256] packed-key digits (zero on entry)
+  const uint32_t* ctx_hist;  // [4][256] raw context digits over records
+  TsumArgs t;
+};
+
+// Some context is out of time order in the input: a stable sort on the
+// whole packed key (or, where context and time do not fit 64 bits, on the
+// time digits and then the context digits), from the input itself when the
+// ingest saw it, else from the context-sorted records; then the tile sums.
+// Digits are taken from the key's offsets, so no pass goes over bits that
+// ts_min and ctx_min have in common.
+__global__ __launch_bounds__(kSortThreads, 4) void k_full_sort(FullSortArgs a) {
+  DevPlan* p = a.r.plan;
+  if (!p->unsorted) return;
+  __shared__ RadixShared s;
+  static_assert(sizeof(TsumShared) <= sizeof(s.key), "tile sums share the stage");
+  TsumShared& ts = *reinterpret_cast<TsumShared*>(s.key);
+  const KeySpace ks = p->rec;
+  const bool wide = ks.wide != 0;
+  const uint64_t n_valid = p->n_valid, n_records = p->n_records;
+  const uint32_t tid = threadIdx.x;
+  const uint32_t src0 = p->early ? 2u : p->rec_final;
+  const uint32_t ran0 = p->early ? 0u : p->rec_active;
+  const uint32_t key_bits = wide ? ks.ts_bits : ks.ts_bits + ks.ctx_bits;
+  const uint32_t nd = (key_bits + 7) / 8;  // key digits (at most 8)
+  {  // histograms of the key digits
+    uint32_t* s_hist = s.pay;  // [8][256]
+    for (uint32_t i = tid; i < nd * kRadixBins; i += kSortThreads) s_hist[i] = 0;
+    const uint64_t n = src0 == 2 ? n_records : n_valid;
+    const uint32_t tiles = (uint32_t)ceil_div(n, kSortTile);
+    const uint64_t* ksrc = a.r.key[src0 & 1u];
+    uint32_t* ctr = phase_ctr(a.r.ctrs, kPhHist);
+    uint32_t mine = 0;
+    for (;;) {
+      const uint32_t t = phase_take(ctr, &s.ticket);
+      if (t >= tiles) break;
+      if (a.r.clear_lb) clear_rows(a.r.lb, t, t + 1);
+      const uint64_t base = (uint64_t)t * kSortTile;
+      uint64_t k[kSortItems];
+      bool ok[kSortItems];
+      if (src0 == 2) {
+        uint4 v[kSortItems];
+#pragma unroll
+        for (int r = 0; r < kSortItems; ++r) {
+          const uint64_t i = base + (uint32_t)r * kSortThreads + tid;
+          v[r] = a.r.rec[i < n ? i : n - 1];
+        }
+#pragma unroll
+        for (int r = 0; r < kSortItems; ++r) {
+          const uint32_t kind = (v[r].w >> 16) & 0xFFu;
+          ok[r] = base + (uint32_t)r * kSortThreads + tid < n && (kind == 1 || kind == 2) && (v[r].w & 0xFFFFu) < a.r.R;
+          const uint64_t t_off = ((uint64_t)v[r].x | ((uint64_t)v[r].y << 32)) - ks.ts_min;
+          const uint64_t c_rel = (uint64_t)v[r].z - ks.ctx_min;
+          k[r] = wide ? t_off : ((ks.ts_bits >= 64 ? 0 : (c_rel << ks.ts_bits)) | t_off);
+        }
+      } else {
+#pragma unroll
+        for (int r = 0; r < kSortItems; ++r) {
+          const uint64_t i = base + (uint32_t)r * kSortThreads + tid;
+          ok[r] = i < n;
+          k[r] = ksrc[i < n ? i : n - 1];
+        }
+      }
+      for (uint32_t d = 0; d < nd; ++d)
+#pragma unroll
+        for (int r = 0; r < kSortItems; ++r)
+          hist_digit(s_hist + d * kRadixBins, (uint32_t)(k[r] >> (8 * d)) & 0xFFu, ok[r]);
+      ++mine;
+      if (t + 1 == tiles) break;
+    }
+    if (!mine) return;  // the blocks with a tile are as many as any later phase has tiles
+    __syncthreads();
+    for (uint32_t i = tid; i < nd * kRadixBins; i += kSortThreads) {
+      const uint32_t h = s_hist[i];
+      if (h) atomicAdd(&a.hist[i], h);
+    }
+    phase_done(ctr, mine, &s.ticket);
+    if (mine < tiles) phase_wait(ctr, tiles, a.r.counters);
+  }
+  // pass k < 8: key digit k; 8 + k: raw context digit k (wide keys only)
+  uint32_t act = digits_varying<8>(a.hist, nd);
+  if (wide) act |= digits_varying<4>(a.ctx_hist, 4) << 8;
+  if (!act && src0 == 2) act = nd ? 1u : 1u << 8;  // one pass packs the records
+  uint32_t src = src0, ran = ran0;
+  for (uint32_t d = 0; d < 12; ++d) {
+    if (!((act >> d) & 1u)) continue;
+    RadixPass ps;
+    ps.src = src;
+    ps.dst = src == 2 ? 0u : src ^ 1u;
+    ps.mode = d < 8 ? kDigKey : kDigCtx;
+    ps.shift = 8 * (d & 7u);
+    ps.tag = 5 + d;
+    ps.n_out = (uint32_t)n_valid;
+    ps.n_elems = src == 2 ? n_records : n_valid;
+    radix_offsets(s, d < 8 ? a.hist + d * kRadixBins : a.ctx_hist + (d - 8) * kRadixBins);
+    bool fin;
+    const uint32_t mine = radix_phase<1>(a.r, s, ks, ps, kPhFull + d, false, &fin);
+    src = ps.dst;
+    ++ran;
+    if (fin && tid == 0) note_slot(p->rs[kPhase2Slot + d], d < 8 ? 4 + d : d - 8, ps);
+    if (!mine) return;
+  }
+  // tile sums of the sorted records, and their scan by the last block (plain
+  // loads: what this XCD's caches hold of the buffers is dropped first)
+  if (tid < 64) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+  __syncthreads();
+  uint32_t* ctr = phase_ctr(a.r.ctrs, kPhTsum);
+  uint32_t mine = 0;
+  for (;;) {
+    const uint32_t vb = phase_take(ctr, &s.ticket);
+    if (vb >= a.t.nblk) break;
+    tsum_run<false, kSortThreads>(a.t, ts, ks, n_valid, src, vb);
+    ++mine;
+    if (vb + 1 == a.t.nblk) break;
+  }
+  if (!mine || phase_done(ctr, mine, &s.ticket) != a.t.nblk) return;
+  mscan_top<kSortThreads>(a.t, ts, ceil_div(n_valid, kMatchTile));
+  if (tid == 0) {
+    p->rec_final = src;
+    p->rec_active = ran;
+  }
+}
+
+hipError_t launch_full_sort(const RunArgs& a, hipStream_t s) {
+  FullSortArgs f{};
+  f.r = radix_args(a);
+  f.hist = a.w.rec_hist + 4 * kRadixBins;
+  f.ctx_hist = a.w.rec_hist;
+  f.t = tsum_args(a);
+  hipLaunchKernelGGL(k_full_sort, dim3(sort_blocks((const void*)k_full_sort, a.n)), dim3(kSortThreads), 0, s, f);
   return hipGetLastError();
 }
 

@@ -12,72 +12,33 @@
 // pops L; otherwise the BEGIN is unclosed), and the instance open at level L
 // when tile t starts is the push at level L of the last earlier tile with
 // key <= L.  Both searches run on a min-tree over the tile keys.
-#include "internal.h"
+#include "tile_tree.h"
 
 namespace argus {
-
-constexpr int64_t kInf = 0x7FFFFFFFFFFFFFFFll;
 
 // ------------------------------------------------------------ tile tree
 
 struct TreeArgs {
   const DevPlan* plan;
-  const TileDesc* tiles;
   int64_t* tree;
-  uint64_t leaves;
+  uint32_t* ctrs;
 };
 
-// Leaves and the bottom levels (subtrees of up to 1024 leaves per block).
-__global__ __launch_bounds__(256) void k_tree_lo(TreeArgs a) {
-  __shared__ int64_t s[2048];
-  const uint64_t ntiles = a.plan->match_tiles;
-  const uint64_t sub = a.leaves < 1024 ? a.leaves : 1024;
-  const uint64_t first = (uint64_t)blockIdx.x * sub;
-  for (uint64_t i = threadIdx.x; i < sub; i += 256) {
-    const uint64_t t = first + i;
-    const int64_t v = t < ntiles ? a.tiles[t].key : kInf;
-    s[sub + i] = v;
-    a.tree[a.leaves + t] = v;
-  }
-  __syncthreads();
-  // A heap over this block's `sub` leaves in LDS (node j has children 2j and
-  // 2j + 1; leaves at sub..2sub-1).  Its level of `width` nodes is part of the
-  // global level of width * gridDim.x nodes, at this block's offset.
-  for (uint64_t width = sub / 2; width >= 1; width >>= 1) {
-    for (uint64_t k = threadIdx.x; k < width; k += 256) {
-      const uint64_t node = width + k;
-      const int64_t l = s[2 * node], r = s[2 * node + 1];
-      const int64_t m = l < r ? l : r;
-      s[node] = m;
-      const uint64_t gwidth = width * gridDim.x;
-      a.tree[gwidth + (uint64_t)blockIdx.x * width + k] = m;
-    }
-    __syncthreads();
-    if (width == 1) break;
-  }
-}
-
-// Upper levels above the per-block subtrees (one block).
-__global__ __launch_bounds__(1024) void k_tree_hi(TreeArgs a, uint64_t roots) {
-  for (uint64_t width = roots / 2; width >= 1; width >>= 1) {
-    for (uint64_t k = threadIdx.x; k < width; k += 1024) {
-      const uint64_t node = width + k;
-      const int64_t l = a.tree[2 * node], r = a.tree[2 * node + 1];
-      a.tree[node] = l < r ? l : r;
-    }
-    __syncthreads();
-    if (width == 1) break;
-  }
+// The levels above the leaves (subtrees of 1024 leaves per block); the last
+// block to finish adds the levels above the subtrees' roots.  (Up to 1024
+// leaves k_match's last block builds the tree.)
+__global__ __launch_bounds__(256) void k_tree(TreeArgs a) {
+  __shared__ int64_t s[2 * kTreeSub];
+  __shared__ uint32_t s_slot;
+  tree_subtree(a.tree, kTreeSub, blockIdx.x, gridDim.x, a.plan->match_tiles, s);
+  if (last_arrival(a.ctrs, kArTree, gridDim.x, &s_slot))
+    tree_subtree(a.tree, gridDim.x, 0, 1, gridDim.x, s);
 }
 
 hipError_t launch_tree(const RunArgs& a, hipStream_t s) {
-  TreeArgs ta{a.w.plan, a.w.tiles, a.w.tree, a.w.tree_leaves};
-  const uint64_t sub = a.w.tree_leaves < 1024 ? a.w.tree_leaves : 1024;
-  const uint64_t blocks = a.w.tree_leaves / sub;
-  hipLaunchKernelGGL(k_tree_lo, dim3((uint32_t)blocks), dim3(256), 0, s, ta);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess || blocks == 1) return e;
-  hipLaunchKernelGGL(k_tree_hi, dim3(1), dim3(1024), 0, s, ta, blocks);
+  if (a.w.tree_leaves <= kTreeSub) return hipSuccess;
+  TreeArgs ta{a.w.plan, a.w.tree, a.w.tile_ctr};
+  hipLaunchKernelGGL(k_tree, dim3((uint32_t)(a.w.tree_leaves / kTreeSub)), dim3(256), 0, s, ta);
   return hipGetLastError();
 }
 
