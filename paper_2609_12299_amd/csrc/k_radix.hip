@@ -252,8 +252,12 @@ __global__ __launch_bounds__(kSortThreads, 4) void k_ctx_sort(CtxSortArgs a) {
     ++ran;
     if (fin && tid == 0) {
       note_slot(p->rs[pos], pos, ps);
-      p->rec_active = ran;
-      if (!runs) p->rec_final = ps.dst;  // over runs: the scatter writes buffer 0
+      // the last pass only: the block of an earlier one's last tile may come
+      // here after a later pass has ended
+      if ((act >> (pos + 1)) == 0) {
+        p->rec_active = ran;
+        if (!runs) p->rec_final = ps.dst;  // over runs: the scatter writes buffer 0
+      }
     }
     if (!mine) return;
   }
