@@ -1127,6 +1127,190 @@ __device__ __forceinline__ bool tile_sums(const uint64_t* se, uint32_t cnt, bool
   return true;
 }
 
+// LDS of one block of the last pass with more than four classes.
+template <int KC>
+struct MsRows {
+  static constexpr int NW = kMergeThreads / 64;
+  static constexpr int NV = 1 + KC + KC * (KC + 1);  // S0, S1', S2', T
+  int32_t wd[NW][8];
+  int32_t wm[NW][8];
+  uint64_t next;
+  uint32_t has_next;
+  uint64_t s1[NW][8];
+  uint64_t m[8][8];
+  uint32_t bins[256];      // gap sum of each set of active classes
+  uint64_t a[NW][8][64];   // a lane's row sums per event class (zero between tiles)
+};
+
+// tile_sums for five to eight classes.  Pair sums per thread would take
+// K(K+1)/2 multiply-adds and as many activity tests per event (at eight
+// classes 202 registers, one block per compute unit: the pass took 2.0 ms over
+// 2^26 records, this way 1.07), so a group of 8 lanes takes an event together,
+// lane y holding class y's count.  Summed by parts, with tau the time from an
+// event to the tile's end,
+//   sum gap l'_x l'_y = tau_first B^2 + sum over events of x of s tau l'_y
+//                                     + sum over events of y of s tau l'_x
+// (s = +-1; the other count does not move), and for C(l', 2) the count before
+// a BEGIN or after an END takes l's place: one multiply-add per event and
+// lane, into the lane's own LDS sum for the event's class.  The gaps go to
+// one bin per set of active classes, whose sums over supersets are the T.
+// The 64 groups of a block take equal stretches of consecutive events.
+// Products are signed 32 x 32 bits: a tile spanning 2^31 cycles or more is
+// left to the wide kernel.
+template <int KC>
+__device__ __forceinline__ bool tile_sums_rows(uint64_t* se, uint32_t cnt, bool first, MsRows<KC>& ss,
+                                               uint64_t* rec, uint32_t es) {
+  static_assert(KC > 4 && KC <= 8, "8 lanes per event");
+  static_assert(kMergeThreads == 512, "64 groups of 8 lanes");
+  constexpr int NP = KC * (KC + 1) / 2;
+  constexpr int NW = MsRows<KC>::NW;
+  constexpr int NV = MsRows<KC>::NV;
+  const uint32_t t = threadIdx.x, lane = t & 63, w = t >> 6, y = lane & 7u;
+  const uint64_t first_w = se[0];
+  const bool has_next = ss.has_next != 0;
+  const uint64_t last_w = has_next ? ss.next : se[lpad(cnt - 1)];
+  const uint64_t g = es >= 64 ? 0ull : (first_w >> es);
+  const uint64_t head = (g & 0xFFFFFFFFull) | ((uint64_t)(first ? 1u : 0u) << 32);
+  if (((last_w >> kEvCodeBits) - (first_w >> kEvCodeBits)) >= (1ull << 31)) {
+    if (t == 0) rec[0] = head | (1ull << 33);
+    return false;
+  }
+  const uint32_t per = (cnt + 63) / 64;
+  const uint32_t d = (t >> 3) * per;
+  const uint32_t nval = d < cnt ? (cnt - d < per ? cnt - d : per) : 0u;
+  auto code_of = [&](uint64_t e) -> uint32_t { return (uint32_t)e & ((1u << kEvCodeBits) - 1u); };
+  // ---- the class's delta over the group's events and its lowest running
+  // count, then the deltas scanned over the block's groups
+  int32_t dd = 0, lmin = 0x7FFFFFFF;
+#pragma unroll 4
+  for (uint32_t j = 0; j < nval; ++j) {
+    const uint32_t c1 = code_of(se[lpad(d + j)]) - 1u;
+    dd += (c1 >> 1) == y ? 1 - 2 * (int32_t)(c1 & 1u) : 0;
+    lmin = dd < lmin ? dd : lmin;
+  }
+  int32_t inc = dd;
+#pragma unroll
+  for (int off = 8; off < 64; off <<= 1) {
+    const int32_t o = __shfl_up(inc, off);
+    inc += lane >= (uint32_t)off ? o : 0;
+  }
+  if (lane >= 56) ss.wd[w][y] = inc;
+  if (t < 256) ss.bins[t] = 0;
+  if (t == 0) se[lpad(cnt)] = last_w;  // the event after the last: the next one, or no gap
+  __syncthreads();
+  int32_t pre = inc - dd;
+#pragma unroll
+  for (int q = 0; q < NW; ++q) pre += q < (int)w ? ss.wd[q][y] : 0;
+  {
+    int32_t m0 = nval ? pre + lmin : 0x7FFFFFFF;
+#pragma unroll
+    for (int off = 8; off < 64; off <<= 1) {
+      const int32_t o = __shfl_xor(m0, off);
+      m0 = o < m0 ? o : m0;
+    }
+    if (lane < 8) ss.wm[w][y] = m0;
+  }
+  __syncthreads();
+  int32_t mp = 0x7FFFFFFF;
+#pragma unroll
+  for (int q = 0; q < NW; ++q) mp = ss.wm[q][y] < mp ? ss.wm[q][y] : mp;
+  mp += kLBias;
+  // ---- the sums
+  const uint32_t t_end = (uint32_t)(last_w >> kEvCodeBits);
+  int32_t l = pre + kLBias;
+  uint64_t s1 = 0;
+  uint64_t* acc = &ss.a[w][0][lane];
+  uint64_t cur = se[lpad(d < cnt ? d : cnt)];
+  uint32_t tau = t_end - (uint32_t)(cur >> kEvCodeBits);
+#pragma unroll 2
+  for (uint32_t j = 0; j < nval; ++j) {
+    const uint64_t nx = se[lpad(d + j + 1)];
+    const uint32_t tau_nx = t_end - (uint32_t)(nx >> kEvCodeBits);
+    const uint32_t code = code_of(cur), c1 = code - 1u, cls = c1 >> 1;
+    const int32_t neg = -(int32_t)(c1 & 1u);  // -1: END
+    const int32_t ln = l + (cls == y ? 1 + 2 * neg : 0);
+    const int32_t v = neg ? ln : l;
+    if (code) atomicAdd((unsigned long long*)&acc[(cls & 7u) * 64], (unsigned long long)((int64_t)(int32_t)tau * ((v ^ neg) - neg)));
+    const uint32_t gap = tau - tau_nx;
+    s1 += (uint64_t)gap * (uint32_t)ln;
+    const uint64_t act = __ballot(ln > mp);
+    if (y == 0 && gap) atomicAdd(&ss.bins[(uint32_t)(act >> lane) & 0xFFu], gap);
+    l = ln;
+    cur = nx;
+    tau = tau_nx;
+  }
+#pragma unroll
+  for (int off = 8; off < 64; off <<= 1) s1 += (uint64_t)__shfl_xor((long long)s1, off);
+  if (lane < 8) ss.s1[w][y] = s1;
+  __syncthreads();
+  // ---- tile totals: wave c adds up class c's rows; the bins' sums over
+  // supersets in the low six classes within each of the first four waves
+  uint64_t r = 0;
+#pragma unroll
+  for (int q = 0; q < NW; ++q) {
+    r += ss.a[q][w][lane];
+    ss.a[q][w][lane] = 0;
+  }
+#pragma unroll
+  for (int off = 8; off < 64; off <<= 1) r += (uint64_t)__shfl_xor((long long)r, off);
+  if (lane < 8) ss.m[w][y] = r;
+  if (t < 256) {
+    uint32_t b = ss.bins[t];
+#pragma unroll
+    for (int bit = 1; bit < 64; bit <<= 1) {
+      const uint32_t o = __shfl_xor(b, bit);
+      b += (lane & (uint32_t)bit) ? 0u : o;
+    }
+    ss.bins[t] = b;
+  }
+  __syncthreads();
+  if (t < (uint32_t)NV) {
+    const uint64_t s0 = (uint32_t)(t_end - (uint32_t)(first_w >> kEvCodeBits));
+    uint64_t sum = 0;
+    if (t == 0) {
+      sum = s0;
+    } else if (t < 1u + KC) {
+#pragma unroll
+      for (int q = 0; q < NW; ++q) sum += ss.s1[q][t - 1];
+    } else {
+      const uint32_t k0 = t - 1 - KC, k = k0 < (uint32_t)NP ? k0 : k0 - NP;
+      uint32_t px = 0, row = 0;  // pair k is (px, px + k - row)
+#pragma unroll
+      for (int x = 1; x < KC; ++x) {
+        const uint32_t at = (uint32_t)pair_index<KC>(x, x);
+        if (k >= at) {
+          px = (uint32_t)x;
+          row = at;
+        }
+      }
+      const uint32_t py = px + k - row;
+      if (k0 < (uint32_t)NP) {
+        constexpr uint64_t B = (uint64_t)kLBias;
+        sum = px == py ? ss.m[px][px] + s0 * (B * (B - 1) / 2) : ss.m[px][py] + ss.m[py][px] + s0 * (B * B);
+      } else {
+        const uint32_t m = (1u << px) | (1u << py);
+#pragma unroll
+        for (uint32_t hi = 0; hi < 256; hi += 64)
+          if ((hi & m) == 0) sum += ss.bins[m | hi];
+      }
+    }
+    rec[1 + KC + t] = sum;
+  } else if (t == (uint32_t)kMergeThreads - 1) {
+    rec[0] = head;
+#pragma unroll
+    for (int x = 0; x < KC; ++x) {
+      int32_t agg = 0, mn = 0x7FFFFFFF;
+#pragma unroll
+      for (int q = 0; q < NW; ++q) {
+        agg += ss.wd[q][x];
+        mn = ss.wm[q][x] < mn ? ss.wm[q][x] : mn;
+      }
+      rec[1 + x] = (uint64_t)(uint32_t)agg | ((uint64_t)(uint32_t)mn << 32);
+    }
+  }
+  return true;
+}
+
 // The last merge pass fused with the class-overlap sums.  Each tile of at
 // most 4096 merged events belongs to one group.  Per tile: merge the input
 // slices in LDS (8 consecutive outputs per thread and stage, written back in
@@ -1143,8 +1327,11 @@ __device__ __forceinline__ void merge_sweep_tiles(const MergeSweepArgs& a) {
   const DevPlan* p = a.plan;
   if (!p->ev_merge || p->m_rounds == 0) return;
   __shared__ uint64_t s_e[kMergeLds];
-  __shared__ MsShared<KC> ss;
-  if constexpr (!WIDE && MsShared<KC>::BINS) {
+  constexpr bool ROWS = !WIDE && KC > 4;
+  __shared__ typename std::conditional<ROWS, MsRows<KC>, MsShared<KC>>::type ss;
+  if constexpr (ROWS) {
+    for (uint32_t i = threadIdx.x; i < sizeof(ss.a) / sizeof(uint64_t); i += kMergeThreads) (&ss.a[0][0][0])[i] = 0;
+  } else if constexpr (!WIDE && MsShared<KC>::BINS) {
     if (threadIdx.x < (uint32_t)kMsThreads)
       for (int m = 0; m < MsShared<KC>::BW; ++m) ss.bins[threadIdx.x * MsShared<KC>::BW + m] = 0;
   }
@@ -1194,7 +1381,8 @@ __device__ __forceinline__ void merge_sweep_tiles(const MergeSweepArgs& a) {
       }
       __syncthreads();
       merge_staged(s_e, tk, t);
-      tile_sums<KC, WIDE>(s_e, cnt, tk.first != 0, ss, rec, es);
+      if constexpr (ROWS) tile_sums_rows<KC>(s_e, cnt, tk.first != 0, ss, rec, es);
+      else tile_sums<KC, WIDE>(s_e, cnt, tk.first != 0, ss, rec, es);
       __syncthreads();
     }
     if (WIDE) __syncthreads();  // s_wide is rewritten for the next tiles
@@ -1202,9 +1390,10 @@ __device__ __forceinline__ void merge_sweep_tiles(const MergeSweepArgs& a) {
 }
 
 // Up to four classes: six waves per SIMD (three blocks per compute unit; the
-// kernel is ALU bound and the extra waves hide the LDS latency).
+// kernel is ALU bound and the extra waves hide the LDS latency); above, LDS
+// for two blocks.
 template <int KC>
-__global__ __launch_bounds__(kMergeThreads, KC <= 4 ? 6 : 1) void k_merge_sweep(MergeSweepArgs a) {
+__global__ __launch_bounds__(kMergeThreads, KC <= 4 ? 6 : 4) void k_merge_sweep(MergeSweepArgs a) {
   merge_sweep_tiles<KC, false>(a);
 }
 

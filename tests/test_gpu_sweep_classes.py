@@ -1,0 +1,60 @@
+"""The class-overlap sums of merged tiles, for every class count: five to
+eight classes are summed by parts, 8 lanes per event and a stretch of events per
+group of lanes, so tile fills around its 64 groups and the spans at which the
+32-bit time no longer holds (2^31; 2^32 for fewer classes) are where it can go
+wrong.  All integers: compared with the oracle bit for bit."""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+
+from gpu_util import assert_parity, gpu_run, log, oracle_run
+
+pytestmark = pytest.mark.gpu
+DTYPE = np.dtype([("ts", "<u8"), ("ctx", "<u4"), ("region", "<u2"), ("kind", "u1"), ("pad", "u1")])
+
+
+def _records(n, span, K, seed, n_ctx=4):
+    """Nested pairs of random regions in `n_ctx` contexts of one group, times spread over [base, base + span]."""
+    rng = np.random.default_rng(seed)
+    r = np.zeros(n, DTYPE)
+    ts = np.sort(rng.integers(0, span, n, endpoint=True, dtype=np.uint64))
+    ts[0], ts[-1] = 0, span
+    r["ts"] = ts + np.uint64(12345)
+    r["ctx"] = rng.integers(0, n_ctx, n)
+    stacks = [[] for _ in range(n_ctx)]
+    for i in range(n):
+        st = stacks[r["ctx"][i]]
+        if st and rng.random() < 0.5:
+            r["kind"][i] = 2
+            r["region"][i] = st.pop() if rng.random() < 0.97 else rng.integers(0, K + 2)
+        else:
+            r["kind"][i] = 1
+            r["region"][i] = rng.integers(0, K + 2)  # the last two: no class
+            st.append(r["region"][i])
+    return r.view(np.uint8).reshape(n, 16)
+
+
+def _params(K):
+    cls = np.array(list(range(K)) + [0xFF, 0xFF], np.uint8)
+    return dict(num_regions=K + 2, num_classes=K, region_class=cls, group_shift=2, num_groups=3)
+
+
+@pytest.mark.parametrize("K", [4, 5, 6, 7, 8])
+@pytest.mark.parametrize("n", [2, 63, 64, 65, 129, 3556, 4097, 30011])
+def test_fill(oracle_mod, n, K):
+    rec = _records(n, 50 * n, K, n * 9 + K, n_ctx=4 if n < 30000 else 12)
+    log(f"[gpu] sweep of {K} classes, {n} records")
+    g = gpu_run(rec, _params(K), with_plan=True)
+    assert g.pop("_plan")["ev_merge"] == 1
+    assert_parity(g, oracle_run(oracle_mod, rec, _params(K)), what=f"K={K} n={n}")
+
+
+@pytest.mark.parametrize("K", [4, 5, 8])
+@pytest.mark.parametrize("span", [0, (1 << 31) - 1, 1 << 31, (1 << 32) - 1, 1 << 32, 1 << 45])
+def test_span(oracle_mod, span, K):
+    rec = _records(900, span, K, K)
+    log(f"[gpu] sweep of {K} classes over {span} cycles")
+    g = gpu_run(rec, _params(K), with_plan=True)
+    assert g.pop("_plan")["ev_merge"] == 1
+    assert_parity(g, oracle_run(oracle_mod, rec, _params(K)), what=f"K={K} span={span}")
