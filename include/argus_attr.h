@@ -406,7 +406,8 @@ enum {
 };
 enum {
   ARGUS_PR_N_PROBES = 0, ARGUS_PR_N_BAD = 1, ARGUS_PR_N_JOINED = 2, ARGUS_PR_N_UNJOINED = 3,
-  ARGUS_PR_N_GROUPS = 4, ARGUS_PR_NUM_COUNTERS = 8 /* 5..7 are zero */
+  ARGUS_PR_N_GROUPS = 4, ARGUS_PR_NUM_COUNTERS = 8 /* 5..7 are zero (7: nonzero only if the
+                                                       library detected an internal error) */
 };
 
 typedef struct argus_probes_config {

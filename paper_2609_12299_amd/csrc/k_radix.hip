@@ -6,20 +6,6 @@
 
 namespace argus {
 
-// Adds this wave's digits (lanes in `valid`) to an LDS histogram: one atomic
-// when every valid lane holds the same digit, else one per lane.
-__device__ __forceinline__ void hist_digit(uint32_t* hist, uint32_t d, bool valid) {
-  const uint64_t vm = __ballot(valid);
-  if (vm == 0) return;
-  const uint32_t first = (uint32_t)__builtin_ctzll(vm);
-  const uint32_t d0 = (uint32_t)__builtin_amdgcn_readlane((int)d, (int)first);
-  if (__ballot(valid && d == d0) == vm) {
-    if (lane_id() == first) atomicAdd(&hist[d0], (uint32_t)__popcll(vm));
-  } else if (valid) {
-    atomicAdd(&hist[d], 1u);
-  }
-}
-
 // ------------------------------------------------- context sort over runs
 //
 // When the input holds long runs of one context (trace buffers written per

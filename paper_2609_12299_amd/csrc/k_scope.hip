@@ -28,7 +28,7 @@
 #include <algorithm>
 #include <mutex>
 
-#include "internal.h"
+#include "radix_tile.h"
 
 namespace argus {
 
@@ -47,20 +47,9 @@ constexpr uint32_t kOrdSlices = 128;                              // blocks per 
 // A stable LSD radix sort over 8-bit digits of 16-byte elements (two u64
 // words, ping-pong buffers).  The first pass may read the instance array
 // instead (word a = BEGIN region, word b = context << 32 | index).
-// Device-side state of a sort whose passes on constant digits are skipped:
-// over all elements, the OR and the AND of each word (bits where they
-// differ mark the digits that vary).  The passes go over word a's bytes
-// 0..7, then word b's bytes 4..7, in that order; a pass that runs moves the
-// elements to the other buffer, so the buffer a pass reads is the parity of
-// the passes before it that run.
-struct SortCtl {
-  uint64_t or_a, and_a, or_b, and_b;
-};
-
 struct SortBufs {
   uint64_t* a[2];
   uint64_t* b[2];
-  SortCtl* ctl;    // NULL: every pass runs, buffers as the caller says
   uint32_t* hist;  // [256][tiles_max], digit-major
   uint32_t* bsum;  // scan block sums
   uint64_t tiles_max;
@@ -69,28 +58,6 @@ struct SortBufs {
   const argus_instance* inst;  // source of the SRC_INST passes
 };
 enum { kSrcBuf = 0, kSrcInst = 1 };
-
-// A pass whose digit is the same for every element leaves the order as it
-// is: it is skipped (its kernels return at once and the buffer stays).
-__device__ __forceinline__ bool sb_skip(const SortBufs& s, int word, int shift) {
-  if (!s.ctl) return false;
-  const uint64_t vary = word ? (s.ctl->or_b ^ s.ctl->and_b) : (s.ctl->or_a ^ s.ctl->and_a);
-  return ((vary >> shift) & 0xFFu) == 0;
-}
-// The buffer holding the elements before the pass on (word, shift) (after
-// all passes: word 1, shift 64).
-__device__ __forceinline__ int sb_in(const SortBufs& s, int in, int word, int shift) {
-  if (!s.ctl) return in;
-  const uint64_t va = s.ctl->or_a ^ s.ctl->and_a, vb = s.ctl->or_b ^ s.ctl->and_b;
-  int ran = 0;
-  for (int sh = 0; sh < 64; sh += 8) {
-    if (word == 0 && sh >= shift) break;
-    ran += ((va >> sh) & 0xFFu) != 0;
-  }
-  if (word == 1)
-    for (int sh = 32; sh < shift; sh += 8) ran += ((vb >> sh) & 0xFFu) != 0;
-  return ran & 1;
-}
 
 __device__ __forceinline__ uint64_t sb_count(const SortBufs& s) {
   if (!s.count_ptr) return s.count_max;
@@ -116,8 +83,6 @@ __device__ __forceinline__ void sb_load(const SortBufs& s, int in, uint64_t e, u
 template <int SRC>
 __global__ __launch_bounds__(kScThreads) void k_sort_hist(SortBufs s, int in, int word, int shift) {
   __shared__ uint32_t s_cnt[256];
-  if (sb_skip(s, word, shift)) return;
-  in = sb_in(s, in, word, shift);
   const uint64_t n = sb_count(s);
   const uint64_t tile = blockIdx.x;
   s_cnt[threadIdx.x] = 0;
@@ -205,12 +170,10 @@ __global__ __launch_bounds__(kScThreads) void k_scan_apply(uint32_t* data, uint6
 // places the stretches, each thread writes its stretch's exclusive prefixes
 // in LDS, and the table goes back with coalesced stores.
 constexpr uint64_t kScSmallMax = 32768;
-__global__ __launch_bounds__(1024) void k_scan_small(uint32_t* data, uint64_t total, SortBufs s,
-                                                     int word, int shift) {
+__global__ __launch_bounds__(1024) void k_scan_small(uint32_t* data, uint64_t total) {
   __shared__ uint32_t s_d[kScSmallMax];
   __shared__ uint32_t s_carry;
   __shared__ uint32_t s_w[16];
-  if (sb_skip(s, word, shift)) return;  // the digit table of a skipped pass
   const uint32_t t = threadIdx.x, n = (uint32_t)total;
   for (uint32_t i = t; i < n; i += 1024) s_d[i] = data[i];
   if (t == 0) s_carry = 0;
@@ -242,9 +205,6 @@ constexpr size_t kScStageBytes = 2 * sizeof(uint64_t) * kScTile;  // dynamic LDS
 template <int SRC>
 __global__ __launch_bounds__(kScThreads) void k_sort_scatter(SortBufs s, int in, int out, int word,
                                                              int shift) {
-  if (sb_skip(s, word, shift)) return;
-  in = sb_in(s, in, word, shift);
-  out = s.ctl ? in ^ 1 : out;
   extern __shared__ __align__(16) uint8_t sc_stage[];
   uint64_t* s_ta = reinterpret_cast<uint64_t*>(sc_stage);
   uint64_t* s_tb = s_ta + kScTile;
@@ -911,11 +871,27 @@ __global__ __launch_bounds__(kScStatThreads) void k_sc_stats(ScopeArgs a) {
 // Section 3.3: a probe's interval (the exposed latency of one operation at
 // one iteration) is joined to the same operation's issue in the same
 // iteration of the reference trace, by identity and scope rather than by
-// timestamp.  The reference instances sorted by (region, context) give, for
-// (operation region, context), a run in which the iteration-th element is
-// the joined instance.  Joined probes are then sorted by (instance,
-// latency), so each group is a run in latency order and its nearest-rank
-// percentiles are read off by position.
+// timestamp: the joined instance is the iteration-th instance of the probe's
+// context with the operation's region.  Joined probes are then sorted by
+// (instance, latency), so each group is a run in latency order and its
+// nearest-rank percentiles are read off by position.
+//
+// Up to kPrIndexRegions regions, an index of the reference is enough to find
+// that instance: per tile of 4096 instances the places of each region's
+// instances (one 16-bit list, in region order) and, per region, the count
+// before each tile.  The instances are in context order, so those of a
+// (context, region) are consecutive among the region's.  The index reads the
+// upper half of every instance once and writes 2 bytes for it; sorting the
+// instances by region, as is done for more regions, reads them twice and
+// writes 16 (on 8.4 M instances 0.07 + 0.03 + 0.12 ms).
+
+constexpr uint32_t kPrIndexRegions = 256;  // one counter per thread of a tile's block
+constexpr uint32_t kPrJoinThreads = 512;
+constexpr uint32_t kPrJoinBlocks = 2048;
+constexpr uint32_t kPrTile = 1024;    // sorted probes per tile of k_pr_groups
+constexpr uint32_t kPrDigits = 12;    // latency bytes 0..7, instance code bytes 0..3
+constexpr uint32_t kPrPhGroups = kPrDigits;  // phase counters: one per sort pass, then the groups' tiles
+constexpr uint32_t kPrCtrWords = (kPrDigits + 1) * kPhaseWords;
 
 struct ProbeArgs {
   const argus_instance* inst;
@@ -923,69 +899,285 @@ struct ProbeArgs {
   uint64_t np;
   uint32_t R;
   uint64_t none;        // instance code of a probe that joined nothing (= max instances)
-  SortBufs ref;         // the reference sorted by (region, context)
+  SortBufs ref;         // R > kPrIndexRegions: the reference sorted by (region, context)
   int ref_buf;
-  SortBufs pb;          // the probes sorted by (instance, latency)
+  // the index of the reference; its counts [R][ref.tiles_max] are in ref.hist
+  uint16_t* list;       // [tiles][4096] places in the tile, in region order
+  uint16_t* lstart;     // [tiles][R] where each region starts in the tile's list
+  uint32_t* tctx;       // [tiles] first context
+  uint32_t* rtot;       // [R] instances of each region
+  // the probes' sort: key = latency, ctxw = instance code
+  RadixArgs r;
+  uint32_t* dig;        // [kPrDigits][256] digit counts
+  uint64_t* scan;       // [tiles of k_pr_groups] look-back words
+  uint32_t* bcnt;       // [join blocks][4] bad, joined, unjoined
+  uint32_t jblocks;
   uint32_t* ref_out;
   uint64_t* completion;
-  uint32_t* flags;      // group heads, then their exclusive scan
   uint64_t* groups;     // [np][ARGUS_PG_WIDTH]
   double* mean;
   uint64_t* counters;
-  uint64_t* vpart;      // [join blocks][4] each block's ORs and ANDs of the sort words
 };
 
-__global__ void k_pr_init(ProbeArgs a) {
-  if (threadIdx.x < ARGUS_PR_NUM_COUNTERS) a.counters[threadIdx.x] = 0;
-
+__global__ __launch_bounds__(kScThreads) void k_pr_init(ProbeArgs a) {
+  const uint64_t i0 = (uint64_t)blockIdx.x * kScThreads + threadIdx.x, stride = (uint64_t)gridDim.x * kScThreads;
+  if (i0 < ARGUS_PR_NUM_COUNTERS) a.counters[i0] = 0;
+  if (a.np == 0) return;
+  if (i0 < 32) a.r.counters[i0] = 0;
+  for (uint64_t i = i0; i < kPrDigits * kRadixBins; i += stride) a.dig[i] = 0;
+  for (uint64_t i = i0; i < kPrCtrWords; i += stride) a.r.ctrs[i] = 0;
+  for (uint64_t i = i0; i < ceil_div(a.np, kPrTile); i += stride) a.scan[i] = 0;
+  for (uint64_t i = i0; i < ceil_div(a.np, kSortTile) * kRadixBins; i += stride) a.r.lb[i] = 0;
 }
 
-__global__ __launch_bounds__(kScThreads) void k_pr_join(ProbeArgs a) {
+// One tile of the index: ranked like a radix pass on the region (each wave
+// takes 1024 consecutive instances), the list staged in LDS.
+__global__ __launch_bounds__(kScThreads) void k_pr_index(ProbeArgs a) {
+  __shared__ uint32_t s_wave[4][256];
+  __shared__ uint32_t s_lstart[256];
+  __shared__ uint32_t s_w[kScThreads / 64];
+  __shared__ uint32_t s_carry;
+  __shared__ __align__(16) uint16_t s_list[kScTile];
+  const uint64_t n = sb_count(a.ref), tile = blockIdx.x, base = tile * kScTile;
+  if (base >= n) return;
+  const uint32_t cnt = n - base < (uint64_t)kScTile ? (uint32_t)(n - base) : kScTile;
+  const uint4* inst = reinterpret_cast<const uint4*>(a.inst);
+  const uint32_t tid = threadIdx.x, w = tid >> 6, lane = tid & 63;
+  uint32_t reg[kScRounds], rk[kScRounds];
+  const uint32_t e0 = w * (kScRounds * 64) + lane;
+#pragma unroll
+  for (int r = 0; r < kScRounds; ++r) {
+    const uint32_t e = e0 + (uint32_t)r * 64;
+    const uint4 h1 = inst[2 * (base + (e < cnt ? e : cnt - 1)) + 1];
+    reg[r] = h1.w & 0xFFFFu;
+    if (r == 0 && tid == 0) a.tctx[tile] = h1.x;
+  }
+#pragma unroll
+  for (int q = 0; q < 4; ++q) s_wave[q][tid] = 0;
+  if (tid == 0) s_carry = 0;
+  __syncthreads();
+  const uint32_t rbits = a.R > 1 ? 32u - (uint32_t)__clz(a.R - 1) : 1u;
+  const uint64_t lt = lanemask_lt();
+#pragma unroll
+  for (int r = 0; r < kScRounds; ++r) {
+    // an instance of another R (its region is not below this one) is in no list
+    const bool valid = e0 + (uint32_t)r * 64 < cnt && reg[r] < a.R;
+    const uint32_t d = valid ? reg[r] : 0u;
+    uint64_t peers = __ballot(valid);
+    for (uint32_t bit = 0; bit < rbits; ++bit) {
+      const bool set = (d >> bit) & 1u;
+      const uint64_t bal = __ballot(set);
+      peers &= set ? bal : ~bal;
+    }
+    uint32_t rank = 0;
+    if (valid) {
+      const uint32_t old = s_wave[w][d];
+      rank = old + (uint32_t)__popcll(peers & lt);
+      __builtin_amdgcn_wave_barrier();
+      if ((peers >> lane) == 1ull) s_wave[w][d] = old + (uint32_t)__popcll(peers);
+    }
+    __builtin_amdgcn_wave_barrier();
+    rk[r] = valid ? rank : 0xFFFFFFFFu;
+  }
+  __syncthreads();
+  uint32_t c = 0;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const uint32_t v = s_wave[q][tid];
+    s_wave[q][tid] = c;
+    c += v;
+  }
+  const uint32_t ls = block_excl_scan<kScThreads>(c, s_w, &s_carry);
+  s_lstart[tid] = ls;
+  if (tid < a.R) {
+    a.ref.hist[(uint64_t)tid * a.ref.tiles_max + tile] = c;
+    a.lstart[tile * a.R + tid] = (uint16_t)ls;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int r = 0; r < kScRounds; ++r)
+    if (rk[r] != 0xFFFFFFFFu) s_list[s_lstart[reg[r]] + s_wave[w][reg[r]] + rk[r]] = (uint16_t)(e0 + (uint32_t)r * 64);
+  __syncthreads();
+  // (the list's end past the tile's valid instances is never read)
+  uint4* dst = reinterpret_cast<uint4*>(a.list + tile * kScTile);
+  const uint4* src = reinterpret_cast<const uint4*>(s_list);
+  for (uint32_t i = tid; i < (s_carry + 7) / 8; i += kScThreads) dst[i] = src[i];
+}
+
+// Per region (a block), its instances before each tile, in place of the
+// tiles' counts, and its total.
+__global__ __launch_bounds__(1024) void k_pr_rscan(ProbeArgs a) {
+  __shared__ uint32_t s_carry;
+  __shared__ uint32_t s_w[16];
+  const uint64_t T = ceil_div(sb_count(a.ref), kScTile);
+  uint32_t* row = a.ref.hist + (uint64_t)blockIdx.x * a.ref.tiles_max;
+  if (threadIdx.x == 0) s_carry = 0;
+  __syncthreads();
+  for (uint64_t t0 = 0; t0 < T; t0 += 1024) {
+    const uint64_t t = t0 + threadIdx.x;
+    const uint32_t v = t < T ? row[t] : 0u;
+    const uint32_t ex = block_excl_scan<1024>(v, s_w, &s_carry);
+    if (t < T) row[t] = ex;
+  }
+  if (threadIdx.x == 0) a.rtot[blockIdx.x] = s_carry;
+}
+
+struct PrJoinShared {
+  uint32_t hist[kPrDigits * kRadixBins];
+  uint32_t cnt[kPrJoinThreads / 64][3];
+};
+
+// A probe's outputs and sort element (x: the joined instance, or a.none).
+// Every lane with a probe of the wave calls it together.
+__device__ __forceinline__ void pr_emit(const ProbeArgs& a, PrJoinShared& s, uint32_t nd_code, uint64_t j,
+                                        uint64_t x, uint64_t lat_in) {
+  const bool hit = x != a.none;
+  const uint64_t lat = hit ? lat_in : 0ull;
+  uint64_t done = kU64Max;
+  if (hit) {
+    const uint4 ib = reinterpret_cast<const uint4*>(a.inst)[2 * x];
+    done = ((uint64_t)ib.x | ((uint64_t)ib.y << 32)) + lat;
+  }
+  a.ref_out[j] = hit ? (uint32_t)x : 0xFFFFFFFFu;
+  a.completion[j] = done;
+  a.r.key[0][j] = lat;
+  a.r.ctxw[0][j] = (uint32_t)x;
+  for (uint32_t d = 0; d < 8; ++d) hist_digit(s.hist + d * kRadixBins, (uint32_t)(lat >> (8 * d)) & 0xFFu, true);
+  for (uint32_t d = 0; d < nd_code; ++d)
+    hist_digit(s.hist + (8 + d) * kRadixBins, (uint32_t)(x >> (8 * d)) & 0xFFu, true);
+}
+
+// Bytes of the instance codes.
+__device__ __forceinline__ uint32_t pr_code_digits(const ProbeArgs& a) { return (bit_width64(a.none | 1ull) + 7) / 8; }
+
+__device__ __forceinline__ void pr_join_begin(PrJoinShared& s) {
+  for (uint32_t i = threadIdx.x; i < kPrDigits * kRadixBins; i += kPrJoinThreads) s.hist[i] = 0;
+  __syncthreads();
+}
+
+// The block's digit counts, and its probe counts (added up by k_pr_groups:
+// an atomic per wave on one counter takes 5 ns each, one after another).
+__device__ __forceinline__ void pr_join_end(const ProbeArgs& a, PrJoinShared& s, uint32_t bad, uint32_t joined,
+                                            uint32_t unjoined) {
+  const uint32_t v[3] = {bad, joined, unjoined};
+#pragma unroll
+  for (int q = 0; q < 3; ++q) {
+    const uint32_t t = rows_sum32(row_sum32(v[q]));
+    if ((threadIdx.x & 63) == 0) s.cnt[threadIdx.x >> 6][q] = t;
+  }
+  __syncthreads();
+  for (uint32_t i = threadIdx.x; i < kPrDigits * kRadixBins; i += kPrJoinThreads)
+    if (s.hist[i]) atomicAdd(&a.dig[i], s.hist[i]);
+  if (threadIdx.x < 3) {
+    uint32_t t = 0;
+    for (uint32_t q = 0; q < kPrJoinThreads / 64; ++q) t += s.cnt[q][threadIdx.x];
+    a.bcnt[4 * blockIdx.x + threadIdx.x] = t;
+  }
+}
+
+// The join by the index: the context's first instance (a search over the
+// tiles' first contexts, then within a tile), the region's instances before
+// it, and from the target's number among the region's instances its tile and
+// its place.  One probe per thread: the searches are short and mostly in the
+// caches.
+__global__ __launch_bounds__(kPrJoinThreads) void k_pr_join_index(ProbeArgs a) {
+  __shared__ PrJoinShared s;
+  pr_join_begin(s);
+  const uint64_t n = sb_count(a.ref);
+  const uint32_t T = (uint32_t)ceil_div(n, kScTile);
+  const uint32_t* iw = reinterpret_cast<const uint32_t*>(a.inst);  // 8 words per instance; 4: context
+  const uint32_t nd_code = pr_code_digits(a);
+  uint32_t bad = 0, joined = 0, unjoined = 0;
+  for (uint64_t j = (uint64_t)blockIdx.x * kPrJoinThreads + threadIdx.x; j < a.np;
+       j += (uint64_t)gridDim.x * kPrJoinThreads) {
+    const uint4 g0 = a.probes[2 * j], g1 = a.probes[2 * j + 1];
+    const uint64_t ts = (uint64_t)g0.x | ((uint64_t)g0.y << 32), te = (uint64_t)g0.z | ((uint64_t)g0.w << 32);
+    const uint32_t ctx = g1.x, it = g1.y, op = g1.z & 0xFFFFu;
+    const bool ok = !(te < ts || op >= a.R);
+    uint64_t x = a.none;
+    if (ok && n) {
+      uint32_t lo = 0, hi = T;  // first tile whose first context is not below ctx
+      while (lo < hi) {
+        const uint32_t m = (lo + hi) >> 1;
+        if (a.tctx[m] < ctx) lo = m + 1;
+        else hi = m;
+      }
+      const uint32_t t0 = lo > 0 ? lo - 1 : 0u;
+      const uint64_t b0 = (uint64_t)t0 * kScTile;
+      // the context's first instance lies in tile t0 or starts the next one
+      uint32_t l0 = 0, l1 = lo > 0 ? (n - b0 < (uint64_t)kScTile ? (uint32_t)(n - b0) : kScTile) : 0u;
+      while (l0 < l1) {
+        const uint32_t m = (l0 + l1) >> 1;
+        if (iw[8 * (b0 + m) + 4] < ctx) l0 = m + 1;
+        else l1 = m;
+      }
+      // the region's instances before it
+      const uint32_t* row = a.ref.hist + (uint64_t)op * a.ref.tiles_max;
+      const uint32_t tot = a.rtot[op], c0 = row[t0], c1 = t0 + 1 < T ? row[t0 + 1] : tot;
+      const uint16_t* ll = a.list + b0 + a.lstart[(uint64_t)t0 * a.R + op];
+      uint32_t k0 = 0, k1 = c1 - c0;
+      while (k0 < k1) {
+        const uint32_t m = (k0 + k1) >> 1;
+        if (ll[m] < l0) k0 = m + 1;
+        else k1 = m;
+      }
+      const uint64_t target = (uint64_t)c0 + k0 + it;
+      if (target < tot) {
+        // the last tile with at most `target` before it, galloping from t0
+        uint64_t a0 = t0, a1 = (uint64_t)t0 + 1, step = 1;
+        while (a1 < T && row[a1] <= target) {
+          a0 = a1;
+          step *= 2;
+          a1 = a0 + step;
+        }
+        if (a1 > T) a1 = T;
+        while (a0 + 1 < a1) {
+          const uint64_t m = (a0 + a1) >> 1;
+          if (row[m] <= target) a0 = m;
+          else a1 = m;
+        }
+        const uint64_t at = a0 * kScTile + a.lstart[a0 * a.R + op] + (uint32_t)(target - row[a0]);
+        const uint64_t y = a0 * kScTile + a.list[at];
+        if (iw[8 * y + 4] == ctx) x = y;
+      }
+    }
+    bad += !ok;
+    joined += ok && x != a.none;
+    unjoined += ok && x == a.none;
+    pr_emit(a, s, nd_code, j, x, te - ts);
+  }
+  pr_join_end(a, s, bad, joined, unjoined);
+}
+
+// The join by the sorted reference (more than kPrIndexRegions regions): for
+// (operation region, context) a run, found by a binary search, in which the
+// iteration-th element is the joined instance.
+__global__ __launch_bounds__(kPrJoinThreads) void k_pr_join(ProbeArgs a) {
+  __shared__ PrJoinShared s;
+  pr_join_begin(s);
   const uint64_t nref = sb_count(a.ref);
   const uint64_t* ra = a.ref.a[a.ref_buf];
   const uint64_t* rb = a.ref.b[a.ref_buf];
+  const uint32_t nd_code = pr_code_digits(a);
   uint32_t bad = 0, joined = 0, unjoined = 0;
-  // the OR and the AND of the sort words (latency; instance code << 32)
-  uint64_t oa = 0, na = ~0ull, ob = 0, nb2 = ~0ull;
   // Two probes per thread (j and j + stride), their reference searches in
   // lockstep: each search is a chain of dependent loads, and two chains per
   // lane keep more in flight.
-  const uint64_t stride = (uint64_t)gridDim.x * kScThreads;
-  auto finish = [&](uint64_t j, uint64_t ts, uint64_t te, uint32_t ctx, uint32_t op, bool ok,
-                    uint64_t tgt) {
-    uint64_t code = a.none, lat = 0, done = kU64Max;
-    if (!ok) {
-      bad += 1;
-    } else {
-      // both words of the target loaded together (index clamped; nref == 0
-      // loads nothing)
-      uint64_t av = ~0ull, bv = 0;
-      if (nref) {
-        const uint64_t tc = tgt < nref ? tgt : nref - 1;
-        av = ra[tc];
-        bv = rb[tc];
-      }
-      if ((tgt < nref) & (av == op) & ((uint32_t)(bv >> 32) == ctx)) {
-        const uint32_t x = (uint32_t)bv;
-        lat = te - ts;
-        const uint4 ib = reinterpret_cast<const uint4*>(a.inst)[2 * (uint64_t)x];
-        done = ((uint64_t)ib.x | ((uint64_t)ib.y << 32)) + lat;
-        code = x;
-        joined += 1;
-      } else {
-        unjoined += 1;
-      }
+  const uint64_t stride = (uint64_t)gridDim.x * kPrJoinThreads;
+  auto finish = [&](uint64_t j, uint64_t lat, uint32_t ctx, uint32_t op, bool ok, uint64_t tgt) {
+    uint64_t x = a.none;
+    if (ok && nref) {
+      // both words of the target loaded together (index clamped)
+      const uint64_t tc = tgt < nref ? tgt : nref - 1;
+      const uint64_t av = ra[tc], bv = rb[tc];
+      if ((tgt < nref) & (av == op) & ((uint32_t)(bv >> 32) == ctx)) x = (uint32_t)bv;
     }
-    a.ref_out[j] = code == a.none ? 0xFFFFFFFFu : (uint32_t)code;
-    a.completion[j] = done;
-    a.pb.a[0][j] = lat;
-    a.pb.b[0][j] = (code << 32) | j;
-    oa |= lat;
-    na &= lat;
-    ob |= code << 32;
-    nb2 &= code << 32;
+    bad += !ok;
+    joined += ok && x != a.none;
+    unjoined += ok && x == a.none;
+    pr_emit(a, s, nd_code, j, x, lat);
   };
-  for (uint64_t j = (uint64_t)blockIdx.x * kScThreads + threadIdx.x; j < a.np; j += 2 * stride) {
+  for (uint64_t j = (uint64_t)blockIdx.x * kPrJoinThreads + threadIdx.x; j < a.np; j += 2 * stride) {
     const uint64_t j1 = j + stride;
     const bool has1 = j1 < a.np;
     const uint4 g0 = a.probes[2 * j], g1 = a.probes[2 * j + 1];
@@ -1013,129 +1205,144 @@ __global__ __launch_bounds__(kScThreads) void k_pr_join(ProbeArgs a) {
         else hi1 = m1;
       }
     }
-    finish(j, ts0, te0, ctx0, op0, ok0, lo0 + it0);
-    if (has1) finish(j1, ts1, te1, ctx1, op1, ok1, lo1 + it1);
+    finish(j, te0 - ts0, ctx0, op0, ok0, lo0 + it0);
+    if (has1) finish(j1, te1 - ts1, ctx1, op1, ok1, lo1 + it1);
   }
-  {
-    // the block's OR and AND, combined over the blocks by k_pr_vary
-    __shared__ uint64_t s_v[kScThreads / 64][4];
+  pr_join_end(a, s, bad, joined, unjoined);
+}
+
+// The probes in (instance code, latency) order: stable passes over the
+// latency's bytes and then the code's, those whose byte is the same for every
+// probe left out, as phases of one kernel.  (A launch for each of three
+// kernels per possible pass took 0.30 ms over 491,520 probes, most of it for
+// passes with nothing to do.)  Which buffer holds the result goes to word 0
+// of the flags.
+__global__ __launch_bounds__(kSortThreads, 4) void k_pr_sort(ProbeArgs a) {
+  __shared__ RadixShared s;
+  KeySpace ks{};
+  ks.ts_bits = 64;
+  ks.wide = 1;
+  uint32_t act = digits_varying<8>(a.dig, 8);
+  act |= digits_varying<4>(a.dig + 8 * kRadixBins, 4) << 8;
+  uint32_t src = 0;
+  for (uint32_t d = 0; d < kPrDigits; ++d) {
+    if (!((act >> d) & 1u)) continue;
+    RadixPass ps;
+    ps.src = src;
+    ps.dst = src ^ 1u;
+    ps.mode = d < 8 ? kDigKey : kDigCtx;
+    ps.shift = 8 * (d & 7u);
+    ps.tag = 1 + d;
+    ps.n_out = (uint32_t)a.np;
+    ps.n_elems = a.np;
+    radix_offsets(s, a.dig + d * kRadixBins);
+    bool fin;
+    const uint32_t mine = radix_phase<3>(a.r, s, ks, ps, d, (act >> (d + 1)) == 0, &fin);
+    src = ps.dst;
+    // (the last pass only: an earlier one's block may come here late)
+    if (fin && threadIdx.x == 0 && (act >> (d + 1)) == 0) a.r.counters[0] = src;
+    if (!mine) return;
+  }
+}
+
+// Tiles of 1024 sorted probes in order: the group heads (the number of the
+// first from a look-back over the tiles), and for each its group's count,
+// sum, issue time, mean and nearest-rank percentiles (its latencies are in
+// increasing order).
+__global__ __launch_bounds__(kScThreads) void k_pr_groups(ProbeArgs a) {
+  __shared__ uint32_t s_slot, s_w[kScThreads / 64], s_ex;
+  constexpr uint32_t kPer = kPrTile / kScThreads;
+  const uint32_t buf = (uint32_t)a.r.counters[0];
+  const uint64_t* la = a.r.key[buf];
+  const uint32_t* code = a.r.ctxw[buf];
+  const uint32_t tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const uint32_t tiles = (uint32_t)ceil_div(a.np, kPrTile), none = (uint32_t)a.none;
+  const uint64_t lt = lanemask_lt();
+  for (;;) {
+    const uint32_t tile = phase_take(phase_ctr(a.r.ctrs, kPrPhGroups), &s_slot);
+    if (tile >= tiles) break;
+    const uint64_t k0 = (uint64_t)tile * kPrTile + w * (kPer * 64) + lane;
+    uint32_t c[kPer];
+    uint64_t hm[kPer];
+    uint32_t heads = 0;
 #pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) {
-      oa |= (uint64_t)__shfl_xor((long long)oa, d);
-      na &= (uint64_t)__shfl_xor((long long)na, d);
-      ob |= (uint64_t)__shfl_xor((long long)ob, d);
-      nb2 &= (uint64_t)__shfl_xor((long long)nb2, d);
+    for (uint32_t q = 0; q < kPer; ++q) {
+      const uint64_t k = k0 + 64 * q;
+      c[q] = k < a.np ? code[k] : none;
+      const uint32_t before = k > 0 && k < a.np ? code[k - 1] : none;
+      hm[q] = __ballot(c[q] != none && (k == 0 || before != c[q]));
+      heads += (uint32_t)__popcll(hm[q]);
     }
-    const uint32_t wv = threadIdx.x >> 6;
-    if ((threadIdx.x & 63) == 0) {
-      s_v[wv][0] = oa;
-      s_v[wv][1] = na;
-      s_v[wv][2] = ob;
-      s_v[wv][3] = nb2;
+    if (lane == 0) s_w[w] = heads;
+    __syncthreads();
+    uint32_t wpre = 0, total = 0;
+#pragma unroll
+    for (uint32_t q = 0; q < kScThreads / 64; ++q) {
+      wpre += q < w ? s_w[q] : 0u;
+      total += s_w[q];
+    }
+    if (w == 0) {
+      const uint32_t ex = (uint32_t)scan_lookback(a.scan, tile, total, a.r.counters);
+      if (lane == 0) s_ex = ex;
     }
     __syncthreads();
-    if (threadIdx.x < 4) {
-      uint64_t v = s_v[0][threadIdx.x];
-      for (int q = 1; q < kScThreads / 64; ++q)
-        v = (threadIdx.x & 1) ? (v & s_v[q][threadIdx.x]) : (v | s_v[q][threadIdx.x]);
-      a.vpart[4 * (uint64_t)blockIdx.x + threadIdx.x] = v;
+    uint64_t g = (uint64_t)s_ex + wpre;
+    if (tile + 1 == tiles && tid == 0) {
+      a.counters[ARGUS_PR_N_PROBES] = a.np;
+      a.counters[ARGUS_PR_N_GROUPS] = (uint64_t)s_ex + total;
+    }
+#pragma unroll
+    for (uint32_t q = 0; q < kPer; ++q) {
+      const uint64_t k = k0 + 64 * q;
+      if ((hm[q] >> lane) & 1u) {
+        const uint32_t r = c[q];
+        // end of the run: the first position whose code exceeds r, galloping
+        uint64_t lo = k + 1, step = 1, hi = k + 2;
+        while (hi <= a.np && code[hi - 1] == r) {
+          lo = hi;
+          step *= 2;
+          hi = lo + step;
+        }
+        if (hi > a.np) hi = a.np + 1;
+        while (lo + 1 < hi) {  // code[lo - 1] == r, code[hi - 1] != r (or past the end)
+          const uint64_t m = (lo + hi) >> 1;
+          if (code[m - 1] == r) lo = m;
+          else hi = m;
+        }
+        const uint64_t cnt = lo - k;
+        uint64_t sum = 0;
+#pragma unroll 4
+        for (uint64_t i = k; i < lo; ++i) sum += la[i];
+        const uint64_t at = g + (uint32_t)__popcll(hm[q] & lt);
+        uint64_t* row = a.groups + at * ARGUS_PG_WIDTH;
+        row[ARGUS_PG_INSTANCE] = r;
+        row[ARGUS_PG_COUNT] = cnt;
+        row[ARGUS_PG_SUM] = sum;
+        const uint4 ib = reinterpret_cast<const uint4*>(a.inst)[2 * (uint64_t)r];
+        row[ARGUS_PG_ISSUE] = (uint64_t)ib.x | ((uint64_t)ib.y << 32);
+        const uint32_t pq[6] = {0, 20, 40, 60, 80, 100};
+#pragma unroll
+        for (int t = 0; t < 6; ++t) {
+          uint64_t rank = ((uint64_t)pq[t] * cnt + 99) / 100;
+          if (rank < 1) rank = 1;
+          row[ARGUS_PG_P0 + t] = la[k + rank - 1];
+        }
+        a.mean[at] = (double)sum / (double)cnt;
+      }
+      g += (uint32_t)__popcll(hm[q]);
+    }
+    if (tile == 0 && w < 3) {
+      // the join blocks' counts
+      uint64_t t = 0;
+      for (uint32_t b = lane; b < a.jblocks; b += 64) t += a.bcnt[4 * b + w];
+      t = rows_sum64(row_sum64(t));
+      if (lane == 0) a.counters[w == 0 ? ARGUS_PR_N_BAD : w == 1 ? ARGUS_PR_N_JOINED : ARGUS_PR_N_UNJOINED] = t;
     }
   }
-  const uint32_t lane = threadIdx.x & 63;
-  const uint32_t v[3] = {bad, joined, unjoined};
-  const int slot[3] = {ARGUS_PR_N_BAD, ARGUS_PR_N_JOINED, ARGUS_PR_N_UNJOINED};
-#pragma unroll
-  for (int q = 0; q < 3; ++q) {
-    const uint32_t t = rows_sum32(row_sum32(v[q]));
-    if (lane == 0 && t) atomicAdd((unsigned long long*)&a.counters[slot[q]], (unsigned long long)t);
-  }
-  if (blockIdx.x == 0 && threadIdx.x == 0) a.counters[ARGUS_PR_N_PROBES] = a.np;
-}
-
-// The blocks' ORs and ANDs of the probe sort words into the sort state.
-__global__ __launch_bounds__(1024) void k_pr_vary(ProbeArgs a, uint32_t blocks) {
-  __shared__ uint64_t s_v[16][4];
-  uint64_t v[4] = {0, ~0ull, 0, ~0ull};
-  for (uint32_t b = threadIdx.x; b < blocks; b += 1024)
-#pragma unroll
-    for (int k = 0; k < 4; ++k)
-      v[k] = (k & 1) ? (v[k] & a.vpart[4 * (uint64_t)b + k]) : (v[k] | a.vpart[4 * (uint64_t)b + k]);
-#pragma unroll
-  for (int d = 32; d >= 1; d >>= 1)
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const uint64_t o = (uint64_t)__shfl_xor((long long)v[k], d);
-      v[k] = (k & 1) ? (v[k] & o) : (v[k] | o);
-    }
-  const uint32_t w = threadIdx.x >> 6;
-  if ((threadIdx.x & 63) == 0)
-#pragma unroll
-    for (int k = 0; k < 4; ++k) s_v[w][k] = v[k];
-  __syncthreads();
-  if (threadIdx.x < 4) {
-    const int k = threadIdx.x;
-    uint64_t r = s_v[0][k];
-    for (int q = 1; q < 16; ++q) r = (k & 1) ? (r & s_v[q][k]) : (r | s_v[q][k]);
-    uint64_t* c = reinterpret_cast<uint64_t*>(a.pb.ctl);
-    c[k] = r;  // or_a, and_a, or_b, and_b
-  }
-}
-
-__device__ __forceinline__ bool pr_head(const uint64_t* b, uint64_t k, uint64_t none) {
-  const uint64_t r = b[k] >> 32;
-  return r != none && (k == 0 || (b[k - 1] >> 32) != r);
-}
-
-__global__ __launch_bounds__(kScThreads) void k_pr_heads(ProbeArgs a, int buf) {
-  buf = sb_in(a.pb, buf, 1, 64);
-  const uint64_t* b = a.pb.b[buf];
-  uint32_t heads = 0;
-  for (uint64_t k = (uint64_t)blockIdx.x * kScThreads + threadIdx.x; k < a.np;
-       k += (uint64_t)gridDim.x * kScThreads) {
-    const uint32_t h = pr_head(b, k, a.none) ? 1u : 0u;
-    a.flags[k] = h;
-    heads += h;
-  }
-  const uint32_t t = rows_sum32(row_sum32(heads));
-  if ((threadIdx.x & 63) == 0 && t)
-    atomicAdd((unsigned long long*)&a.counters[ARGUS_PR_N_GROUPS], (unsigned long long)t);
-}
-
-// One thread per group head: the group's count, sum, issue time, mean and
-// nearest-rank percentiles (its latencies are in increasing order).
-__global__ __launch_bounds__(kScThreads) void k_pr_groups(ProbeArgs a, int buf) {
-  buf = sb_in(a.pb, buf, 1, 64);
-  const uint64_t* la = a.pb.a[buf];
-  const uint64_t* b = a.pb.b[buf];
-  for (uint64_t k = (uint64_t)blockIdx.x * kScThreads + threadIdx.x; k < a.np;
-       k += (uint64_t)gridDim.x * kScThreads) {
-    if (!pr_head(b, k, a.none)) continue;
-    const uint64_t r = b[k] >> 32;
-    // end of the run: first position whose instance code exceeds r
-    uint64_t lo = k + 1, hi = a.np;
-    while (lo < hi) {
-      const uint64_t mid = (lo + hi) >> 1;
-      if ((b[mid] >> 32) > r) hi = mid;
-      else lo = mid + 1;
-    }
-    const uint64_t cnt = lo - k;
-    uint64_t sum = 0;
-    for (uint64_t i = k; i < lo; ++i) sum += la[i];
-    const uint64_t g = a.flags[k];
-    uint64_t* row = a.groups + g * ARGUS_PG_WIDTH;
-    row[ARGUS_PG_INSTANCE] = r;
-    row[ARGUS_PG_COUNT] = cnt;
-    row[ARGUS_PG_SUM] = sum;
-    const uint4 ib = reinterpret_cast<const uint4*>(a.inst)[2 * r];
-    row[ARGUS_PG_ISSUE] = (uint64_t)ib.x | ((uint64_t)ib.y << 32);
-    const uint32_t q[6] = {0, 20, 40, 60, 80, 100};
-#pragma unroll
-    for (int t = 0; t < 6; ++t) {
-      uint64_t rank = ((uint64_t)q[t] * cnt + 99) / 100;
-      if (rank < 1) rank = 1;
-      row[ARGUS_PG_P0 + t] = la[k + rank - 1];
-    }
-    a.mean[g] = (double)sum / (double)cnt;
+  // (a wait that gave up, which does not happen, shows in the last counter)
+  if (blockIdx.x == 0 && tid == 0) {
+    const uint64_t e = ld_agent(&a.r.counters[31]);
+    if (e) a.counters[ARGUS_PR_NUM_COUNTERS - 1] = e;
   }
 }
 
@@ -1567,21 +1774,30 @@ ScLayout sc_layout(uint64_t max_inst) {
 }
 
 struct PrLayout {
-  SortLayout ref, pr;
-  size_t hist, bsum, flags, ctl, vpart, total;
+  SortLayout ref;
+  size_t hist, bsum, list, lstart, tctx, rtot, key[2], code[2], dig, lb, scan, ctrs, flag, bcnt, total;
 };
 PrLayout pr_layout(uint64_t max_inst, uint64_t np) {
   Carver c;
   PrLayout L{};
+  const uint64_t tiles = tiles_for(max_inst), n = np ? np : 1;
   L.ref = carve_sort(c, max_inst);
-  L.pr = carve_sort(c, np);
-  const uint64_t tiles = std::max(tiles_for(max_inst), tiles_for(np));
   L.hist = c.take(sizeof(uint32_t) * 256 * tiles);
-  const uint64_t sb = std::max(scan_blocks_for(256 * tiles), scan_blocks_for(np));
-  L.bsum = c.take(sizeof(uint32_t) * sb);
-  L.flags = c.take(sizeof(uint32_t) * (np ? np : 1));
-  L.ctl = c.take(sizeof(SortCtl));
-  L.vpart = c.take(sizeof(uint64_t) * 4 * 4096);  // the join's blocks (at most 4096)
+  L.bsum = c.take(sizeof(uint32_t) * scan_blocks_for(256 * tiles));
+  L.list = c.take(sizeof(uint16_t) * kScTile * tiles);
+  L.lstart = c.take(sizeof(uint16_t) * 256 * tiles);
+  L.tctx = c.take(sizeof(uint32_t) * tiles);
+  L.rtot = c.take(sizeof(uint32_t) * 256);
+  for (int k = 0; k < 2; ++k) {
+    L.key[k] = c.take(sizeof(uint64_t) * n);
+    L.code[k] = c.take(sizeof(uint32_t) * n);
+  }
+  L.dig = c.take(sizeof(uint32_t) * kPrDigits * kRadixBins);
+  L.lb = c.take(sizeof(uint64_t) * kRadixBins * ceil_div(n, kSortTile));
+  L.scan = c.take(sizeof(uint64_t) * ceil_div(n, kPrTile));
+  L.ctrs = c.take(sizeof(uint32_t) * kPrCtrWords);
+  L.flag = c.take(sizeof(uint64_t) * 32);
+  L.bcnt = c.take(sizeof(uint32_t) * 4 * kPrJoinBlocks);
   L.total = c.o;
   return L;
 }
@@ -1602,12 +1818,9 @@ SortBufs make_bufs(char* base, const SortLayout& L, size_t hist, size_t bsum, ui
   return s;
 }
 
-void scan_u32(uint32_t* data, uint64_t total, uint32_t* bsum, hipStream_t st,
-              const SortBufs* sk = nullptr, int word = 0, int shift = 0) {
+void scan_u32(uint32_t* data, uint64_t total, uint32_t* bsum, hipStream_t st) {
   if (total <= kScSmallMax) {
-    SortBufs none{};
-    hipLaunchKernelGGL(k_scan_small, dim3(1), dim3(1024), 0, st, data, total, sk ? *sk : none,
-                       word, shift);
+    hipLaunchKernelGGL(k_scan_small, dim3(1), dim3(1024), 0, st, data, total);
     return;
   }
   const uint32_t blocks = (uint32_t)scan_blocks_for(total ? total : 1);
@@ -1627,7 +1840,7 @@ void sort_pass(const SortBufs& s, bool from_inst, int in, int out, int word, int
   else
     hipLaunchKernelGGL(k_sort_hist<kSrcBuf>, dim3(tiles), dim3(kScThreads), 0, st, s, in, word,
                        shift);
-  scan_u32(s.hist, 256ull * s.tiles_max, s.bsum, st, &s, word, shift);
+  scan_u32(s.hist, 256ull * s.tiles_max, s.bsum, st);
   if (from_inst)
     hipLaunchKernelGGL(k_sort_scatter<kSrcInst>, dim3(tiles), dim3(kScThreads), kScStageBytes, st, s,
                        in, out, word, shift);
@@ -1637,10 +1850,10 @@ void sort_pass(const SortBufs& s, bool from_inst, int in, int out, int word, int
 }
 
 // The instances sorted by (BEGIN region, context), canonical order kept
-// within; returns the buffer holding the result.
-int sort_reference(const SortBufs& s, uint32_t R, hipStream_t st) {
+// within (more than 256 regions: two digits); returns the buffer holding the
+// result.
+int sort_reference(const SortBufs& s, hipStream_t st) {
   sort_pass(s, true, 0, 0, 0, 0, st);
-  if (R <= 256) return 0;
   sort_pass(s, false, 0, 1, 0, 8, st);
   return 1;
 }
@@ -1744,7 +1957,7 @@ extern "C" int argus_attr_scope(const argus_scope_config* cfg, const argus_scope
                        dim3(kScThreads), 0, st, a);
     a.hkey = reinterpret_cast<uint32_t*>(a.s.b[1]);  // the sort buffers are free
   } else {
-    const int buf = sort_reference(a.s, a.R, st);
+    const int buf = sort_reference(a.s, st);
     a.pairs = a.s.a[buf ^ 1];  // free once the sort is done
     hipLaunchKernelGGL(k_sc_ordinal, dim3(sc_grid(io->max_instances, kScTile, 2048)),
                        dim3(kScThreads), 0, st, a, buf);
@@ -1810,34 +2023,42 @@ extern "C" int argus_attr_probes(const argus_probes_config* cfg, const argus_pro
   a.none = io->max_instances;
   a.ref = make_bufs(base, L.ref, L.hist, L.bsum, io->max_instances, io->d_n_instances,
                     io->d_instances);
-  a.pb = make_bufs(base, L.pr, L.hist, L.bsum, io->n_probes, nullptr, io->d_instances);
-  a.pb.ctl = reinterpret_cast<SortCtl*>(base + L.ctl);  // passes on constant digits are skipped
-  a.vpart = reinterpret_cast<uint64_t*>(base + L.vpart);
+  a.list = (uint16_t*)(base + L.list);
+  a.lstart = (uint16_t*)(base + L.lstart);
+  a.tctx = (uint32_t*)(base + L.tctx);
+  a.rtot = (uint32_t*)(base + L.rtot);
+  for (int k = 0; k < 2; ++k) {
+    a.r.key[k] = (uint64_t*)(base + L.key[k]);
+    a.r.ctxw[k] = (uint32_t*)(base + L.code[k]);
+  }
+  a.dig = (uint32_t*)(base + L.dig);
+  a.r.lb = (uint64_t*)(base + L.lb);
+  a.scan = (uint64_t*)(base + L.scan);
+  a.r.ctrs = (uint32_t*)(base + L.ctrs);
+  a.r.counters = (uint64_t*)(base + L.flag);
+  a.bcnt = (uint32_t*)(base + L.bcnt);
   a.ref_out = io->d_ref;
   a.completion = io->d_completion;
-  a.flags = (uint32_t*)(base + L.flags);
   a.groups = io->d_groups;
   a.mean = io->d_mean;
   a.counters = io->d_counters;
   hipStream_t st = (hipStream_t)stream_v;
-  hipLaunchKernelGGL(k_pr_init, dim3(1), dim3(64), 0, st, a);
+  const uint64_t clear = std::max<uint64_t>(ceil_div(a.np, kSortTile) * kRadixBins, kPrDigits * kRadixBins);
+  hipLaunchKernelGGL(k_pr_init, dim3(sc_grid(clear, kScThreads, 2048)), dim3(kScThreads), 0, st, a);
   if (a.np > 0) {
-    a.ref_buf = sort_reference(a.ref, a.R, st);
-    const uint32_t jb = sc_grid(a.np, 2 * kScThreads, 4096);  // two probes per thread
-    hipLaunchKernelGGL(k_pr_join, dim3(jb), dim3(kScThreads), 0, st, a);
-    hipLaunchKernelGGL(k_pr_vary, dim3(1), dim3(1024), 0, st, a, jb);
-    // (instance, latency) order: the latency's eight bytes, then the
-    // instance code's bytes (stable LSD)
-    int in = 0;
-    for (int byte = 0; byte < 8; ++byte, in ^= 1) sort_pass(a.pb, false, in, in ^ 1, 0, 8 * byte, st);
-    const uint32_t code_bits = 64u - (uint32_t)__builtin_clzll(a.none | 1ull);
-    for (uint32_t byte = 0; 8 * byte < code_bits; ++byte, in ^= 1)
-      sort_pass(a.pb, false, in, in ^ 1, 1, 32 + 8 * (int)byte, st);
-    hipLaunchKernelGGL(k_pr_heads, dim3(sc_grid(a.np, kScThreads, 4096)), dim3(kScThreads), 0, st,
-                       a, in);
-    scan_u32(a.flags, a.np, a.pb.bsum, st);
-    hipLaunchKernelGGL(k_pr_groups, dim3(sc_grid(a.np, kScThreads, 4096)), dim3(kScThreads), 0,
-                       st, a, in);
+    if (a.R <= kPrIndexRegions) {
+      const uint32_t tiles = (uint32_t)a.ref.tiles_max;
+      hipLaunchKernelGGL(k_pr_index, dim3(tiles), dim3(kScThreads), 0, st, a);
+      hipLaunchKernelGGL(k_pr_rscan, dim3(a.R), dim3(1024), 0, st, a);
+      a.jblocks = sc_grid(a.np, kPrJoinThreads, kPrJoinBlocks);
+      hipLaunchKernelGGL(k_pr_join_index, dim3(a.jblocks), dim3(kPrJoinThreads), 0, st, a);
+    } else {
+      a.ref_buf = sort_reference(a.ref, st);
+      a.jblocks = sc_grid(a.np, 2 * kPrJoinThreads, kPrJoinBlocks);  // two probes per thread
+      hipLaunchKernelGGL(k_pr_join, dim3(a.jblocks), dim3(kPrJoinThreads), 0, st, a);
+    }
+    hipLaunchKernelGGL(k_pr_sort, dim3(sort_blocks((const void*)k_pr_sort, a.np)), dim3(kSortThreads), 0, st, a);
+    hipLaunchKernelGGL(k_pr_groups, dim3(sc_grid(a.np, kPrTile, 2048)), dim3(kScThreads), 0, st, a);
   }
   return hipGetLastError() == hipSuccess ? ARGUS_OK : ARGUS_E_HIP;
 }

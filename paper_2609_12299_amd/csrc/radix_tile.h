@@ -98,6 +98,20 @@ ARGUS_DEV uint32_t sort_excl_scan(uint32_t v, uint32_t* scratch, uint32_t* total
   return pre + x - v;
 }
 
+// Adds this wave's digits (lanes in `valid`) to an LDS histogram: one atomic
+// when every valid lane holds the same digit, else one per lane.
+__device__ __forceinline__ void hist_digit(uint32_t* hist, uint32_t d, bool valid) {
+  const uint64_t vm = __ballot(valid);
+  if (vm == 0) return;
+  const uint32_t first = (uint32_t)__builtin_ctzll(vm);
+  const uint32_t d0 = (uint32_t)__builtin_amdgcn_readlane((int)d, (int)first);
+  if (__ballot(valid && d == d0) == vm) {
+    if (lane_id() == first) atomicAdd(&hist[d0], (uint32_t)__popcll(vm));
+  } else if (valid) {
+    atomicAdd(&hist[d], 1u);
+  }
+}
+
 // The digits (of N consecutive histograms, the first `nd`) that vary: more
 // than one bin in use.  The same in every thread.
 template <int N>
@@ -128,7 +142,7 @@ ARGUS_DEV void clear_rows(uint64_t* lb, uint64_t r0, uint64_t r1) {
 }
 
 // Records (RAW 1) or overlap events of instances (RAW 2) as the raw source;
-// RAW 0: packed buffers only.
+// RAW 0: packed buffers only; RAW 3: packed buffers without payloads.
 template <int RAW>
 __device__ __forceinline__ void radix_tile(const RadixArgs& a, RadixShared& s, const KeySpace& ks,
                                            const RadixPass& ps, uint64_t tile) {
@@ -155,7 +169,7 @@ __device__ __forceinline__ void radix_tile(const RadixArgs& a, RadixShared& s, c
     const uint64_t rel = wide ? c : (ks.ts_bits >= 64 ? 0ull : (k >> ks.ts_bits));
     return (uint32_t)((ks.ctx_min + rel) >> ps.shift) & 0xFFu;
   };
-  if (RAW == 0 || ps.src < 2) {
+  if (RAW == 0 || RAW == 3 || ps.src < 2) {
     const uint64_t* ksrc = ps.src ? a.key[1] : a.key[0];
     const uint32_t* psrc = ps.src ? a.pay[1] : a.pay[0];
     const uint32_t* csrc = ps.src ? a.ctxw[1] : a.ctxw[0];
@@ -163,7 +177,7 @@ __device__ __forceinline__ void radix_tile(const RadixArgs& a, RadixShared& s, c
     for (int r = 0; r < kSortItems; ++r) {
       const uint64_t e = clamp(elem(r));
       key[r] = ld_agent(&ksrc[e]);
-      pay[r] = ld_agent(&psrc[e]);
+      pay[r] = RAW != 3 ? ld_agent(&psrc[e]) : 0u;
       cw[r] = wide ? ld_agent(&csrc[e]) : 0u;
     }
 #pragma unroll
@@ -322,7 +336,7 @@ __device__ __forceinline__ void radix_tile(const RadixArgs& a, RadixShared& s, c
     if (d < 256) {
       const uint32_t lp = s.start[d] + s.wave[w][d] + rank[r];
       s.key[lp] = key[r];
-      s.pay[lp] = pay[r];
+      if (RAW != 3) s.pay[lp] = pay[r];
       s.cw[lp] = cw[r];
       s.dig[lp] = (uint8_t)d;
     }
@@ -344,7 +358,7 @@ __device__ __forceinline__ void radix_tile(const RadixArgs& a, RadixShared& s, c
       continue;
     }
     st_agent(&kd[gp], s.key[i]);
-    st_agent(&pd[gp], s.pay[i]);
+    if (RAW != 3) st_agent(&pd[gp], s.pay[i]);
     if (wide) st_agent(&cd[gp], s.cw[i]);
   }
   __syncthreads();
