@@ -846,23 +846,34 @@ __global__ __launch_bounds__(kScStatThreads) void k_sc_stats(ScopeArgs a) {
       }
     }
   }
+  // the counters once per block (an atomic per wave on one counter takes 5 ns
+  // each, one after another)
   const uint32_t lane = threadIdx.x & 63;
-  if (a.fast) {
 #pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) {
-      const uint32_t o = __shfl_xor(best, d);
-      best = best > o ? best : o;
-    }
-    if (lane == 0 && best)
-      atomicMax((unsigned long long*)&a.counters[ARGUS_SC_N_ITERATIONS], (unsigned long long)best);
+  for (int d = 32; d >= 1; d >>= 1) {
+    const uint32_t o = __shfl_xor(best, d);
+    best = best > o ? best : o;
   }
+  __shared__ uint32_t s_cnt[6][kScStatThreads / 64];
   const uint32_t v[5] = {c_in, c_m, c_mm, c_u, c_s};
-  const int slot[5] = {ARGUS_SC_N_IN_SCOPE, ARGUS_SC_N_MATCHED, ARGUS_SC_N_MISMATCHED,
-                       ARGUS_SC_N_UNCLOSED, ARGUS_SC_N_SELF_NESTED};
 #pragma unroll
   for (int q = 0; q < 5; ++q) {
     const uint32_t t = rows_sum32(row_sum32(v[q]));
-    if (lane == 0 && t) atomicAdd((unsigned long long*)&a.counters[slot[q]], (unsigned long long)t);
+    if (lane == 0) s_cnt[q][threadIdx.x >> 6] = t;
+  }
+  if (lane == 0) s_cnt[5][threadIdx.x >> 6] = a.fast ? best : 0u;
+  __syncthreads();
+  if (threadIdx.x < 6) {
+    constexpr int slot[6] = {ARGUS_SC_N_IN_SCOPE, ARGUS_SC_N_MATCHED,     ARGUS_SC_N_MISMATCHED,
+                             ARGUS_SC_N_UNCLOSED, ARGUS_SC_N_SELF_NESTED, ARGUS_SC_N_ITERATIONS};
+    unsigned long long t = 0;
+    for (uint32_t q = 0; q < kScStatThreads / 64; ++q) {
+      const uint32_t x = s_cnt[threadIdx.x][q];
+      t = threadIdx.x < 5 ? t + x : (t > x ? t : x);
+    }
+    unsigned long long* dst = (unsigned long long*)&a.counters[slot[threadIdx.x]];
+    if (t && threadIdx.x < 5) atomicAdd(dst, t);
+    else if (t) atomicMax(dst, t);
   }
   if (blockIdx.x == 0 && threadIdx.x == 0) a.counters[ARGUS_SC_N_INSTANCES] = n;
 }
