@@ -1367,6 +1367,8 @@ __global__ __launch_bounds__(kScThreads) void k_pr_groups(ProbeArgs a) {
 // simply the element before it, when that one has level L, the same context
 // and the same parent.
 
+constexpr uint32_t kHoMaxCompact = 4096;  // compaction blocks
+
 struct HandoffArgs {
   const argus_instance* inst;
   const uint64_t* n_inst;
@@ -1375,6 +1377,8 @@ struct HandoffArgs {
   uint32_t* comp;    // instances of level <= L in canonical order
   uint64_t* status;  // [tiles] look-back words of the compaction (count, flags)
   uint32_t* tctr;    // tile counter of the compaction
+  uint32_t* atl;     // [compaction blocks] instances of level L each saw
+  uint32_t cblocks;  // compaction blocks launched
   uint64_t* mtot;    // instances compacted
   uint64_t* pairs;  // [R][R][4]: count, sum, min, max (the output)
   uint32_t* dkey;   // [dumps][kHoSlots]: each pair block's hash table keys (0: empty)
@@ -1408,11 +1412,13 @@ __global__ __launch_bounds__(kScThreads) void k_ho_init(HandoffArgs a) {
 }
 
 // The instances of level <= L compacted in canonical order, in one pass:
-// blocks take tiles of 4096 instances in order (a counter), count the
-// tile's qualifying instances (a ballot per round of 64, the waves' counts
-// through LDS), publish the count, find the count before the tile by
-// decoupled look-back, and write the indices.  The tile holding the last
-// instance records the total.
+// blocks take tiles of 4096 instances in order (a counter; a block takes its
+// next tile once this one's loads are on their way, so that the counter's
+// round trip is hidden: nothing waits for a tile that comes after one still
+// in work), count the tile's qualifying instances (a ballot per round of 64,
+// the waves' counts through LDS), publish the count, find the count before
+// the tile by decoupled look-back, 64 tiles a step, and write the indices.
+// The tile holding the last instance records the total.
 __global__ __launch_bounds__(kScThreads) void k_ho_compact(HandoffArgs a) {
   __shared__ uint32_t s_tile, s_w[kScThreads / 64];
   __shared__ uint64_t s_base;
@@ -1422,8 +1428,10 @@ __global__ __launch_bounds__(kScThreads) void k_ho_compact(HandoffArgs a) {
   const uint32_t tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const uint64_t lt = lanemask_lt();
   uint32_t at = 0;
+  uint32_t nxt = 0;  // (thread 0) the block's next tile
+  if (tid == 0) nxt = atomicAdd(a.tctr, 1u);
   for (;;) {
-    if (tid == 0) s_tile = atomicAdd(a.tctr, 1u);
+    if (tid == 0) s_tile = nxt;
     __syncthreads();
     const uint64_t tile = s_tile;
     if (tile >= T) break;
@@ -1437,6 +1445,7 @@ __global__ __launch_bounds__(kScThreads) void k_ho_compact(HandoffArgs a) {
       const uint64_t x = base + w * (kScRounds * 64) + (uint32_t)r * 64 + lane;
       lv[r] = iw[8 * (x < n ? x : n - 1) + 6];
     }
+    if (tid == 0) nxt = atomicAdd(a.tctr, 1u);
     uint32_t wc = 0;
 #pragma unroll
     for (int r = 0; r < kScRounds; ++r) {
@@ -1455,33 +1464,37 @@ __global__ __launch_bounds__(kScThreads) void k_ho_compact(HandoffArgs a) {
       wpre += q < (int)w ? s_w[q] : 0u;
       cnt += s_w[q];
     }
-    if (tid == 0) {
+    if (w == 0) {
+      // the tile of one wave: 64 predecessors per round trip, nearest first
       uint64_t excl = 0;
-      if (tile == 0) {
-        st_agent(&a.status[0], kFlagIncl | cnt);
-      } else {
-        st_agent(&a.status[tile], kFlagAgg | cnt);
-        int64_t tt = (int64_t)tile - 1;
-        uint32_t spins = 0;
-        while (tt >= 0) {
-          const uint64_t v = ld_agent(&a.status[tt]);
-          const uint64_t f = v & ~kValMask;
-          if (f == 0) {
-            if (++spins > kMaxSpins) {
-              atomicOr((unsigned long long*)&a.counters[ARGUS_HO_INTERNAL], 1ull);
-              break;
-            }
-            backoff();
-            continue;
+      if (lane == 0) st_agent(&a.status[tile], (tile == 0 ? kFlagIncl : kFlagAgg) | cnt);
+      int64_t top = (int64_t)tile - 1;
+      uint32_t spins = 0;
+      while (top >= 0) {
+        const int64_t q = top - (int64_t)lane;
+        const uint64_t v = q >= 0 ? ld_agent(&a.status[q]) : kFlagIncl;
+        const uint64_t f = v & ~kValMask;
+        const uint64_t mi = __ballot(f == kFlagIncl), mn = __ballot(f == 0);
+        const uint32_t ji = mi ? (uint32_t)__builtin_ctzll(mi) : 64u;  // nearest inclusive
+        const uint32_t jn = mn ? (uint32_t)__builtin_ctzll(mn) : 64u;  // nearest not published
+        const bool found = ji < jn;
+        const uint32_t use = found ? ji + 1 : jn;  // lanes [0, use) are summed
+        excl += rows_sum64(row_sum64(lane < use ? (v & kValMask) : 0ull));
+        if (found) break;
+        top -= jn;
+        if (jn == 0) {
+          if (++spins > kMaxSpins) {
+            if (lane == 0) atomicOr((unsigned long long*)&a.counters[ARGUS_HO_INTERNAL], 1ull);
+            break;
           }
-          excl += v & kValMask;
-          if (f == kFlagIncl) break;
-          --tt;
+          backoff();
         }
-        st_agent(&a.status[tile], kFlagIncl | (excl + cnt));
       }
-      s_base = excl;
-      if (tile == T - 1) *a.mtot = excl + cnt;
+      if (lane == 0) {
+        if (tile != 0) st_agent(&a.status[tile], kFlagIncl | (excl + cnt));
+        s_base = excl;
+        if (tile == T - 1) *a.mtot = excl + cnt;
+      }
     }
     __syncthreads();
     uint64_t o = s_base + wpre;
@@ -1493,9 +1506,13 @@ __global__ __launch_bounds__(kScThreads) void k_ho_compact(HandoffArgs a) {
       o += (uint32_t)__popcll(qm[r]);
     }
   }
+  // the block's instances of level L, added up by k_ho_pairs (an atomic per
+  // wave on one counter takes 5 ns each, one after another)
+  __syncthreads();
   const uint32_t tot = rows_sum32(row_sum32(at));
-  if (lane == 0 && tot)
-    atomicAdd((unsigned long long*)&a.counters[ARGUS_HO_N_AT_LEVEL], (unsigned long long)tot);
+  if (lane == 0) s_w[w] = tot;
+  __syncthreads();
+  if (tid == 0) a.atl[blockIdx.x] = s_w[0] + s_w[1] + s_w[2] + s_w[3];
 }
 
 // Successive pairs, aggregated per block in an LDS hash table of (x region,
@@ -1628,12 +1645,25 @@ __global__ __launch_bounds__(kHoThreads) void k_ho_pairs(HandoffArgs a) {
     gaps += ok ? 1 : 0;
     gsum += gap;
   }
-  const uint64_t g1 = rows_sum64(row_sum64(gaps)), g2 = rows_sum64(row_sum64(gsum));
+  // the counters once per block, not per wave; block 0 adds up the
+  // compaction's counts of level L
+  __shared__ uint64_t s_red[3][kHoThreads / 64];
+  uint64_t atl = 0;
+  if (blockIdx.x == 0)
+    for (uint32_t b = threadIdx.x; b < a.cblocks; b += kHoThreads) atl += a.atl[b];
+  const uint64_t g1 = rows_sum64(row_sum64(gaps)), g2 = rows_sum64(row_sum64(gsum)), g3 = rows_sum64(row_sum64(atl));
   if ((threadIdx.x & 63) == 0) {
-    if (g1) atomicAdd((unsigned long long*)&a.counters[ARGUS_HO_N_GAPS], (unsigned long long)g1);
-    if (g2) atomicAdd((unsigned long long*)&a.counters[ARGUS_HO_GAP_SUM], (unsigned long long)g2);
+    s_red[0][threadIdx.x >> 6] = g1;
+    s_red[1][threadIdx.x >> 6] = g2;
+    s_red[2][threadIdx.x >> 6] = g3;
   }
   __syncthreads();
+  if (threadIdx.x < 3) {
+    uint64_t v = 0;
+    for (uint32_t q = 0; q < kHoThreads / 64; ++q) v += s_red[threadIdx.x][q];
+    constexpr int slot[3] = {ARGUS_HO_N_GAPS, ARGUS_HO_GAP_SUM, ARGUS_HO_N_AT_LEVEL};
+    if (v) atomicAdd((unsigned long long*)&a.counters[slot[threadIdx.x]], (unsigned long long)v);
+  }
   for (int i = threadIdx.x; i < 65; i += kHoThreads)
     if (s_hist[i]) atomicAdd((unsigned long long*)&a.hist[i], s_hist[i]);
   uint32_t* dk = a.dkey + (uint64_t)blockIdx.x * kHoSlots;
@@ -2077,7 +2107,7 @@ extern "C" int argus_attr_probes(const argus_probes_config* cfg, const argus_pro
 namespace {
 
 struct HoLayout {
-  size_t comp, status, tctr, mtot, dkey, dval, total;
+  size_t comp, status, tctr, atl, mtot, dkey, dval, total;
 };
 HoLayout ho_layout(uint64_t max_instances, uint32_t R) {
   Carver c;
@@ -2086,6 +2116,7 @@ HoLayout ho_layout(uint64_t max_instances, uint32_t R) {
   L.comp = c.take(sizeof(uint32_t) * m);
   L.status = c.take(sizeof(uint64_t) * tiles_for(m));
   L.tctr = c.take(sizeof(uint32_t));
+  L.atl = c.take(sizeof(uint32_t) * kHoMaxCompact);
   L.mtot = c.take(sizeof(uint64_t));
   L.dkey = c.take(sizeof(uint32_t) * (uint64_t)kHoMaxDumps * kHoSlots);
   L.dval = c.take(sizeof(uint64_t) * 4 * (uint64_t)kHoMaxDumps * kHoSlots);
@@ -2130,6 +2161,7 @@ extern "C" int argus_attr_handoffs(const argus_handoffs_config* cfg, const argus
   a.comp = (uint32_t*)(base + HL.comp);
   a.status = (uint64_t*)(base + HL.status);
   a.tctr = (uint32_t*)(base + HL.tctr);
+  a.atl = (uint32_t*)(base + HL.atl);
   a.mtot = (uint64_t*)(base + HL.mtot);
   a.dkey = (uint32_t*)(base + HL.dkey);
   a.dval = (uint64_t*)(base + HL.dval);
@@ -2145,11 +2177,10 @@ extern "C" int argus_attr_handoffs(const argus_handoffs_config* cfg, const argus
   if (io->max_instances > 0) {
     const uint32_t g = sc_grid(io->max_instances, kScThreads, 4096);
     // resident blocks only: they take the tiles in order
-    hipLaunchKernelGGL(k_ho_compact,
-                       dim3((uint32_t)std::min<uint64_t>(tiles_for(io->max_instances),
-                                                         persistent_blocks((const void*)k_ho_compact,
-                                                                           kScThreads))),
-                       dim3(kScThreads), 0, st, a);
+    a.cblocks = (uint32_t)std::min<uint64_t>(
+        std::min<uint64_t>(tiles_for(io->max_instances), persistent_blocks((const void*)k_ho_compact, kScThreads)),
+        kHoMaxCompact);
+    hipLaunchKernelGGL(k_ho_compact, dim3(a.cblocks), dim3(kScThreads), 0, st, a);
     // resident blocks only (one per compute unit): each stores its table once
     a.dumps = (uint32_t)std::min<uint64_t>(
         std::min<uint64_t>(g, persistent_blocks((const void*)k_ho_pairs, kHoThreads)), kHoMaxDumps);
