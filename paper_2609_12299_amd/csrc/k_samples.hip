@@ -54,6 +54,12 @@ struct SampArgs {
 };
 
 constexpr int kSampThreads = 256;
+// The join's blocks: 16 waves, so that few blocks add to the counters (adds
+// to one line of memory take 5 ns each, one after another: six counters from
+// each of 4096 blocks of 4 waves were 0.1 ms).
+constexpr int kJoinThreads = 1024;
+constexpr int kPcRegs = 4;  // rows of up to 256 regions held in registers (k_s_pc)
+constexpr uint32_t kTotalRegions = 64 * kPcRegs;  // up to here k_s_pc also takes the regions' totals
 
 // Zero the count table and the counters (a fill kernel: no memset node when
 // the caller captures the launch in a graph).
@@ -63,30 +69,16 @@ __global__ __launch_bounds__(kSampThreads) void k_s_clear(SampArgs a) {
   for (uint64_t i = (uint64_t)blockIdx.x * kSampThreads + threadIdx.x; i < total; i += stride)
     a.n[i] = 0;
   if (blockIdx.x == 0 && threadIdx.x < ARGUS_S_NUM_COUNTERS) a.counters[threadIdx.x] = 0;
+  if (a.R <= kTotalRegions)
+    for (uint64_t i = (uint64_t)blockIdx.x * kSampThreads + threadIdx.x; i < a.R; i += stride) a.region_total[i] = 0;
 }
 
-// Sum of a per-thread u64 over the block, added to *dst by one thread.
-__device__ __forceinline__ void block_add(uint64_t v, uint64_t* dst, uint64_t* s_part) {
-  v = row_sum64(v);
-  v = rows_sum64(v);
-  const int w = threadIdx.x >> 6;
-  if ((threadIdx.x & 63) == 0) s_part[w] = v;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    uint64_t t = 0;
-    for (int k = 0; k < kSampThreads / 64; ++k) t += s_part[k];
-    if (t) atomicAdd((unsigned long long*)dst, (unsigned long long)t);
-  }
-  __syncthreads();
-}
-
-__global__ __launch_bounds__(kSampThreads) void k_s_join(SampArgs a) {
-  __shared__ uint64_t s_part[kSampThreads / 64];
+__global__ __launch_bounds__(kJoinThreads) void k_s_join(SampArgs a) {
   const uint64_t avail = *a.n_inst;
   const uint64_t ni = avail < a.max_inst ? avail : a.max_inst;
   const uint4* inst = reinterpret_cast<const uint4*>(a.inst);  // two uint4 per instance
   uint64_t bad = 0, wt = 0, watt = 0, wun = 0, winner = 0, wbadi = 0;
-  const uint64_t stride = (uint64_t)gridDim.x * kSampThreads;
+  const uint64_t stride = (uint64_t)gridDim.x * kJoinThreads;
   // blocks go to the 8 XCDs round-robin: give each XCD a contiguous eighth
   // of the block indices (when the grid divides by 8), so that neighbouring
   // samples, whose searches end in the same lines, share one L2
@@ -137,7 +129,7 @@ __global__ __launch_bounds__(kSampThreads) void k_s_join(SampArgs a) {
   // twice the requests in flight.  The search finds the first instance whose
   // (context, begin time) exceeds the sample's; the key is compared with
   // bitwise operators, so that a level's two loads go out together.
-  for (uint64_t i = (uint64_t)bid * kSampThreads + threadIdx.x; i < a.ns; i += 2 * stride) {
+  for (uint64_t i = (uint64_t)bid * kJoinThreads + threadIdx.x; i < a.ns; i += 2 * stride) {
     const uint64_t i1 = i + stride;
     const bool has1 = i1 < a.ns;
     const uint4 s0 = a.smp[i], s1 = a.smp[has1 ? i1 : i];
@@ -176,23 +168,37 @@ __global__ __launch_bounds__(kSampThreads) void k_s_join(SampArgs a) {
     if (ok0) finish(lo0, ts0, ctx0, pc0, w0);
     if (ok1) finish(lo1, ts1, ctx1, pc1, w1);
   }
-  block_add(bad, &a.counters[ARGUS_S_N_BAD_PC], s_part);
-  block_add(wt, &a.counters[ARGUS_S_W_TOTAL], s_part);
-  block_add(watt, &a.counters[ARGUS_S_W_ATTRIBUTED], s_part);
-  block_add(wun, &a.counters[ARGUS_S_W_UNATTRIBUTED], s_part);
-  block_add(winner, &a.counters[ARGUS_S_W_INNER_UNMATCHED], s_part);
-  block_add(wbadi, &a.counters[ARGUS_S_W_BAD_INSTANCE], s_part);
+  // the block's sums, added by six lanes of one wave in one request
+  constexpr int kWaves = kJoinThreads / 64;
+  __shared__ uint64_t s_part[6][kWaves];
+  const uint64_t v[6] = {bad, wt, watt, wun, winner, wbadi};
+#pragma unroll
+  for (int q = 0; q < 6; ++q) {
+    const uint64_t t = rows_sum64(row_sum64(v[q]));
+    if ((threadIdx.x & 63) == 0) s_part[q][threadIdx.x >> 6] = t;
+  }
+  __syncthreads();
+  if (threadIdx.x < 6) {
+    constexpr int slot[6] = {ARGUS_S_N_BAD_PC,       ARGUS_S_W_TOTAL,           ARGUS_S_W_ATTRIBUTED,
+                             ARGUS_S_W_UNATTRIBUTED, ARGUS_S_W_INNER_UNMATCHED, ARGUS_S_W_BAD_INSTANCE};
+    uint64_t t = 0;
+    for (int q = 0; q < kWaves; ++q) t += s_part[threadIdx.x][q];
+    if (t) atomicAdd((unsigned long long*)&a.counters[slot[threadIdx.x]], (unsigned long long)t);
+  }
   if (blockIdx.x == 0 && threadIdx.x == 0) a.counters[ARGUS_S_N_SAMPLES] = a.ns;
 }
 
 // One wave per PC: T(p), the owners, alpha (one rounded division each) and
-// H(p) (per-lane sums, then a fixed butterfly over the wave).
-constexpr int kPcRegs = 4;  // rows of up to 256 regions held in registers
+// H(p) (per-lane sums, then a fixed butterfly over the wave).  Where a row is
+// held in registers, a lane sees the same regions in every row: their totals
+// are added up on the way and once per block to memory, so that the counts
+// are not read again.
 __global__ __launch_bounds__(kSampThreads) void k_s_pc(SampArgs a) {
   const uint64_t wave = ((uint64_t)blockIdx.x * kSampThreads + threadIdx.x) >> 6;
   const uint64_t nwaves = (uint64_t)gridDim.x * (kSampThreads / 64);
   const uint32_t lane = threadIdx.x & 63;
   uint64_t pairs = 0;
+  uint64_t rt[kPcRegs] = {};
   for (uint64_t p = wave; p < a.P; p += nwaves) {
     const uint64_t* row = a.n + p * a.R;
     double* arow = a.alpha + p * a.R;
@@ -211,6 +217,7 @@ __global__ __launch_bounds__(kSampThreads) void k_s_pc(SampArgs a) {
 #pragma unroll
       for (int k = 0; k < kPcRegs; ++k) {
         if (lane + 64u * k >= a.R) v[k] = 0;
+        rt[k] += v[k];
         t += v[k];
         own += v[k] != 0;
       }
@@ -257,11 +264,30 @@ __global__ __launch_bounds__(kSampThreads) void k_s_pc(SampArgs a) {
     }
     pairs += own;
   }
-  if (lane == 0 && pairs)
-    atomicAdd((unsigned long long*)&a.counters[ARGUS_S_N_PAIRS], (unsigned long long)pairs);
+  __shared__ uint64_t s_pairs[kSampThreads / 64];
+  __shared__ uint64_t s_rt[kSampThreads / 64][kTotalRegions];
+  const uint32_t w = threadIdx.x >> 6;
+  if (lane == 0) s_pairs[w] = pairs;
+  if (a.R <= kTotalRegions) {
+#pragma unroll
+    for (int k = 0; k < kPcRegs; ++k) s_rt[w][lane + 64u * k] = rt[k];
+  }
+  __syncthreads();
+  if (a.R <= kTotalRegions && threadIdx.x < a.R) {
+    static_assert(kSampThreads >= (int)kTotalRegions, "a thread per region");
+    uint64_t t = 0;
+    for (int q = 0; q < kSampThreads / 64; ++q) t += s_rt[q][threadIdx.x];
+    if (t) atomicAdd((unsigned long long*)&a.region_total[threadIdx.x], (unsigned long long)t);
+  }
+  if (threadIdx.x == 0) {
+    uint64_t t = 0;
+    for (int q = 0; q < kSampThreads / 64; ++q) t += s_pairs[q];
+    if (t) atomicAdd((unsigned long long*)&a.counters[ARGUS_S_N_PAIRS], (unsigned long long)t);
+  }
 }
 
-// Per region r: its total count (an integer sum, in any order), and each
+// Per region r: its total count (an integer sum, in any order; with more
+// regions than k_s_pc takes the totals of), and each
 // lifted metric as the products alpha(r, p) * m(p), each rounded, summed in
 // a fixed order (the paper fixes none): 512 strands, strand j adding from +0
 // and in increasing p the products with p mod 512 = j, then the strands
@@ -290,7 +316,7 @@ __global__ __launch_bounds__(kLiftStrands) void k_s_region(SampArgs a) {
   const uint64_t r = (uint64_t)(blockIdx.x % 8) * per + blockIdx.x / 8;
   if (r >= a.R) return;  // the whole block, before any barrier
   const uint32_t j = threadIdx.x, lane = j & 63, w = j >> 6;
-  const bool totals = blockIdx.y == 0;
+  const bool totals = blockIdx.y == 0 && a.R > kTotalRegions;
   const uint32_t k0 = blockIdx.y * kLiftMetrics;
   const uint32_t mk = a.M > k0 ? (a.M - k0 < kLiftMetrics ? a.M - k0 : kLiftMetrics) : 0u;
   const double* m0 = mk > 0 ? a.metrics + (uint64_t)k0 * a.P : nullptr;
@@ -451,12 +477,12 @@ extern "C" int argus_attr_samples(const argus_samples_config* cfg, const argus_s
   hipStream_t s = (hipStream_t)stream_v;
   hipLaunchKernelGGL(k_s_clear, dim3(grid_for(P * R, kSampThreads, 4096)), dim3(kSampThreads), 0,
                      s, a);
-  hipLaunchKernelGGL(k_s_join, dim3(grid_for(a.ns, kSampThreads, 4096)), dim3(kSampThreads), 0, s,
-                     a);
-  hipLaunchKernelGGL(k_s_pc, dim3(grid_for(P, kSampThreads / 64, 4096)), dim3(kSampThreads), 0,
-                     s, a);
+  // (the blocks that fit at once, two per compute unit)
+  hipLaunchKernelGGL(k_s_join, dim3(grid_for(a.ns, kJoinThreads, 512)), dim3(kJoinThreads), 0, s, a);
+  // few enough blocks that their adds to the totals do not queue
+  hipLaunchKernelGGL(k_s_pc, dim3(grid_for(P, kSampThreads / 64, 2048)), dim3(kSampThreads), 0, s, a);
   const uint32_t lift_y = M > 0 ? (uint32_t)((M + kLiftMetrics - 1) / kLiftMetrics) : 1u;
-  hipLaunchKernelGGL(k_s_region, dim3(8 * (uint32_t)((R + 7) / 8), lift_y), dim3(kLiftStrands), 0, s,
+  if (M > 0 || R > kTotalRegions) hipLaunchKernelGGL(k_s_region, dim3(8 * (uint32_t)((R + 7) / 8), lift_y), dim3(kLiftStrands), 0, s,
                      a);
   return hipGetLastError() == hipSuccess ? ARGUS_OK : ARGUS_E_HIP;
 }
