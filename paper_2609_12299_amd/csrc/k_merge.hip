@@ -926,13 +926,6 @@ __device__ __forceinline__ void sweep8(const uint64_t* se, uint32_t d, uint32_t 
   }
 }
 
-// Wave sum of a 64-bit value, result in lane 0.
-__device__ __forceinline__ uint64_t wave_sum64(uint64_t v) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off);
-  return v;
-}
-
 // The sums of a tile are taken by its first kMsThreads threads, each over
 // kMsItems consecutive events: fewer, longer sequential runs mean fewer
 // per-thread partial sums to reduce across the block.
@@ -1417,17 +1410,20 @@ struct OvtArgs {
 };
 
 constexpr int kOvtThreads = 256;
+// Tile records per block: with more than four classes a wave's worth, whose
+// pairs are then spread over the block's threads.
+constexpr int ovt_tiles(int kc) { return kc > 4 ? 64 : kOvtThreads; }
 
-// Per block of 256 tile records: whether a segment starts in it, and the
+// Per block of tile records: whether a segment starts in it, and the
 // class-count deltas since the last start (or of the whole block).
 template <int KC>
-__global__ __launch_bounds__(kOvtThreads) void k_ovt_agg(OvtArgs a) {
+__global__ __launch_bounds__(ovt_tiles(KC)) void k_ovt_agg(OvtArgs a) {
   constexpr int RW = tile_rec_words(KC);
   const DevPlan* p = a.plan;
   if (!p->ev_merge || p->m_rounds == 0) return;
   const uint64_t n_tiles = p->mr[p->m_rounds - 1].n_tiles;
-  const uint64_t tile = (uint64_t)blockIdx.x * kOvtThreads + threadIdx.x;
-  if ((uint64_t)blockIdx.x * kOvtThreads >= n_tiles) return;
+  const uint64_t tile = (uint64_t)blockIdx.x * ovt_tiles(KC) + threadIdx.x;
+  if ((uint64_t)blockIdx.x * ovt_tiles(KC) >= n_tiles) return;
   __shared__ uint32_t s_last;
   __shared__ int64_t s_sum[KC];
   if (threadIdx.x == 0) s_last = 0;
@@ -1457,7 +1453,8 @@ __global__ __launch_bounds__(kOvtThreads) void k_ovt_agg(OvtArgs a) {
 // group's rows.
 template <int KC>
 __global__ __launch_bounds__(kOvtThreads) void k_ovt_final(OvtArgs a) {
-  constexpr int KM = KC <= 2 ? 2 : (KC <= 4 ? 4 : 8);  // stride of the pair index
+  static_assert(KC <= 4, "k_ovt_final_pairs takes more classes");
+  constexpr int KM = KC <= 2 ? 2 : 4;  // stride of the pair index
   constexpr int NP = KC * (KC + 1) / 2;
   constexpr int RW = tile_rec_words(KC);
   const DevPlan* p = a.plan;
@@ -1603,62 +1600,176 @@ __global__ __launch_bounds__(kOvtThreads) void k_ovt_final(OvtArgs a) {
       qq[k] = 0;
     }
   }
-  if constexpr (2 * NP <= 32) {
-    // Tiles of one group are adjacent: per group present in the wave, its
-    // lanes' values are summed across the wave and added once.
-    uint64_t pend = __ballot(in && g < a.G);
-    while (pend) {
-      const uint32_t gc = (uint32_t)__shfl((int)g, __ffsll((unsigned long long)pend) - 1);
-      const uint64_t mine = __ballot(g == gc) & pend;
-      pend &= ~mine;
-      const bool take = (mine >> lane) & 1ull;
-      uint64_t vals[2 * NP];
+  // Tiles of one group are adjacent: per group present in the wave, its
+  // lanes' values are summed across the wave and added once.
+  uint64_t pend = __ballot(in && g < a.G);
+  while (pend) {
+    const uint32_t gc = (uint32_t)__shfl((int)g, __ffsll((unsigned long long)pend) - 1);
+    const uint64_t mine = __ballot(g == gc) & pend;
+    pend &= ~mine;
+    const bool take = (mine >> lane) & 1ull;
+    uint64_t vals[2 * NP];
 #pragma unroll
-      for (int k = 0; k < NP; ++k) {
-        vals[k] = take ? uu[k] : 0ull;
-        vals[NP + k] = take ? qq[k] : 0ull;
-      }
-      uint32_t idx;
-      const uint64_t r = wave_sums64<2 * NP>(vals, &idx);
-      if ((lane & 1u) == 0 && idx < 2u * NP && r) {
-        // pair idx % NP in row order, at its place in a group's rows
-        const uint32_t k = idx < (uint32_t)NP ? idx : idx - NP;
-        uint32_t pi = 0;
-        int kk = 0;
-#pragma unroll
-        for (int x = 0; x < KC; ++x) {
-#pragma unroll
-          for (int y = x; y < KC; ++y, ++kk)
-            if ((uint32_t)kk == k) pi = (uint32_t)pair_index<KM>(x, y);
-        }
-        uint64_t* dst = idx < (uint32_t)NP ? a.ov_u : a.ov_q;
-        atomicAdd((unsigned long long*)&dst[(uint64_t)gc * kSweepQWords + pi], (unsigned long long)r);
-      }
+    for (int k = 0; k < NP; ++k) {
+      vals[k] = take ? uu[k] : 0ull;
+      vals[NP + k] = take ? qq[k] : 0ull;
     }
-    if (in && g >= a.G && g != 0xFFFFFFFFu) flag_internal_error(a.counters, 256);
-    return;
-  }
-  // whole waves of one group add once; everything else per tile
-  const uint32_t g0 = __shfl(g, 0);
-  const bool uniform = __ballot(g != g0) == 0ull;
-  int k = 0;
+    uint32_t idx;
+    const uint64_t r = wave_sums64<2 * NP>(vals, &idx);
+    if ((lane & 1u) == 0 && idx < 2u * NP && r) {
+      // pair idx % NP in row order, at its place in a group's rows
+      const uint32_t k = idx < (uint32_t)NP ? idx : idx - NP;
+      uint32_t pi = 0;
+      int kk = 0;
 #pragma unroll
-  for (int x = 0; x < KC; ++x) {
+      for (int x = 0; x < KC; ++x) {
 #pragma unroll
-    for (int y = x; y < KC; ++y, ++k) {
-      uint64_t uv = uu[k], qv = qq[k];
-      if (uniform) {
-        uv = wave_sum64(uv);
-        qv = wave_sum64(qv);
+        for (int y = x; y < KC; ++y, ++kk)
+          if ((uint32_t)kk == k) pi = (uint32_t)pair_index<KM>(x, y);
       }
-      if ((!uniform || lane == 0) && g < a.G) {
-        const uint64_t at = (uint64_t)g * kSweepQWords + (uint64_t)pair_index<KM>(x, y);
-        if (uv) atomicAdd((unsigned long long*)&a.ov_u[at], (unsigned long long)uv);
-        if (qv) atomicAdd((unsigned long long*)&a.ov_q[at], (unsigned long long)qv);
-      }
+      uint64_t* dst = idx < (uint32_t)NP ? a.ov_u : a.ov_q;
+      atomicAdd((unsigned long long*)&dst[(uint64_t)gc * kSweepQWords + pi], (unsigned long long)r);
     }
   }
   if (in && g >= a.G && g != 0xFFFFFFFFu) flag_internal_error(a.counters, 256);
+}
+
+// The same for more than four classes: one wave finds the counts entering the
+// block's 64 tiles, then each thread takes one class pair over a stretch of
+// them and adds once per group.  (One thread per tile with all pairs took 212
+// registers and up to 72 scattered adds per tile: 0.18 ms over 2^26 records.)
+template <int KC>
+__global__ __launch_bounds__(kOvtThreads) void k_ovt_final_pairs(OvtArgs a) {
+  static_assert(KC > 4, "k_ovt_final takes fewer classes");
+  constexpr int NP = KC * (KC + 1) / 2;
+  constexpr int RW = tile_rec_words(KC);
+  constexpr uint32_t TB = (uint32_t)ovt_tiles(KC);
+  const DevPlan* p = a.plan;
+  if (!p->ev_merge || p->m_rounds == 0) return;
+  const uint64_t n_tiles = p->mr[p->m_rounds - 1].n_tiles;
+  const uint64_t blk0 = (uint64_t)blockIdx.x * TB;
+  if (blk0 >= n_tiles) return;
+  const uint32_t t = threadIdx.x, lane = t & 63;
+  const uint32_t cnt = n_tiles - blk0 < TB ? (uint32_t)(n_tiles - blk0) : TB;
+  __shared__ int64_t s_cin[TB][KC];
+  __shared__ uint32_t s_g[TB], s_always[TB];
+  if (t < 64) {
+    // ---- carry into this block: blocks before it back to a reset
+    int64_t acc[KC];
+#pragma unroll
+    for (int x = 0; x < KC; ++x) acc[x] = 0;
+    int64_t top = (int64_t)blockIdx.x - 1;
+    while (top >= 0) {
+      const int64_t bb = top - (int64_t)lane;
+      uint32_t reset = 1;  // before block 0: nothing
+      int64_t val[KC];
+#pragma unroll
+      for (int x = 0; x < KC; ++x) val[x] = 0;
+      if (bb >= 0) {
+        const int64_t* b = a.blk + (uint64_t)bb * (1 + KC);
+        reset = b[0] != 0;
+#pragma unroll
+        for (int x = 0; x < KC; ++x) val[x] = b[1 + x];
+      }
+      const uint64_t mr = __ballot(reset);
+      const int jr = mr ? __ffsll((unsigned long long)mr) - 1 : 64;  // nearest reset
+#pragma unroll
+      for (int x = 0; x < KC; ++x) {
+        int64_t vv = (int)lane <= jr ? val[x] : 0;
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) vv += __shfl_xor(vv, off);
+        acc[x] += vv;
+      }
+      if (jr < 64) break;
+      top -= 64;
+    }
+    // ---- segmented scan of the tile deltas
+    const bool in = lane < cnt;
+    const uint64_t* r = a.rec + (blk0 + (in ? lane : 0u)) * RW;
+    const uint64_t head = r[0];
+    const bool first = in && ((head >> 32) & 1u);
+    int32_t dv[KC], mn[KC];
+#pragma unroll
+    for (int x = 0; x < KC; ++x) {
+      const uint64_t v = r[1 + x];
+      dv[x] = in ? (int32_t)(uint32_t)v : 0;
+      mn[x] = (int32_t)(uint32_t)(v >> 32);
+    }
+    uint32_t xr = first ? 1u : 0u;
+    int64_t xs[KC];
+#pragma unroll
+    for (int x = 0; x < KC; ++x) xs[x] = dv[x];
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+      const uint32_t yr = __shfl_up(xr, off);
+      int64_t ys[KC];
+#pragma unroll
+      for (int x = 0; x < KC; ++x) ys[x] = __shfl_up(xs[x], off);
+      if ((int)lane >= off && !xr) {
+        xr = yr;
+#pragma unroll
+        for (int x = 0; x < KC; ++x) xs[x] += ys[x];
+      }
+    }
+    uint32_t always = 0;
+#pragma unroll
+    for (int x = 0; x < KC; ++x) {
+      // what enters: the inclusive sum less its own, and the carry where no
+      // segment starts before (or at) the tile
+      const int64_t c = first ? 0 : xs[x] - dv[x] + (xr ? 0 : acc[x]);
+      s_cin[lane][x] = c;
+      always |= c + mn[x] > 0 ? 1u << x : 0u;
+    }
+    s_g[lane] = (uint32_t)head;
+    s_always[lane] = always;
+    if (in && (uint32_t)head >= a.G && (uint32_t)head != 0xFFFFFFFFu) flag_internal_error(a.counters, 256);
+  }
+  __syncthreads();
+  constexpr uint32_t NS = kOvtThreads / NP, PER = (TB + NS - 1) / NS;
+  const uint32_t k = t % NP, sub = t / NP;
+  if (sub >= NS) return;
+  uint32_t px = 0, row = 0;  // pair k is (px, px + k - row)
+#pragma unroll
+  for (int x = 1; x < KC; ++x) {
+    const uint32_t at = (uint32_t)pair_index<KC>(x, x);
+    if (k >= at) {
+      px = (uint32_t)x;
+      row = at;
+    }
+  }
+  const uint32_t py = px + k - row;
+  const uint32_t kx = (uint32_t)(px * KC - px * (px - 1) / 2), ky = (uint32_t)(py * KC - py * (py - 1) / 2);
+  const uint32_t out = px * 8 - px * (px - 1) / 2 + (py - px);  // rows of eight classes
+  uint64_t u = 0, q = 0;
+  uint32_t cur = 0xFFFFFFFFu;
+  auto flush = [&]() {
+    if (cur < a.G) {
+      const uint64_t at = (uint64_t)cur * kSweepQWords + out;
+      if (u) atomicAdd((unsigned long long*)&a.ov_u[at], (unsigned long long)u);
+      if (q) atomicAdd((unsigned long long*)&a.ov_q[at], (unsigned long long)q);
+    }
+    u = 0;
+    q = 0;
+  };
+  const uint32_t i1 = (sub + 1) * PER < cnt ? (sub + 1) * PER : cnt;
+#pragma unroll 2
+  for (uint32_t i = sub * PER; i < i1; ++i) {
+    const uint64_t* r = a.rec + (blk0 + i) * RW;
+    const uint64_t S0 = r[1 + KC], s1x = r[2 + KC + px], s1y = r[2 + KC + py], s2 = r[2 + 2 * KC + k];
+    const uint64_t* T = r + 2 + 2 * KC + NP;  // pair order; T[x][x] = T[x]
+    const uint64_t tx = T[kx], ty = T[ky], txy = T[k];
+    if (s_g[i] != cur) {
+      flush();
+      cur = s_g[i];
+    }
+    const bool alx = (s_always[i] >> px) & 1u, aly = (s_always[i] >> py) & 1u;
+    const int64_t avx = s_cin[i][px] - kLBias, avy = s_cin[i][py] - kLBias;
+    const uint64_t ax = (uint64_t)avx, ay = (uint64_t)avy;
+    u += alx && aly ? S0 : alx ? ty : aly ? tx : txy;
+    q += px == py ? s2 + ax * s1x + (uint64_t)((avx * (avx - 1)) / 2) * S0
+                  : s2 + ax * s1y + ay * s1x + ax * ay * S0;
+  }
+  flush();
 }
 
 #define ARGUS_KC_SWITCH(K, F) \
@@ -1694,11 +1805,20 @@ hipError_t launch_merge_sweep(const RunArgs& a, hipStream_t s) {
   o.ov_q = a.w.ov_q;
   o.counters = a.out.d_counters;
   o.G = a.G;
-  const uint64_t ob = ceil_div(a.w.tiles_cap ? a.w.tiles_cap : 1, kOvtThreads);
+  const uint32_t tb = (uint32_t)ovt_tiles((int)a.K);
+  const uint64_t ob = ceil_div(a.w.tiles_cap ? a.w.tiles_cap : 1, tb);
   void* oargs[] = {&o};
-  e = hipLaunchKernel(ARGUS_KC_SWITCH(a.K, k_ovt_agg), dim3((uint32_t)ob), dim3(kOvtThreads), oargs, 0, s);
+  e = hipLaunchKernel(ARGUS_KC_SWITCH(a.K, k_ovt_agg), dim3((uint32_t)ob), dim3(tb), oargs, 0, s);
   if (e != hipSuccess) return e;
-  return hipLaunchKernel(ARGUS_KC_SWITCH(a.K, k_ovt_final), dim3((uint32_t)ob), dim3(kOvtThreads), oargs, 0, s);
+  const void* fin = a.K == 1   ? (const void*)k_ovt_final<1>
+                    : a.K == 2 ? (const void*)k_ovt_final<2>
+                    : a.K == 3 ? (const void*)k_ovt_final<3>
+                    : a.K == 4 ? (const void*)k_ovt_final<4>
+                    : a.K == 5 ? (const void*)k_ovt_final_pairs<5>
+                    : a.K == 6 ? (const void*)k_ovt_final_pairs<6>
+                    : a.K == 7 ? (const void*)k_ovt_final_pairs<7>
+                               : (const void*)k_ovt_final_pairs<8>;
+  return hipLaunchKernel(fin, dim3((uint32_t)ob), dim3(kOvtThreads), oargs, 0, s);
 }
 
 }  // namespace argus
