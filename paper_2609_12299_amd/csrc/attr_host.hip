@@ -31,11 +31,11 @@ struct argus_attr {
 
 namespace argus {
 
-uint64_t persistent_blocks(const void* kernel, int threads) {
+uint64_t persistent_blocks(const void* kernel, int threads, size_t lds) {
   int dev = 0, cus = 256, per_cu = 1;
   if (hipGetDevice(&dev) == hipSuccess)
     (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, threads, 0) != hipSuccess ||
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, threads, lds) != hipSuccess ||
       per_cu < 1)
     per_cu = 1;
   return (uint64_t)cus * (uint64_t)per_cu;

@@ -607,7 +607,7 @@ hipError_t launch_ov_final(const RunArgs& a, hipStream_t s);
 
 // Number of blocks of `kernel` that fit on the device at once (all CUs at
 // the kernel's occupancy): the grid of a persistent kernel.
-uint64_t persistent_blocks(const void* kernel, int threads);
+uint64_t persistent_blocks(const void* kernel, int threads, size_t lds = 0);
 
 // Launch geometry helpers shared by host code.
 __host__ __device__ inline uint64_t ceil_div(uint64_t a, uint64_t b) { return (a + b - 1) / b; }

@@ -301,7 +301,10 @@ constexpr uint32_t kSoMaxRegions = 4096;
 constexpr uint32_t kSoCont = 1;    // the chunk's last context continues into the next chunk
 constexpr uint32_t kSoWhole = 2;   // the chunk holds one context
 constexpr uint32_t kSoPcont = 4;   // the chunk's first context began in an earlier chunk
-constexpr uint32_t kSoPending = 0x80000000u;  // ordinal still lacks its chunk's carry
+constexpr uint32_t kSoPending = 0x80000000u;  // ordinal still lacks its chunk's carry: region << 12 | local
+constexpr uint32_t kSoMaskShift = 16;         // bits 16..31: the chunk's granules that may hold instances in scope
+constexpr uint32_t kSoGranule = kScTile / 16; // 256 instances
+static_assert(kSoMaxRegions <= 4096 && kScTile <= 4096, "12 bits each in a pending ordinal");
 constexpr uint32_t kSoSeg = 256;   // chunks per segment of the carry scan
 
 struct ScopeArgs {
@@ -316,14 +319,18 @@ struct ScopeArgs {
   SortBufs s;         // count = the instances
   uint32_t* octr;     // [kOrdMaxBuckets] pairs gathered per bucket so far
   uint64_t* pairs;    // [count] ordinal << 32 | index, by bucket (a free sort buffer)
-  uint32_t* hkey;     // [count] histogram key of each instance (a free sort buffer)
+  uint32_t* hkey;     // [count] histogram keys (a free sort buffer): one per instance, or (fast) those
+                      // of each granule's matched instances in scope, from the granule's start
+  uint16_t* gcnt;     // [granules] histogram keys of each granule (a free sort buffer)
+  uint32_t* cneed;    // [chunks] 1: a chunk inside one context whose ordinals reach the window (ditto)
   // chunk-local ordinals
   uint32_t fast;      // 1: k_so_local wrote the ordinals; k_sc_stats adds the carries
   uint32_t* tail;     // [chunks][R] counts of the chunk's last context per region, then
                       // the carry entering each chunk whose first context began earlier
-  uint32_t* cflag;    // [chunks] kSoCont | kSoWhole | kSoPcont
+  uint32_t* cflag;    // [chunks] kSoCont | kSoWhole | kSoPcont, and the granules' bits
   uint32_t* segb;     // [segments][R] segment composites, then the carry entering each
   uint32_t* segm;     // [segments] 1: the segment passes its entering carry on
+  uint32_t hslice, hslices, hranges;  // k_sc_hist: regions per slice, slices, ranges of granules
 };
 
 // Fill kernel for the outputs that are accumulated.
@@ -527,6 +534,15 @@ __device__ __forceinline__ uint32_t wave_incl_max32(uint32_t v) {
 // zero.  The loads of kSoBatch rounds are issued together.
 constexpr int kSoBatch = 16;
 
+__device__ __forceinline__ bool in_range32(uint64_t v, uint32_t lo, uint32_t hi) {
+  return lo <= v && v <= hi;
+}
+// The context's part of a scope: warp role and group.
+__device__ __forceinline__ bool in_scope_ctx(const argus_scope& sc, uint32_t ctx) {
+  const uint64_t group = sc.group_shift >= 32 ? 0ull : (uint64_t)(ctx >> sc.group_shift);
+  return in_range32(ctx & sc.role_mask, sc.role_lo, sc.role_hi) && in_range32(group, sc.group_lo, sc.group_hi);
+}
+
 __global__ __launch_bounds__(kScThreads) void k_so_local(ScopeArgs a) {
   extern __shared__ uint32_t so_cnt[];  // [4 waves][R]: context start << 16 | count
   const uint64_t n = sb_count(a.s);
@@ -548,7 +564,7 @@ __global__ __launch_bounds__(kScThreads) void k_so_local(ScopeArgs a) {
     uint32_t f = F == L ? kSoWhole : 0u;
     if (base > 0 && ctx_before == F) f |= kSoPcont;
     if (base + cnt < n && ctx_after == L) f |= kSoCont;
-    if (lane == 0) a.cflag[c] = f;
+    uint32_t maybe = 0;  // granules that may hold instances in scope
     for (uint32_t r = lane; r < a.R; r += 64) cr[r] = 0;
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
@@ -601,13 +617,19 @@ __global__ __launch_bounds__(kScThreads) void k_so_local(ScopeArgs a) {
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        if (in) {
-          // the chunk's first context starts at position 0
-          const bool pending = (f & kSoPcont) && seg == 0;
-          a.ordinal[base + e] = pending ? (kSoPending | local) : local;
-        }
+        // the chunk's first context starts at position 0
+        const bool pending = ok && (f & kSoPcont) && seg == 0;
+        if (in) a.ordinal[base + e] = pending ? (kSoPending | (reg << 12) | local) : local;
+        // (a pending ordinal only grows by its carry)
+        const bool cand = ok && in_scope_ctx(a.sc, ctx) && local <= a.sc.iter_hi &&
+                          (pending || local >= a.sc.iter_lo) && (!a.region_mask || a.region_mask[rc] != 0);
+        if (__ballot(cand)) maybe |= 1u << (r0 / kSoGranule);
         }
       }
+    }
+    if (lane == 0) {
+      a.cflag[c] = f | (maybe << kSoMaskShift);
+      a.cneed[c] = 0;
     }
     if (f & kSoCont) {
       // the last context's counts (its start: the last element's)
@@ -700,24 +722,102 @@ __global__ __launch_bounds__(kScThreads) void k_so_down(ScopeArgs a) {
       if (f[u] & kSoPcont) a.tail[c * a.R + r] = x;  // the carry entering chunk c
       const uint32_t tv = (f[u] & kSoCont) ? t[u] : 0u;
       const bool keep = (f[u] & (kSoCont | kSoWhole | kSoPcont)) == (kSoCont | kSoWhole | kSoPcont);
+      // the region's ordinals in a chunk inside one context: [x, x + tv)
+      if (keep && tv && x <= a.sc.iter_hi && x + tv > a.sc.iter_lo) a.cneed[c] = 1;
       x = keep ? x + tv : tv;
     }
   }
-}
-
-__device__ __forceinline__ bool in_range32(uint64_t v, uint32_t lo, uint32_t hi) {
-  return lo <= v && v <= hi;
 }
 
 // Scoped statistics in canonical order.  With LDS_ROWS, each block keeps
 // the twelve scalar columns of every region in LDS (LDS atomics), and adds
 // them to the output once at the end; without, every column goes straight
 // to the output with global atomics.  The histograms are counted afterwards
-// from one key per instance (k_hist over slices of regions).
+// from the keys of the matched instances in scope (k_sc_hist).
+//
+// A wave takes granules of 256 instances.  The ordinal pass has marked the
+// granules that may hold instances in scope (and the carry scan the chunks
+// inside one context whose ordinals reach the iteration window); elsewhere
+// only the ordinals are completed, from the 4-byte words that hold what is
+// needed for it, and the 32-byte instances are not read: 0.88 -> 0.38 ms on 67 M
+// instances (iterations 0..15 of half the groups).
 constexpr uint32_t kScLdsRegions = 1024;  // 12 x 8 B x 1024 = 96 KiB of LDS
 constexpr int kScStatThreads = 1024;
 constexpr int kScCols = 12;               // ARGUS_RS_COUNT .. ARGUS_RS_SELF_NESTED
-constexpr int kScStatItems = 2;           // instances per thread and step
+constexpr uint32_t kScHistLds = 150 * 1024;
+
+struct ScCounts {
+  uint32_t in, m, mm, u, s, best;
+};
+
+// Adds one instance in scope (h0, h1: its halves; ex: its exclusive time;
+// preg: its parent's region) to the statistics; its histogram key, or none.
+template <class ColPtr>
+__device__ __forceinline__ uint32_t sc_add(const ScopeArgs& a, const uint4& h0, const uint4& h1, uint64_t ex,
+                                           uint32_t preg, ScCounts& c, ColPtr col_ptr) {
+  const uint32_t reg = h1.w & 0xFFFFu, ereg = h1.w >> 16;
+  c.in += 1;
+  if (ereg == kNoEnd) {
+    c.u += 1;
+    atomicAdd(col_ptr(reg, ARGUS_RS_UNCLOSED), 1ull);
+    return 0xFFFFFFFFu;
+  }
+  if (ereg != reg) {
+    c.mm += 1;
+    atomicAdd(col_ptr(reg, ARGUS_RS_MISM_AS_BEGIN), 1ull);
+    if (ereg < a.R) atomicAdd(col_ptr(ereg, ARGUS_RS_MISM_AS_END), 1ull);
+    return 0xFFFFFFFFu;
+  }
+  c.m += 1;
+  const uint64_t tb = (uint64_t)h0.x | ((uint64_t)h0.y << 32), te = (uint64_t)h0.z | ((uint64_t)h0.w << 32);
+  const uint64_t d = te - tb;
+  atomicAdd(col_ptr(reg, ARGUS_RS_COUNT), 1ull);
+  atomicAdd(col_ptr(reg, ARGUS_RS_INCL_SUM), (unsigned long long)d);
+  atomicAdd(col_ptr(reg, ARGUS_RS_EXCL_SUM), (unsigned long long)ex);
+  atomicMin(col_ptr(reg, ARGUS_RS_INCL_MIN), (unsigned long long)d);
+  atomicMax(col_ptr(reg, ARGUS_RS_INCL_MAX), (unsigned long long)d);
+  atomicMin(col_ptr(reg, ARGUS_RS_EXCL_MIN), (unsigned long long)ex);
+  atomicMax(col_ptr(reg, ARGUS_RS_EXCL_MAX), (unsigned long long)ex);
+  if (preg == reg) {
+    c.s += 1;
+    atomicAdd(col_ptr(reg, ARGUS_RS_SELF_NESTED), 1ull);
+  }
+  return (reg << 16) | (bit_width64(d) << 8) | bit_width64(ex);
+}
+
+// The counters, once per block (an atomic per wave on one counter takes 5 ns
+// each, one after another).  Every thread of the block calls it.
+__device__ __forceinline__ void sc_counters(const ScopeArgs& a, const ScCounts& c, uint64_t n) {
+  __shared__ uint32_t s_cnt[6][kScStatThreads / 64];
+  const uint32_t lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const uint32_t v[5] = {c.in, c.m, c.mm, c.u, c.s};
+#pragma unroll
+  for (int q = 0; q < 5; ++q) {
+    const uint32_t t = rows_sum32(row_sum32(v[q]));
+    if (lane == 0) s_cnt[q][w] = t;
+  }
+  uint32_t best = c.best;
+#pragma unroll
+  for (int d = 32; d >= 1; d >>= 1) {
+    const uint32_t o = __shfl_xor(best, d);
+    best = best > o ? best : o;
+  }
+  if (lane == 0) s_cnt[5][w] = best;
+  __syncthreads();
+  if (threadIdx.x < 6) {
+    constexpr int slot[6] = {ARGUS_SC_N_IN_SCOPE, ARGUS_SC_N_MATCHED,     ARGUS_SC_N_MISMATCHED,
+                             ARGUS_SC_N_UNCLOSED, ARGUS_SC_N_SELF_NESTED, ARGUS_SC_N_ITERATIONS};
+    unsigned long long t = 0;
+    for (uint32_t q = 0; q < kScStatThreads / 64; ++q) {
+      const uint32_t x = s_cnt[threadIdx.x][q];
+      t = threadIdx.x < 5 ? t + x : (t > x ? t : x);
+    }
+    unsigned long long* dst = (unsigned long long*)&a.counters[slot[threadIdx.x]];
+    if (t && threadIdx.x < 5) atomicAdd(dst, t);
+    else if (t) atomicMax(dst, t);
+  }
+  if (blockIdx.x == 0 && threadIdx.x == 0) a.counters[ARGUS_SC_N_INSTANCES] = n;
+}
 
 template <bool LDS_ROWS>
 __global__ __launch_bounds__(kScStatThreads) void k_sc_stats(ScopeArgs a) {
@@ -736,146 +836,190 @@ __global__ __launch_bounds__(kScStatThreads) void k_sc_stats(ScopeArgs a) {
     return LDS_ROWS ? &srow[(uint64_t)reg * kScCols + col]
                     : (unsigned long long*)(a.stats + (uint64_t)reg * ARGUS_RS_WIDTH + col);
   };
-  uint32_t c_in = 0, c_m = 0, c_mm = 0, c_u = 0, c_s = 0, best = 0;
-  // kScStatItems instances per thread and step: their instance and ordinal
-  // loads together, issued one step ahead; then (in scope and matched only)
-  // the exclusive times and parents' regions together
-  const uint64_t step = (uint64_t)gridDim.x * kScStatThreads;
-  const uint64_t first = (uint64_t)blockIdx.x * kScStatThreads + threadIdx.x;
-  uint4 p0[kScStatItems], p1[kScStatItems];
-  uint32_t pord[kScStatItems];
-  auto issue = [&](uint64_t xs) {
+  ScCounts cc{};
+  constexpr int IT = kSoGranule / 64;
+  const uint32_t lane = threadIdx.x & 63;
+  const uint64_t lt = lanemask_lt();
+  const uint64_t granules = (n + kSoGranule - 1) / kSoGranule;
+  const uint64_t step = (uint64_t)gridDim.x * (kScStatThreads / 64);
+  // blocks take neighbouring granules in the same step, so that the chunks
+  // that hold instances in scope spread over the chip
+  uint64_t g = (uint64_t)(threadIdx.x >> 6) * gridDim.x + blockIdx.x;
+  uint32_t pord[IT], pflag = 0, pneed = 0;
+  auto issue = [&](uint64_t gi) {  // one granule ahead
+    const uint64_t c = gi / (kScTile / kSoGranule);
+    pflag = a.cflag[c];
+    pneed = a.cneed[c];
 #pragma unroll
-    for (int j = 0; j < kScStatItems; ++j) {
-      const uint64_t x = xs + j * step;
-      const uint64_t xc = x < n ? x : n - 1;
-      p0[j] = inst[2 * xc];
-      p1[j] = inst[2 * xc + 1];
-      pord[j] = a.ordinal[xc];
+    for (int j = 0; j < IT; ++j) {
+      const uint64_t x = gi * kSoGranule + 64u * j + lane;
+      pord[j] = a.ordinal[x < n ? x : n - 1];
     }
   };
-  if (first < n) issue(first);
-  for (uint64_t x0 = first; x0 < n; x0 += step * kScStatItems) {
-    uint4 h0[kScStatItems], h1[kScStatItems];
-    uint32_t ord[kScStatItems];
+  if (g < granules) issue(g);
+  for (; g < granules; g += step) {
+    const uint64_t x0 = g * kSoGranule + lane, c = g / (kScTile / kSoGranule);
+    const uint32_t f = pflag, need_chunk = pneed;
+    uint32_t ord[IT];
 #pragma unroll
-    for (int j = 0; j < kScStatItems; ++j) {
-      h0[j] = p0[j];
-      h1[j] = p1[j];
-      ord[j] = pord[j];
+    for (int j = 0; j < IT; ++j) ord[j] = pord[j];
+    constexpr uint32_t kInside = kSoCont | kSoWhole | kSoPcont;
+    const bool need = ((f >> (kSoMaskShift + (uint32_t)(g % (kScTile / kSoGranule)))) & 1u) &&
+                      ((f & kInside) != kInside || need_chunk);
+    // chunk-local ordinals: add the carry of the context entering the chunk
+    uint32_t carry[IT];
+#pragma unroll
+    for (int j = 0; j < IT; ++j)
+      carry[j] = (ord[j] & kSoPending) ? a.tail[c * a.R + ((ord[j] >> 12) & 0xFFFu)] : 0u;
+    uint4 h0[IT], h1[IT];
+    if (need) {
+#pragma unroll
+      for (int j = 0; j < IT; ++j) {
+        const uint64_t x = x0 + 64u * j;
+        const uint64_t xc = x < n ? x : n - 1;
+        h0[j] = inst[2 * xc];
+        h1[j] = inst[2 * xc + 1];
+      }
     }
-    bool in[kScStatItems];
-    uint64_t exv[kScStatItems];
-    uint32_t preg[kScStatItems];
+    if (g + step < granules) issue(g + step);
 #pragma unroll
-    for (int j = 0; j < kScStatItems; ++j) {
-      const uint64_t x = x0 + j * step;
-      const uint32_t ctx = h1[j].x, reg = h1[j].w & 0xFFFFu, ereg = h1[j].w >> 16;
-      if (a.fast && x < n) {
-        // chunk-local ordinal: add the carry of the context entering the chunk
+    for (int j = 0; j < IT; ++j) {
+      const uint64_t x = x0 + 64u * j;
+      if (x < n) {
         if (ord[j] & kSoPending) {
-          ord[j] = (ord[j] & ~kSoPending) + (reg < a.R ? a.tail[(x / kScTile) * a.R + reg] : 0u);
+          ord[j] = (ord[j] & 0xFFFu) + carry[j];
           a.ordinal[x] = ord[j];
         }
-        best = best > ord[j] + 1 ? best : ord[j] + 1;
+        cc.best = cc.best > ord[j] + 1 ? cc.best : ord[j] + 1;
       }
-      const uint64_t group = a.sc.group_shift >= 32 ? 0ull : (uint64_t)(ctx >> a.sc.group_shift);
-      in[j] = x < n && in_range32(ctx & a.sc.role_mask, a.sc.role_lo, a.sc.role_hi) &&
-              in_range32(group, a.sc.group_lo, a.sc.group_hi) &&
-              in_range32(ord[j], a.sc.iter_lo, a.sc.iter_hi) && reg < a.R &&
-              (!a.region_mask || a.region_mask[reg] != 0);
-      const bool mt = in[j] && ereg == reg;
-      exv[j] = mt ? a.excl[x] : 0ull;
-      const uint32_t par = h1[j].y;
-      preg[j] = mt && par != kNoParent && par < n ? (inst[2 * (uint64_t)par + 1].w & 0xFFFFu)
-                                                  : 0xFFFFFFFFu;
     }
-    // the next step's loads, issued after this step's dependent loads (a
-    // wait for a load also waits for every load issued before it)
-    if (x0 + step * kScStatItems < n) issue(x0 + step * kScStatItems);
+    uint32_t keys = 0;
+    if (need) {
+      bool in[IT];
+      uint64_t exv[IT];
+      uint32_t preg[IT];
 #pragma unroll
-    for (int j = 0; j < kScStatItems; ++j) {
-    const uint64_t x = x0 + j * step;
-    if (x >= n) continue;
-    const uint32_t reg = h1[j].w & 0xFFFFu, ereg = h1[j].w >> 16;
-    // the instance's histogram key (none unless matched and in scope)
-    uint32_t hk = 0xFFFFFFFFu;
-    if (in[j]) {
-      c_in += 1;
-      if (ereg == kNoEnd) {
-        c_u += 1;
-        atomicAdd(col_ptr(reg, ARGUS_RS_UNCLOSED), 1ull);
-      } else if (ereg != reg) {
-        c_mm += 1;
-        atomicAdd(col_ptr(reg, ARGUS_RS_MISM_AS_BEGIN), 1ull);
-        if (ereg < a.R) atomicAdd(col_ptr(ereg, ARGUS_RS_MISM_AS_END), 1ull);
-      } else {
-        c_m += 1;
-        const uint64_t tb = (uint64_t)h0[j].x | ((uint64_t)h0[j].y << 32);
-        const uint64_t te = (uint64_t)h0[j].z | ((uint64_t)h0[j].w << 32);
-        const uint64_t d = te - tb, ex = exv[j];
-        atomicAdd(col_ptr(reg, ARGUS_RS_COUNT), 1ull);
-        atomicAdd(col_ptr(reg, ARGUS_RS_INCL_SUM), (unsigned long long)d);
-        atomicAdd(col_ptr(reg, ARGUS_RS_EXCL_SUM), (unsigned long long)ex);
-        atomicMin(col_ptr(reg, ARGUS_RS_INCL_MIN), (unsigned long long)d);
-        atomicMax(col_ptr(reg, ARGUS_RS_INCL_MAX), (unsigned long long)d);
-        atomicMin(col_ptr(reg, ARGUS_RS_EXCL_MIN), (unsigned long long)ex);
-        atomicMax(col_ptr(reg, ARGUS_RS_EXCL_MAX), (unsigned long long)ex);
-        hk = (reg << 16) | (bit_width64(d) << 8) | bit_width64(ex);
-        if (preg[j] == reg) {
-          c_s += 1;
-          atomicAdd(col_ptr(reg, ARGUS_RS_SELF_NESTED), 1ull);
-        }
+      for (int j = 0; j < IT; ++j) {
+        const uint64_t x = x0 + 64u * j;
+        const uint32_t reg = h1[j].w & 0xFFFFu, ereg = h1[j].w >> 16;
+        in[j] = x < n && in_scope_ctx(a.sc, h1[j].x) && in_range32(ord[j], a.sc.iter_lo, a.sc.iter_hi) &&
+                reg < a.R && (!a.region_mask || a.region_mask[reg] != 0);
+        const bool mt = in[j] && ereg == reg;
+        exv[j] = mt ? a.excl[x] : 0ull;
+        const uint32_t par = h1[j].y;
+        preg[j] = mt && par != kNoParent && par < n ? (inst[2 * (uint64_t)par + 1].w & 0xFFFFu)
+                                                    : 0xFFFFFFFFu;
+      }
+#pragma unroll
+      for (int j = 0; j < IT; ++j) {
+        uint32_t hk = 0xFFFFFFFFu;
+        if (in[j]) hk = sc_add(a, h0[j], h1[j], exv[j], preg[j], cc, col_ptr);
+        const uint64_t m = __ballot(hk != 0xFFFFFFFFu);
+        if (hk != 0xFFFFFFFFu) a.hkey[g * kSoGranule + keys + (uint32_t)__popcll(m & lt)] = hk;
+        keys += (uint32_t)__popcll(m);
       }
     }
-    a.hkey[x] = hk;
-    }
+    if (lane == 0) a.gcnt[g] = (uint16_t)keys;
   }
   if (LDS_ROWS) {
     __syncthreads();
     for (uint32_t i = threadIdx.x; i < a.R * kScCols; i += kScStatThreads) {
       const uint32_t col = i % kScCols, reg = i / kScCols;
       const unsigned long long v = srow[i];
-      unsigned long long* g = (unsigned long long*)(a.stats + (uint64_t)reg * ARGUS_RS_WIDTH + col);
+      unsigned long long* dst = (unsigned long long*)(a.stats + (uint64_t)reg * ARGUS_RS_WIDTH + col);
       if (col == ARGUS_RS_INCL_MIN || col == ARGUS_RS_EXCL_MIN) {
-        if (v != ~0ull) atomicMin(g, v);
+        if (v != ~0ull) atomicMin(dst, v);
       } else if (col == ARGUS_RS_INCL_MAX || col == ARGUS_RS_EXCL_MAX) {
-        if (v) atomicMax(g, v);
+        if (v) atomicMax(dst, v);
       } else if (v) {
-        atomicAdd(g, v);
+        atomicAdd(dst, v);
       }
     }
   }
-  // the counters once per block (an atomic per wave on one counter takes 5 ns
-  // each, one after another)
-  const uint32_t lane = threadIdx.x & 63;
-#pragma unroll
-  for (int d = 32; d >= 1; d >>= 1) {
-    const uint32_t o = __shfl_xor(best, d);
-    best = best > o ? best : o;
-  }
-  __shared__ uint32_t s_cnt[6][kScStatThreads / 64];
-  const uint32_t v[5] = {c_in, c_m, c_mm, c_u, c_s};
-#pragma unroll
-  for (int q = 0; q < 5; ++q) {
-    const uint32_t t = rows_sum32(row_sum32(v[q]));
-    if (lane == 0) s_cnt[q][threadIdx.x >> 6] = t;
-  }
-  if (lane == 0) s_cnt[5][threadIdx.x >> 6] = a.fast ? best : 0u;
+  sc_counters(a, cc, n);
+}
+
+// The log2 histograms from the granules' keys: each block covers one slice of
+// regions in LDS over one range of the granules (the slices of a range are 8
+// blocks apart: on one XCD, whose L2 they share).  A wave takes 64 granules at
+// a time and, of those with keys, eight at once: a granule's keys are one
+// 16-byte load per lane.
+__global__ __launch_bounds__(kScStatThreads) void k_sc_hist(ScopeArgs a) {
+  extern __shared__ __align__(16) uint8_t sc_smem[];
+  uint32_t* s_h = reinterpret_cast<uint32_t*>(sc_smem);
+  const uint32_t b = blockIdx.x, grp = b / (8 * a.hslices), rem = b % (8 * a.hslices);
+  const uint32_t range = grp * 8 + rem % 8, r0 = rem / 8 * a.hslice;
+  if (range >= a.hranges || r0 >= a.R) return;
+  const uint32_t nr = (r0 + a.hslice < a.R ? r0 + a.hslice : a.R) - r0;
+  for (uint32_t i = threadIdx.x; i < nr * 130; i += kScStatThreads) s_h[i] = 0;
   __syncthreads();
-  if (threadIdx.x < 6) {
-    constexpr int slot[6] = {ARGUS_SC_N_IN_SCOPE, ARGUS_SC_N_MATCHED,     ARGUS_SC_N_MISMATCHED,
-                             ARGUS_SC_N_UNCLOSED, ARGUS_SC_N_SELF_NESTED, ARGUS_SC_N_ITERATIONS};
-    unsigned long long t = 0;
-    for (uint32_t q = 0; q < kScStatThreads / 64; ++q) {
-      const uint32_t x = s_cnt[threadIdx.x][q];
-      t = threadIdx.x < 5 ? t + x : (t > x ? t : x);
+  const uint64_t granules = (sb_count(a.s) + kSoGranule - 1) / kSoGranule;
+  const uint32_t lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const uint64_t step = (uint64_t)a.hranges * (kScStatThreads / 64) * 64;
+  for (uint64_t g0 = ((uint64_t)w * a.hranges + range) * 64; g0 < granules; g0 += step) {
+    const uint32_t cnt = g0 + lane < granules ? a.gcnt[g0 + lane] : 0u;
+    uint64_t left = __ballot(cnt != 0);
+    while (left) {
+      uint4 v[8];
+      uint32_t kn[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        kn[u] = 0;
+        v[u] = make_uint4(0, 0, 0, 0);
+        if (left) {
+          const uint32_t q = (uint32_t)__builtin_ctzll(left);
+          left &= left - 1;
+          kn[u] = (uint32_t)__builtin_amdgcn_readlane((int)cnt, (int)q);
+          if (4 * lane < kn[u]) v[u] = reinterpret_cast<const uint4*>(a.hkey + (g0 + q) * kSoGranule)[lane];
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        const uint32_t k[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
+#pragma unroll
+        for (uint32_t e = 0; e < 4; ++e) {
+          const uint32_t r = k[e] >> 16;
+          if (4 * lane + e >= kn[u] || r < r0 || r - r0 >= nr) continue;
+          atomicAdd(&s_h[(r - r0) * 130 + ((k[e] >> 8) & 0xFFu)], 1u);
+          atomicAdd(&s_h[(r - r0) * 130 + 65 + (k[e] & 0xFFu)], 1u);
+        }
+      }
     }
-    unsigned long long* dst = (unsigned long long*)&a.counters[slot[threadIdx.x]];
-    if (t && threadIdx.x < 5) atomicAdd(dst, t);
-    else if (t) atomicMax(dst, t);
   }
-  if (blockIdx.x == 0 && threadIdx.x == 0) a.counters[ARGUS_SC_N_INSTANCES] = n;
+  __syncthreads();
+  for (uint32_t i = threadIdx.x; i < nr * 130; i += kScStatThreads) {
+    const uint32_t h = s_h[i];
+    if (h)
+      atomicAdd((unsigned long long*)&a.stats[(uint64_t)(r0 + i / 130) * ARGUS_RS_WIDTH + ARGUS_RS_HIST_INCL + i % 130],
+                (unsigned long long)h);
+  }
+}
+
+// More than kSoMaxRegions regions: the ordinals are final, and every
+// instance is read; one histogram key each.
+__global__ __launch_bounds__(kScStatThreads) void k_sc_stats_sorted(ScopeArgs a) {
+  const uint64_t n = sb_count(a.s);
+  const uint4* inst = reinterpret_cast<const uint4*>(a.inst);
+  ScCounts cc{};
+  auto col_ptr = [&](uint32_t reg, uint32_t col) -> unsigned long long* {
+    return (unsigned long long*)(a.stats + (uint64_t)reg * ARGUS_RS_WIDTH + col);
+  };
+  for (uint64_t x = (uint64_t)blockIdx.x * kScStatThreads + threadIdx.x; x < n;
+       x += (uint64_t)gridDim.x * kScStatThreads) {
+    const uint4 h0 = inst[2 * x], h1 = inst[2 * x + 1];
+    const uint32_t ord = a.ordinal[x], reg = h1.w & 0xFFFFu;
+    uint32_t hk = 0xFFFFFFFFu;
+    if (in_scope_ctx(a.sc, h1.x) && in_range32(ord, a.sc.iter_lo, a.sc.iter_hi) && reg < a.R &&
+        (!a.region_mask || a.region_mask[reg] != 0)) {
+      const bool mt = (h1.w >> 16) == reg;
+      const uint64_t ex = mt ? a.excl[x] : 0ull;
+      const uint32_t preg = mt && h1.y != kNoParent && h1.y < n ? (inst[2 * (uint64_t)h1.y + 1].w & 0xFFFFu)
+                                                                : 0xFFFFFFFFu;
+      hk = sc_add(a, h0, h1, ex, preg, cc, col_ptr);
+    }
+    a.hkey[x] = hk;
+  }
+  sc_counters(a, cc, n);
 }
 
 // ------------------------------------------------ probe <-> reference join
@@ -1978,6 +2122,10 @@ extern "C" int argus_attr_scope(const argus_scope_config* cfg, const argus_scope
   hipLaunchKernelGGL(k_sc_init, dim3(sc_grid((uint64_t)a.R * ARGUS_RS_WIDTH, kScThreads, 1024)),
                      dim3(kScThreads), 0, st, a);
   if (a.fast) {
+    // the sort buffers are free
+    a.hkey = reinterpret_cast<uint32_t*>(a.s.b[1]);
+    a.gcnt = reinterpret_cast<uint16_t*>(a.s.a[1]);
+    a.cneed = reinterpret_cast<uint32_t*>(a.s.a[0]);
     const uint64_t chunks = tiles_for(io->max_instances);
     const uint64_t segs = (chunks + kSoSeg - 1) / kSoSeg;
     // four chunks at a time per block (a wave each), each wave with its row
@@ -1996,7 +2144,6 @@ extern "C" int argus_attr_scope(const argus_scope_config* cfg, const argus_scope
     hipLaunchKernelGGL(k_so_top, dim3((a.R + kScThreads - 1) / kScThreads), dim3(kScThreads), 0, st, a);
     hipLaunchKernelGGL(k_so_down, dim3((uint32_t)((cells + kScThreads - 1) / kScThreads)),
                        dim3(kScThreads), 0, st, a);
-    a.hkey = reinterpret_cast<uint32_t*>(a.s.b[1]);  // the sort buffers are free
   } else {
     const int buf = sort_reference(a.s, st);
     a.pairs = a.s.a[buf ^ 1];  // free once the sort is done
@@ -2007,23 +2154,39 @@ extern "C" int argus_attr_scope(const argus_scope_config* cfg, const argus_scope
     hipLaunchKernelGGL(k_sc_ord_place, dim3((uint32_t)(blocks ? blocks : 1)), dim3(kScThreads), 0, st, a);
     a.hkey = reinterpret_cast<uint32_t*>(a.s.b[buf ^ 1]);  // free once the sort is done
   }
-  if (a.R <= kScLdsRegions) {
-    const size_t lds = (size_t)a.R * kScCols * sizeof(uint64_t);
-    (void)hipFuncSetAttribute((const void*)k_sc_stats<true>,
-                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    // one block per compute unit: each flushes its rows once
-    hipLaunchKernelGGL(k_sc_stats<true>,
-                       dim3((uint32_t)std::min<uint64_t>(persistent_blocks((const void*)k_sc_stats<true>,
-                                                                           kScStatThreads),
-                                                         sc_grid(io->max_instances, kScStatThreads, 4096))),
-                       dim3(kScStatThreads), lds, st, a);
-  } else {
-    hipLaunchKernelGGL(k_sc_stats<false>, dim3(sc_grid(io->max_instances, kScStatThreads, 4096)),
-                       dim3(kScStatThreads), 0, st, a);
+  if (io->max_instances == 0) {
+    // (no instance: the counters stand as k_sc_init left them)
+    return hipGetLastError() == hipSuccess ? ARGUS_OK : ARGUS_E_HIP;
   }
-  if (io->max_instances > 0 &&
-      launch_hist_keys(a.hkey, io->d_n_instances, io->max_instances, a.stats, a.R, st) != hipSuccess)
-    return ARGUS_E_HIP;
+  if (a.fast) {
+    const uint64_t waves = (io->max_instances + kSoGranule - 1) / kSoGranule;
+    const bool rows = a.R <= kScLdsRegions;
+    const size_t lds = rows ? (size_t)a.R * kScCols * sizeof(uint64_t) : 0;
+    const void* kern = rows ? (const void*)k_sc_stats<true> : (const void*)k_sc_stats<false>;
+    if (rows) (void)hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    // the blocks that fit at once: each flushes its rows once
+    const uint64_t fit = persistent_blocks(kern, kScStatThreads, lds);
+    const uint32_t blocks = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(fit, (waves + 15) / 16));
+    if (rows) hipLaunchKernelGGL(k_sc_stats<true>, dim3(blocks), dim3(kScStatThreads), lds, st, a);
+    else hipLaunchKernelGGL(k_sc_stats<false>, dim3(blocks), dim3(kScStatThreads), 0, st, a);
+    // as few slices of regions as fit, of equal size
+    const uint32_t slices = (uint32_t)ceil_div((uint64_t)a.R * 130 * sizeof(uint32_t), kScHistLds);
+    a.hslice = (uint32_t)ceil_div(a.R, slices);
+    a.hslices = slices;
+    const size_t hb = (size_t)a.hslice * 130 * sizeof(uint32_t);
+    (void)hipFuncSetAttribute((const void*)k_sc_hist, hipFuncAttributeMaxDynamicSharedMemorySize, (int)hb);
+    // as many ranges as fit at once: each block clears and flushes its slice
+    // once (256 ranges of 4 slices, four times the blocks that fit, took 141 us
+    // where few granules have keys)
+    const uint64_t hfit = ceil_div(persistent_blocks((const void*)k_sc_hist, kScStatThreads, hb), 8ull * slices) * 8;
+    a.hranges = (uint32_t)std::min<uint64_t>(hfit, ceil_div(ceil_div(waves, 16 * 64), 8) * 8);
+    hipLaunchKernelGGL(k_sc_hist, dim3(a.hranges * slices), dim3(kScStatThreads), hb, st, a);
+  } else {
+    hipLaunchKernelGGL(k_sc_stats_sorted, dim3(sc_grid(io->max_instances, kScStatThreads, 1024)),
+                       dim3(kScStatThreads), 0, st, a);
+    if (launch_hist_keys(a.hkey, io->d_n_instances, io->max_instances, a.stats, a.R, st) != hipSuccess)
+      return ARGUS_E_HIP;
+  }
   return hipGetLastError() == hipSuccess ? ARGUS_OK : ARGUS_E_HIP;
 }
 
