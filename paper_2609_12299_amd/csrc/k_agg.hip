@@ -491,12 +491,16 @@ hipError_t launch_hist_keys(const uint32_t* keys, const uint64_t* d_count, uint6
   // as few slices as fit, of equal size
   const uint32_t slices = (uint32_t)ceil_div((uint64_t)R * kHistBytes, kHistLdsBytes);
   const uint32_t slice = (uint32_t)ceil_div(R, slices);
+  const size_t hb = (size_t)slice * kHistBytes;
+  (void)hipFuncSetAttribute((const void*)k_hist, hipFuncAttributeMaxDynamicSharedMemorySize, (int)hb);
+  // at most the ranges whose blocks fit at once (up to 256): each block clears
+  // and flushes its slice once
+  const uint64_t fit = ceil_div(persistent_blocks((const void*)k_hist, 1024, hb), slices);
   uint64_t ranges = ceil_div(count_max ? count_max : 1, 1024 * 64);
+  if (ranges > fit) ranges = fit;
   if (ranges > 256) ranges = 256;
   ranges = ceil_div(ranges, 8) * 8;
   HistArgs h{d_count, count_max, keys, rstats, R, slice, slices, (uint32_t)ranges};
-  const size_t hb = (size_t)slice * kHistBytes;
-  (void)hipFuncSetAttribute((const void*)k_hist, hipFuncAttributeMaxDynamicSharedMemorySize, (int)hb);
   hipLaunchKernelGGL(k_hist, dim3((uint32_t)(ranges * slices)), dim3(1024), hb, s, h);
   return hipGetLastError();
 }
