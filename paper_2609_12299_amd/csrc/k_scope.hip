@@ -1512,6 +1512,8 @@ __global__ __launch_bounds__(kScThreads) void k_pr_groups(ProbeArgs a) {
 // and the same parent.
 
 constexpr uint32_t kHoMaxCompact = 4096;  // compaction blocks
+constexpr uint32_t kHoThreads = 1024;
+constexpr uint32_t kHoTile = kHoThreads * kScRounds;  // instances per compaction tile
 
 struct HandoffArgs {
   const argus_instance* inst;
@@ -1547,7 +1549,7 @@ __global__ __launch_bounds__(kScThreads) void k_ho_init(HandoffArgs a) {
     for (uint64_t i = first; i < a.max_inst; i += stride) a.parent_gap[i] = 0;
   if (first < 65) a.hist[first] = 0;
   if (first < ARGUS_HO_NUM_COUNTERS) a.counters[first] = 0;
-  const uint64_t tiles = (a.max_inst + kScTile - 1) / kScTile;
+  const uint64_t tiles = (a.max_inst + kHoTile - 1) / kHoTile;
   for (uint64_t i = first; i < tiles; i += stride) a.status[i] = 0;
   if (first == 0) {
     *a.tctr = 0;
@@ -1556,18 +1558,18 @@ __global__ __launch_bounds__(kScThreads) void k_ho_init(HandoffArgs a) {
 }
 
 // The instances of level <= L compacted in canonical order, in one pass:
-// blocks take tiles of 4096 instances in order (a counter; a block takes its
+// blocks take tiles of 16384 instances in order (a counter; a block takes its
 // next tile once this one's loads are on their way, so that the counter's
 // round trip is hidden: nothing waits for a tile that comes after one still
 // in work), count the tile's qualifying instances (a ballot per round of 64,
 // the waves' counts through LDS), publish the count, find the count before
 // the tile by decoupled look-back, 64 tiles a step, and write the indices.
 // The tile holding the last instance records the total.
-__global__ __launch_bounds__(kScThreads) void k_ho_compact(HandoffArgs a) {
-  __shared__ uint32_t s_tile, s_w[kScThreads / 64];
+__global__ __launch_bounds__(kHoThreads) void k_ho_compact(HandoffArgs a) {
+  __shared__ uint32_t s_tile, s_w[kHoThreads / 64];
   __shared__ uint64_t s_base;
   const uint64_t n = ho_count(a);
-  const uint64_t T = (n + kScTile - 1) / kScTile;
+  const uint64_t T = (n + kHoTile - 1) / kHoTile;
   const uint32_t* iw = reinterpret_cast<const uint32_t*>(a.inst);  // 8 words per instance
   const uint32_t tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const uint64_t lt = lanemask_lt();
@@ -1579,7 +1581,7 @@ __global__ __launch_bounds__(kScThreads) void k_ho_compact(HandoffArgs a) {
     __syncthreads();
     const uint64_t tile = s_tile;
     if (tile >= T) break;
-    const uint64_t base = tile * kScTile;
+    const uint64_t base = tile * kHoTile;
     uint64_t qm[kScRounds];  // ballot of the qualifying lanes of each round
     uint32_t lv[kScRounds];
     // all the tile's loads issued before the first is used (indices clamped
@@ -1604,7 +1606,7 @@ __global__ __launch_bounds__(kScThreads) void k_ho_compact(HandoffArgs a) {
     __syncthreads();
     uint32_t wpre = 0, cnt = 0;
 #pragma unroll
-    for (int q = 0; q < kScThreads / 64; ++q) {
+    for (int q = 0; q < kHoThreads / 64; ++q) {
       wpre += q < (int)w ? s_w[q] : 0u;
       cnt += s_w[q];
     }
@@ -1656,7 +1658,11 @@ __global__ __launch_bounds__(kScThreads) void k_ho_compact(HandoffArgs a) {
   const uint32_t tot = rows_sum32(row_sum32(at));
   if (lane == 0) s_w[w] = tot;
   __syncthreads();
-  if (tid == 0) a.atl[blockIdx.x] = s_w[0] + s_w[1] + s_w[2] + s_w[3];
+  if (tid == 0) {
+    uint32_t t = 0;
+    for (uint32_t q = 0; q < kHoThreads / 64; ++q) t += s_w[q];
+    a.atl[blockIdx.x] = t;
+  }
 }
 
 // Successive pairs, aggregated per block in an LDS hash table of (x region,
@@ -1675,7 +1681,6 @@ __global__ __launch_bounds__(kScThreads) void k_ho_compact(HandoffArgs a) {
 // parents, where an add per lane would queue 64 atomics on one address).
 constexpr uint32_t kHoSlots = 4096;
 constexpr int kHoProbes = 16;
-constexpr uint32_t kHoThreads = 1024;
 constexpr uint32_t kHoHashShift = 20;  // 32 - log2(kHoSlots)
 constexpr uint32_t kHoMaxDumps = 256;  // pair blocks at most: one per compute unit
 
@@ -2341,9 +2346,9 @@ extern "C" int argus_attr_handoffs(const argus_handoffs_config* cfg, const argus
     const uint32_t g = sc_grid(io->max_instances, kScThreads, 4096);
     // resident blocks only: they take the tiles in order
     a.cblocks = (uint32_t)std::min<uint64_t>(
-        std::min<uint64_t>(tiles_for(io->max_instances), persistent_blocks((const void*)k_ho_compact, kScThreads)),
+        std::min<uint64_t>(ceil_div(io->max_instances, kHoTile), persistent_blocks((const void*)k_ho_compact, kHoThreads)),
         kHoMaxCompact);
-    hipLaunchKernelGGL(k_ho_compact, dim3(a.cblocks), dim3(kScThreads), 0, st, a);
+    hipLaunchKernelGGL(k_ho_compact, dim3(a.cblocks), dim3(kHoThreads), 0, st, a);
     // resident blocks only (one per compute unit): each stores its table once
     a.dumps = (uint32_t)std::min<uint64_t>(
         std::min<uint64_t>(g, persistent_blocks((const void*)k_ho_pairs, kHoThreads)), kHoMaxDumps);
