@@ -386,29 +386,32 @@ __global__ __launch_bounds__(256) void k_ingest(IngestArgs a) {
     s_red[w][7] = cmax;
   }
   __syncthreads();
-  if (threadIdx.x == 0) {
-    uint64_t v[8];
-    for (int k = 0; k < 8; ++k) v[k] = s_red[0][k];
-    for (int q = 1; q < 4; ++q) {
-      for (int k = 0; k < 4; ++k) v[k] += s_red[q][k];
-      v[4] = s_red[q][4] < v[4] ? s_red[q][4] : v[4];
-      v[5] = s_red[q][5] > v[5] ? s_red[q][5] : v[5];
-      v[6] = s_red[q][6] < v[6] ? s_red[q][6] : v[6];
-      v[7] = s_red[q][7] > v[7] ? s_red[q][7] : v[7];
+  // The block's counters, several lanes of one wave in one request where they
+  // do the same to one line: such requests are served one after another, ten
+  // from each of a thousand blocks at the end of the kernel.
+  if (threadIdx.x < 9) {
+    const uint32_t k = threadIdx.x;
+    // 0..3: valid, bad kind, bad region, BEGIN; 4: END; 5, 6: ts and context
+    // minima, 7, 8: maxima
+    constexpr int slot[9] = {ARGUS_C_N_VALID, ARGUS_C_N_BAD_KIND, ARGUS_C_N_BAD_REGION, ARGUS_C_N_BEGIN, ARGUS_C_N_END,
+                             ARGUS_C_TS_MIN,  ARGUS_C_CTX_MIN,    ARGUS_C_TS_MAX,       ARGUS_C_CTX_MAX};
+    constexpr int col[9] = {0, 1, 2, 3, 0, 4, 6, 5, 7};
+    uint64_t v = k == 5 || k == 6 ? kU64Max : 0ull, valid = 0;
+    for (int q = 0; q < 4; ++q) {
+      const uint64_t x = s_red[q][col[k]];
+      if (k < 5) v += x - (k == 4 ? s_red[q][3] : 0ull);
+      else if (k < 7) v = x < v ? x : v;
+      else v = x > v ? x : v;
+      valid += s_red[q][0];
     }
-    unsigned long long* c = (unsigned long long*)a.counters;
-    if (v[0]) atomicAdd(&c[ARGUS_C_N_VALID], v[0]);
-    if (v[1]) atomicAdd(&c[ARGUS_C_N_BAD_KIND], v[1]);
-    if (v[2]) atomicAdd(&c[ARGUS_C_N_BAD_REGION], v[2]);
-    if (v[3]) atomicAdd(&c[ARGUS_C_N_BEGIN], v[3]);
-    if (v[0] - v[3]) atomicAdd(&c[ARGUS_C_N_END], v[0] - v[3]);
-    if (s_runs) atomicAdd((unsigned long long*)&a.plan->n_runs, s_runs);
-    if (v[0]) {
-      atomicMin(&c[ARGUS_C_TS_MIN], v[4]);
-      atomicMax(&c[ARGUS_C_TS_MAX], v[5]);
-      atomicMin(&c[ARGUS_C_CTX_MIN], v[6]);
-      atomicMax(&c[ARGUS_C_CTX_MAX], v[7]);
+    unsigned long long* c = (unsigned long long*)&a.counters[slot[k]];
+    if (k < 5) {
+      if (v) atomicAdd(c, v);
+    } else if (valid) {
+      if (k < 7) atomicMin(c, v);
+      else atomicMax(c, v);
     }
+    if (k == 0 && s_runs) atomicAdd((unsigned long long*)&a.plan->n_runs, s_runs);
   }
   for (int i = threadIdx.x; i < 4 * kRadixBins; i += 256) {
     const uint32_t h = (&s_hist[0][0])[i];
