@@ -358,10 +358,16 @@ __global__ __launch_bounds__(256) void k_agg_reduce(const uint64_t* part, uint32
   const bool is_min = f == 2 || f == 5, is_max = f == 3 || f == 6;
   const uint32_t b0 = blockIdx.y * kAggRun, b1 = b0 + kAggRun < nblk ? b0 + kAggRun : nblk;
   uint64_t v = is_min ? kU64Max : 0;
-#pragma unroll 8
-  for (uint32_t b = b0; b < b1; ++b) {
-    const uint64_t x = part[((uint64_t)b * kAggFields + f) * R + r];
-    v = is_min ? (x < v ? x : v) : is_max ? (x > v ? x : v) : v + x;
+  // all loads of the run in flight together (past its end: the last block
+  // again, dropped)
+  uint64_t x[kAggRun];
+#pragma unroll
+  for (uint32_t u = 0; u < kAggRun; ++u)
+    x[u] = part[((uint64_t)(b0 + u < b1 ? b0 + u : b1 - 1) * kAggFields + f) * R + r];
+#pragma unroll
+  for (uint32_t u = 0; u < kAggRun; ++u) {
+    const uint64_t y = b0 + u < b1 ? x[u] : (is_min ? kU64Max : 0);
+    v = is_min ? (y < v ? y : v) : is_max ? (y > v ? y : v) : v + y;
   }
   if (v == (is_min ? kU64Max : 0)) return;
   constexpr int col[kAggFields] = {ARGUS_RS_COUNT,      ARGUS_RS_INCL_SUM,      ARGUS_RS_INCL_MIN,
