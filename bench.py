@@ -226,8 +226,8 @@ def bench_part(args, d: dict, rec_np: np.ndarray, dev) -> dict:
             return attribute_samples(inst, cnt, smp, R, P, metrics=met)
         units, unit_name = S, "samples"
         # each sample, its owner instance and a count update; the [P][R] table
-        # cleared, read twice, alpha written and read (2 metrics)
-        per_call = 56.0 * S + 8.0 * P * R * 6
+        # cleared and read (twice beyond 256 regions), alpha written and read
+        per_call = 56.0 * S + 8.0 * P * R * (4 if R <= 256 else 5)
         what = (f"{S} PC samples over {P} PCs (2 metrics) on the instances of the "
                 f"{WORKLOADS[args.config]}")
     elif part == "scope":
@@ -237,10 +237,14 @@ def bench_part(args, d: dict, rec_np: np.ndarray, dev) -> dict:
         if R <= 4096:
             # chunk-local ordinals (context and region half of each instance in,
             # ordinal out); the carry scan over the chunks' counts (R words per
-            # chunk of 4096: written, read, read and written); statistics
-            # (instance, exclusive time, ordinal in and out, histogram key out);
-            # the histogram pass over the keys
-            per_call = nb * (16.0 + 4.0 + 16.0 * R / 4096 + 32.0 + 8.0 + 4.0 + 4.0 + 4.0 + 4.0)
+            # chunk of 4096: written, read, read and written); the ordinals
+            # completed (in and out); per instance in scope itself, its exclusive
+            # time and its histogram key, out and in
+            per_call = None
+
+            def call_bytes(r):
+                return (nb * (16.0 + 4.0 + 16.0 * R / 4096 + 4.0 + 4.0)
+                        + int(r["counters"].cpu().numpy()[1]) * (32.0 + 8.0 + 4.0 + 4.0))
         else:
             passes = 2 if R > 256 else 1
             # sort passes; ordinals (sorted element in, pair out; pair in, ordinal
@@ -256,11 +260,12 @@ def bench_part(args, d: dict, rec_np: np.ndarray, dev) -> dict:
             return join_probes(inst, cnt, pr, R)
         units, unit_name = len(pr_np), "probes"
 
-        def probe_bytes(r):
-            # the reference sort pass(es); the join (probe and reference
-            # instance in, outputs and sort element out); the sort passes the
-            # library runs: those whose byte of the latency or the instance
-            # code is not the same for every probe
+        def call_bytes(r):
+            # the index of the reference (context and region half of each
+            # instance in, place out; beyond 256 regions two sort passes); the
+            # join (probe and reference instance in, outputs and sort element
+            # out); the sort passes the library runs: those whose byte of the
+            # latency or the instance code is not the same for every probe
             ref = r["ref"][:len(pr_np)].cpu().numpy().astype(np.uint64)
             joined = ref != np.uint64(0xFFFFFFFF)
             lat = np.where(joined, pr_np["t_end"] - pr_np["t_start"], np.uint64(0))
@@ -273,8 +278,8 @@ def bench_part(args, d: dict, rec_np: np.ndarray, dev) -> dict:
                 d = np.bitwise_or.reduce(v) ^ np.bitwise_and.reduce(v)
                 return sum(1 for k in range(nbytes) if (int(d) >> (8 * k)) & 0xFF)
             passes = varying(lat, 8) + varying(code, 4)
-            return (nb * 48.0 * (2 if R > 256 else 1)
-                    + len(pr_np) * (64.0 + 32.0 + 48.0 * passes))
+            return (nb * (48.0 * 2 if R > 256 else 18.0)
+                    + len(pr_np) * (64.0 + 12.0 + 12.0 + 24.0 * passes))
         per_call = None
         what = (f"{len(pr_np)} probes (3 operations x 16 iterations x 5 repeats per warp) joined "
                 f"to the {WORKLOADS[args.config]}")
@@ -303,7 +308,7 @@ def bench_part(args, d: dict, rec_np: np.ndarray, dev) -> dict:
     torch.cuda.synchronize()
     ms = e0.elapsed_time(e1) / args.steps
     if per_call is None:
-        per_call = probe_bytes(res[-1])
+        per_call = call_bytes(res[-1])
     del res
     ra.close()
     gbs = per_call / (ms * 1e-3) / 1e9
