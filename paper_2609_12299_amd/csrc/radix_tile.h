@@ -56,13 +56,12 @@ struct RadixShared {
   uint32_t wave[kSortWaves][kRadixBins];  // per-wave counts, then wave prefixes
   uint32_t off[kRadixBins];      // global start of each digit
   uint32_t start[kRadixBins];    // tile-local start of each digit
-  uint32_t gbase[kRadixBins];    // global start of this tile's digit run
+  uint32_t gbase[kRadixBins];    // global start of this tile's digit run, less its tile-local start
   uint32_t scr[kSortWaves];
   uint32_t total;
   __align__(16) uint64_t key[kSortTile];
   uint32_t pay[kSortTile];
   uint32_t cw[kSortTile];
-  uint8_t dig[kSortTile];
 };
 
 struct RadixArgs {
@@ -325,7 +324,7 @@ __device__ __forceinline__ void radix_tile(const RadixArgs& a, RadixShared& s, c
       }
       st_agent(lb, radix_word(kFlagIncl, ps.tag, (excl + tot) & kRadixVal));
     }
-    s.gbase[dgt] = s.off[dgt] + (uint32_t)excl;
+    s.gbase[dgt] = s.off[dgt] + (uint32_t)excl - s.start[dgt];
   }
   __syncthreads();
 
@@ -337,29 +336,30 @@ __device__ __forceinline__ void radix_tile(const RadixArgs& a, RadixShared& s, c
       const uint32_t lp = s.start[d] + s.wave[w][d] + rank[r];
       s.key[lp] = key[r];
       if (RAW != 3) s.pay[lp] = pay[r];
-      s.cw[lp] = cw[r];
-      s.dig[lp] = (uint8_t)d;
+      if (wide) s.cw[lp] = cw[r];
     }
   }
   __syncthreads();
 
   // Write out: consecutive staged elements of one digit go to consecutive
-  // global positions.
+  // global positions.  (The digit is taken from the staged key again: the
+  // tile's LDS accesses conflict, so it stages as little as it can.)
   const uint32_t total = s.total;
   uint64_t* kd = a.key[ps.dst];
   uint32_t* pd = a.pay[ps.dst];
   uint32_t* cd = a.ctxw[ps.dst];
   const uint32_t n_out = ps.n_out;
   for (uint32_t i = tid; i < total; i += kSortThreads) {
-    const uint32_t d = s.dig[i];
-    const uint32_t gp = s.gbase[d] + (i - s.start[d]);
+    const uint64_t k = s.key[i];
+    const uint32_t c = wide ? s.cw[i] : 0u;
+    const uint32_t gp = s.gbase[digit(k, c)] + i;
     if (gp >= n_out) {
       flag_internal_error(a.counters, 2);
       continue;
     }
-    st_agent(&kd[gp], s.key[i]);
+    st_agent(&kd[gp], k);
     if (RAW != 3) st_agent(&pd[gp], s.pay[i]);
-    if (wide) st_agent(&cd[gp], s.cw[i]);
+    if (wide) st_agent(&cd[gp], c);
   }
   __syncthreads();
 }
