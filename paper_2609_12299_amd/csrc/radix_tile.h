@@ -53,9 +53,8 @@ constexpr uint64_t kRadixVal = 0xFFFFFFFFull;
 
 struct RadixShared {
   uint32_t ticket;
-  uint32_t wave[kSortWaves][kRadixBins];  // per-wave counts, then wave prefixes
+  uint32_t wave[kSortWaves][kRadixBins];  // per-wave counts, then their places in the staged tile
   uint32_t off[kRadixBins];      // global start of each digit
-  uint32_t start[kRadixBins];    // tile-local start of each digit
   uint32_t gbase[kRadixBins];    // global start of this tile's digit run, less its tile-local start
   uint32_t scr[kSortWaves];
   uint32_t total;
@@ -268,23 +267,28 @@ __device__ __forceinline__ void radix_tile(const RadixArgs& a, RadixShared& s, c
   // tile-local starts.
   const uint32_t dgt = (uint32_t)tid;
   const bool digits = dgt < (uint32_t)kRadixBins;
-  uint32_t tot = 0;
+  uint32_t tot = 0, wc[kSortWaves];
   uint64_t* lb = a.lb + tile * kRadixBins + dgt;
   if (digits) {
 #pragma unroll
     for (int q = 0; q < kSortWaves; ++q) {
-      const uint32_t c = s.wave[q][dgt];
-      s.wave[q][dgt] = tot;
-      tot += c;
+      wc[q] = s.wave[q][dgt];
+      tot += wc[q];
     }
     // published before the tile's own scan: the successors wait for it
     st_agent(lb, radix_word(tile == 0 ? kFlagIncl : kFlagAgg, ps.tag, tot));
   }
-  {
-    uint32_t all;
-    const uint32_t ex = sort_excl_scan(tot, s.scr, &all);
-    if (digits) s.start[dgt] = ex;
-    if (tid == 0) s.total = all;
+  uint32_t all;
+  const uint32_t start = sort_excl_scan(tot, s.scr, &all);  // the digit's place in the staged tile
+  if (tid == 0) s.total = all;
+  if (digits) {
+    // each wave's first place of the digit
+    uint32_t at = start;
+#pragma unroll
+    for (int q = 0; q < kSortWaves; ++q) {
+      s.wave[q][dgt] = at;
+      at += wc[q];
+    }
   }
   // Decoupled look-back on the count of this digit in earlier tiles.
   if (digits) {
@@ -324,7 +328,7 @@ __device__ __forceinline__ void radix_tile(const RadixArgs& a, RadixShared& s, c
       }
       st_agent(lb, radix_word(kFlagIncl, ps.tag, (excl + tot) & kRadixVal));
     }
-    s.gbase[dgt] = s.off[dgt] + (uint32_t)excl - s.start[dgt];
+    s.gbase[dgt] = s.off[dgt] + (uint32_t)excl - start;
   }
   __syncthreads();
 
@@ -333,7 +337,7 @@ __device__ __forceinline__ void radix_tile(const RadixArgs& a, RadixShared& s, c
   for (int r = 0; r < kSortItems; ++r) {
     const uint32_t d = dig[r];
     if (d < 256) {
-      const uint32_t lp = s.start[d] + s.wave[w][d] + rank[r];
+      const uint32_t lp = s.wave[w][d] + rank[r];
       s.key[lp] = key[r];
       if (RAW != 3) s.pay[lp] = pay[r];
       if (wide) s.cw[lp] = cw[r];
