@@ -1153,7 +1153,8 @@ __global__ __launch_bounds__(kScThreads) void k_pr_index(ProbeArgs a) {
   for (int r = 0; r < kScRounds; ++r)
     if (rk[r] != 0xFFFFFFFFu) s_list[s_lstart[reg[r]] + s_wave[w][reg[r]] + rk[r]] = (uint16_t)(e0 + (uint32_t)r * 64);
   __syncthreads();
-  // (the list's end past the tile's valid instances is never read)
+  // (the list's end past the tile's valid instances, up to seven of a last
+  // request, is never read)
   uint4* dst = reinterpret_cast<uint4*>(a.list + tile * kScTile);
   const uint4* src = reinterpret_cast<const uint4*>(s_list);
   for (uint32_t i = tid; i < (s_carry + 7) / 8; i += kScThreads) dst[i] = src[i];
@@ -1971,13 +1972,17 @@ PrLayout pr_layout(uint64_t max_inst, uint64_t np) {
   Carver c;
   PrLayout L{};
   const uint64_t tiles = tiles_for(max_inst), n = np ? np : 1;
+  // the reference is sorted or indexed, as the regions go: the index lies
+  // where the sort's buffers would
+  Carver ix = c;
   L.ref = carve_sort(c, max_inst);
+  L.list = ix.take(sizeof(uint16_t) * 8 * ceil_div(max_inst ? max_inst : 1, 8));
+  L.lstart = ix.take(sizeof(uint16_t) * 256 * tiles);
+  L.tctx = ix.take(sizeof(uint32_t) * tiles);
+  L.rtot = ix.take(sizeof(uint32_t) * 256);
+  c.o = std::max(c.o, ix.o);
   L.hist = c.take(sizeof(uint32_t) * 256 * tiles);
   L.bsum = c.take(sizeof(uint32_t) * scan_blocks_for(256 * tiles));
-  L.list = c.take(sizeof(uint16_t) * kScTile * tiles);
-  L.lstart = c.take(sizeof(uint16_t) * 256 * tiles);
-  L.tctx = c.take(sizeof(uint32_t) * tiles);
-  L.rtot = c.take(sizeof(uint32_t) * 256);
   for (int k = 0; k < 2; ++k) {
     L.key[k] = c.take(sizeof(uint64_t) * n);
     L.code[k] = c.take(sizeof(uint32_t) * n);

@@ -1,0 +1,38 @@
+"""Workspace sizes that callers may hold fixed buffers of: a call never asks for
+more than it did when the ABI's version 1 was first published."""
+from __future__ import annotations
+
+import random
+
+import pytest
+
+from paper_2609_12299_amd import attr
+
+TILE = 4096  # instances (or probes) per tile of the digit tables
+
+
+def take(nbytes: int) -> int:
+    return (max(nbytes, 1) + 255) // 256 * 256
+
+
+def sizes(limit: int):
+    rng = random.Random(5)
+    edges = [0, 1, 7, 8, 9, 127, 128, TILE - 1, TILE, TILE + 1, 2 * TILE + 1, limit]
+    return edges + [min(limit, int(2 ** rng.uniform(0, 31))) for _ in range(60)]
+
+
+def first_probes(m: int, p: int) -> int:
+    """Two sorts (reference, probes) of 32 bytes per element, their digit
+    table and its scan sums, a flag per probe, the sort state and 4096 blocks'
+    digit masks."""
+    tiles = max(-(-max(m, 1) // TILE), -(-max(p, 1) // TILE))
+    scan = max(-(-256 * tiles // 4096), -(-p // 4096))
+    return (4 * take(8 * max(m, 1)) + 4 * take(8 * max(p, 1)) + take(1024 * tiles) + take(4 * scan)
+            + take(4 * max(p, 1)) + take(32) + take(32 * 4096))
+
+
+@pytest.mark.parametrize("m", sizes((1 << 31) - 1))
+def test_probe_join(m):
+    for p in sizes((1 << 31) - 1):
+        need = attr.argus_attr_probes_workspace_bytes(m, p)
+        assert 0 < need <= first_probes(m, p), (m, p)
