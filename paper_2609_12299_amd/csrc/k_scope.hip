@@ -1524,7 +1524,8 @@ struct HandoffArgs {
   uint32_t* comp;    // instances of level <= L in canonical order
   uint64_t* status;  // [tiles] look-back words of the compaction (count, flags)
   uint32_t* tctr;    // tile counter of the compaction
-  uint32_t* atl;     // [compaction blocks] instances of level L each saw
+  uint32_t* atl;     // [compaction blocks] instances of level L each saw, where pair block 0 later
+                     // dumps (it has added them up by then)
   uint32_t cblocks;  // compaction blocks launched
   uint64_t* mtot;    // instances compacted
   uint64_t* pairs;  // [R][R][4]: count, sum, min, max (the output)
@@ -1684,6 +1685,7 @@ constexpr uint32_t kHoSlots = 4096;
 constexpr int kHoProbes = 16;
 constexpr uint32_t kHoHashShift = 20;  // 32 - log2(kHoSlots)
 constexpr uint32_t kHoMaxDumps = 256;  // pair blocks at most: one per compute unit
+static_assert(sizeof(uint32_t) * kHoMaxCompact <= sizeof(uint64_t) * 4 * kHoSlots, "level counts lie in one dump");
 
 __device__ __forceinline__ uint32_t ho_hash(uint32_t key) { return key * 2654435761u; }
 
@@ -2280,7 +2282,7 @@ extern "C" int argus_attr_probes(const argus_probes_config* cfg, const argus_pro
 namespace {
 
 struct HoLayout {
-  size_t comp, status, tctr, atl, mtot, dkey, dval, total;
+  size_t comp, status, tctr, mtot, dkey, dval, total;
 };
 HoLayout ho_layout(uint64_t max_instances, uint32_t R) {
   Carver c;
@@ -2289,7 +2291,6 @@ HoLayout ho_layout(uint64_t max_instances, uint32_t R) {
   L.comp = c.take(sizeof(uint32_t) * m);
   L.status = c.take(sizeof(uint64_t) * tiles_for(m));
   L.tctr = c.take(sizeof(uint32_t));
-  L.atl = c.take(sizeof(uint32_t) * kHoMaxCompact);
   L.mtot = c.take(sizeof(uint64_t));
   L.dkey = c.take(sizeof(uint32_t) * (uint64_t)kHoMaxDumps * kHoSlots);
   L.dval = c.take(sizeof(uint64_t) * 4 * (uint64_t)kHoMaxDumps * kHoSlots);
@@ -2334,10 +2335,10 @@ extern "C" int argus_attr_handoffs(const argus_handoffs_config* cfg, const argus
   a.comp = (uint32_t*)(base + HL.comp);
   a.status = (uint64_t*)(base + HL.status);
   a.tctr = (uint32_t*)(base + HL.tctr);
-  a.atl = (uint32_t*)(base + HL.atl);
   a.mtot = (uint64_t*)(base + HL.mtot);
   a.dkey = (uint32_t*)(base + HL.dkey);
   a.dval = (uint64_t*)(base + HL.dval);
+  a.atl = (uint32_t*)a.dval;
   a.pairs = io->d_pairs;
   a.hist = io->d_hist;
   a.parent_gap = io->d_parent_gap;

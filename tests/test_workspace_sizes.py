@@ -36,3 +36,13 @@ def test_probe_join(m):
     for p in sizes((1 << 31) - 1):
         need = attr.argus_attr_probes_workspace_bytes(m, p)
         assert 0 < need <= first_probes(m, p), (m, p)
+
+
+@pytest.mark.parametrize("m", sizes((1 << 31) - 1))
+def test_handoffs(m):
+    """The compacted indices, a look-back word per tile, two counters, and 256
+    hash tables of 4096 pairs (key, and count, sum, least, largest)."""
+    need = attr.argus_attr_handoffs_workspace_bytes(m, 7)
+    first = (take(4 * max(m, 1)) + take(8 * -(-max(m, 1) // TILE)) + take(4) + take(8)
+             + take(4 * 256 * 4096) + take(32 * 256 * 4096))
+    assert 0 < need <= first, m
