@@ -830,6 +830,7 @@ hipError_t launch_merge(const RunArgs& a, int round, hipStream_t s) {
 // is summed again with 64-bit gaps by a second, rarely busy kernel.
 
 constexpr int32_t kLBias = kMergeTile;  // |l| <= 4096 inside a tile
+constexpr uint32_t kTauMid = 1u << 31;  // see tile_sums_rows
 
 // Words of one tile record for KC classes: group | first << 32 | wide << 33,
 // then per class (delta | min << 32), S0, S1'[KC], S2'[NP], T[NP] (pairs
@@ -1145,11 +1146,15 @@ struct MsRows {
 //                                     + sum over events of y of s tau l'_x
 // (s = +-1; the other count does not move), and for C(l', 2) the count before
 // a BEGIN or after an END takes l's place: one multiply-add per event and
-// lane, into the lane's own LDS sum for the event's class.  The gaps go to
-// one bin per set of active classes, whose sums over supersets are the T.
-// The 64 groups of a block take equal stretches of consecutive events.
-// Products are signed 32 x 32 bits: a tile spanning 2^31 cycles or more is
-// left to the wide kernel.
+// lane, into the lane's own LDS sum for the event's class.  Products are
+// signed 32 x 32 bits, so tau is taken less 2^31, which holds every span
+// below 2^32; with f the summed product and c = 2^31 the sum is then
+//   (tau_first - c) f_before + sum over events of (tau - c) (change of f) + c f_after.
+// (Left to the wide kernel, 2^22 records whose tiles span 2^31 to 2^32 cycles
+// took 15.6 ms of a run that takes 0.46 this way.)
+// The gaps go to one bin per set of active classes, whose sums over supersets
+// are the T.  The 64 groups of a block take equal stretches of consecutive
+// events.
 template <int KC>
 __device__ __forceinline__ bool tile_sums_rows(uint64_t* se, uint32_t cnt, bool first, MsRows<KC>& ss,
                                                uint64_t* rec, uint32_t es) {
@@ -1164,7 +1169,7 @@ __device__ __forceinline__ bool tile_sums_rows(uint64_t* se, uint32_t cnt, bool 
   const uint64_t last_w = has_next ? ss.next : se[lpad(cnt - 1)];
   const uint64_t g = es >= 64 ? 0ull : (first_w >> es);
   const uint64_t head = (g & 0xFFFFFFFFull) | ((uint64_t)(first ? 1u : 0u) << 32);
-  if (((last_w >> kEvCodeBits) - (first_w >> kEvCodeBits)) >= (1ull << 31)) {
+  if (((last_w >> kEvCodeBits) - (first_w >> kEvCodeBits)) >= (1ull << 32)) {
     if (t == 0) rec[0] = head | (1ull << 33);
     return false;
   }
@@ -1208,17 +1213,17 @@ __device__ __forceinline__ bool tile_sums_rows(uint64_t* se, uint32_t cnt, bool 
 #pragma unroll
   for (int q = 0; q < NW; ++q) mp = ss.wm[q][y] < mp ? ss.wm[q][y] : mp;
   mp += kLBias;
-  // ---- the sums
-  const uint32_t t_end = (uint32_t)(last_w >> kEvCodeBits);
+  // ---- the sums (tau less 2^31)
+  const uint32_t t_mid = (uint32_t)(last_w >> kEvCodeBits) - kTauMid;
   int32_t l = pre + kLBias;
   uint64_t s1 = 0;
   uint64_t* acc = &ss.a[w][0][lane];
   uint64_t cur = se[lpad(d < cnt ? d : cnt)];
-  uint32_t tau = t_end - (uint32_t)(cur >> kEvCodeBits);
+  uint32_t tau = t_mid - (uint32_t)(cur >> kEvCodeBits);
 #pragma unroll 2
   for (uint32_t j = 0; j < nval; ++j) {
     const uint64_t nx = se[lpad(d + j + 1)];
-    const uint32_t tau_nx = t_end - (uint32_t)(nx >> kEvCodeBits);
+    const uint32_t tau_nx = t_mid - (uint32_t)(nx >> kEvCodeBits);
     const uint32_t code = code_of(cur), c1 = code - 1u, cls = c1 >> 1;
     const int32_t neg = -(int32_t)(c1 & 1u);  // -1: END
     const int32_t ln = l + (cls == y ? 1 + 2 * neg : 0);
@@ -1258,7 +1263,7 @@ __device__ __forceinline__ bool tile_sums_rows(uint64_t* se, uint32_t cnt, bool 
   }
   __syncthreads();
   if (t < (uint32_t)NV) {
-    const uint64_t s0 = (uint32_t)(t_end - (uint32_t)(first_w >> kEvCodeBits));
+    const uint64_t s0 = (uint32_t)((uint32_t)(last_w >> kEvCodeBits) - (uint32_t)(first_w >> kEvCodeBits));
     uint64_t sum = 0;
     if (t == 0) {
       sum = s0;
@@ -1279,7 +1284,14 @@ __device__ __forceinline__ bool tile_sums_rows(uint64_t* se, uint32_t cnt, bool 
       const uint32_t py = px + k - row;
       if (k0 < (uint32_t)NP) {
         constexpr uint64_t B = (uint64_t)kLBias;
-        sum = px == py ? ss.m[px][px] + s0 * (B * (B - 1) / 2) : ss.m[px][py] + ss.m[py][px] + s0 * (B * B);
+        uint64_t lx = B, ly = B;  // the counts after the tile's last event
+#pragma unroll
+        for (int q = 0; q < NW; ++q) {
+          lx += (uint64_t)(int64_t)ss.wd[q][px];
+          ly += (uint64_t)(int64_t)ss.wd[q][py];
+        }
+        sum = px == py ? ss.m[px][px] + (s0 - kTauMid) * (B * (B - 1) / 2) + kTauMid * (lx * (lx - 1) / 2)
+                       : ss.m[px][py] + ss.m[py][px] + (s0 - kTauMid) * (B * B) + kTauMid * (lx * ly);
       } else {
         const uint32_t m = (1u << px) | (1u << py);
 #pragma unroll

@@ -1,8 +1,8 @@
 """The class-overlap sums of merged tiles, for every class count: five to
 eight classes are summed by parts, 8 lanes per event and a stretch of events per
 group of lanes, so tile fills around its 64 groups and the spans at which the
-32-bit time no longer holds (2^31; 2^32 for fewer classes) are where it can go
-wrong.  All integers: compared with the oracle bit for bit."""
+32-bit time no longer holds (2^32, and 2^31 where its products turn negative)
+are where it can go wrong.  All integers: compared with the oracle bit for bit."""
 from __future__ import annotations
 
 import numpy as np
@@ -58,3 +58,34 @@ def test_span(oracle_mod, span, K):
     g = gpu_run(rec, _params(K), with_plan=True)
     assert g.pop("_plan")["ev_merge"] == 1
     assert_parity(g, oracle_run(oracle_mod, rec, _params(K)), what=f"K={K} span={span}")
+
+
+@pytest.mark.parametrize("K", [4, 5, 8])
+def test_span_time(K):
+    """Tiles spanning up to 2^32 cycles are summed once, with 32-bit times: the last pass over them
+    takes as long as over short ones (the 64-bit kernel beyond takes 20 times as long)."""
+    import torch
+
+    from paper_2609_12299_amd import RegionAttribution
+    p = _params(K)
+    n, n_ctx = 1 << 20, 4096  # 1024 groups of 4 contexts, a tile of 1024 records each
+    rng = np.random.default_rng(K)
+    r = np.zeros(n, DTYPE)
+    r["ctx"] = np.arange(n) // (n // n_ctx)
+    r["kind"] = 1 + np.arange(n) % 2
+    r["region"] = np.repeat(rng.integers(0, K, n // 2), 2)
+    step = np.sort(rng.integers(0, 1000, (n_ctx, n // n_ctx)), axis=1).astype(np.uint64)
+    ms = {}
+    for scale in (1, 4_000_000):  # the longest tiles span 4e9 cycles: below 2^32, above 2^31
+        r["ts"] = (step * np.uint64(scale)).reshape(-1)
+        rec = torch.from_numpy(r.view(np.uint8)).to("cuda")
+        ra = RegionAttribution(p["num_regions"], K, p["region_class"], 2, n_ctx // 4, max_records=n)
+        for _ in range(2):
+            ra.run(rec)
+        ra.set_timing(True)
+        for _ in range(5):
+            ra.run(rec)
+        ms[scale] = min(t for name, t in ra.kernel_times() if name == "merge_sweep")
+        ra.close()
+    log(f"[gpu] last pass, {K} classes: {ms}")
+    assert ms[4_000_000] < 2 * ms[1]
