@@ -830,7 +830,6 @@ hipError_t launch_merge(const RunArgs& a, int round, hipStream_t s) {
 // is summed again with 64-bit gaps by a second, rarely busy kernel.
 
 constexpr int32_t kLBias = kMergeTile;  // |l| <= 4096 inside a tile
-constexpr uint32_t kTauMid = 1u << 31;  // see tile_sums_rows
 
 // Words of one tile record for KC classes: group | first << 32 | wide << 33,
 // then per class (delta | min << 32), S0, S1'[KC], S2'[NP], T[NP] (pairs
@@ -1128,6 +1127,7 @@ struct MsRows {
   static constexpr int NV = 1 + KC + KC * (KC + 1);  // S0, S1', S2', T
   int32_t wd[NW][8];
   int32_t wm[NW][8];
+  int32_t last[8];  // counts after the tile's last event
   uint64_t next;
   uint32_t has_next;
   uint64_t s1[NW][8];
@@ -1199,6 +1199,7 @@ __device__ __forceinline__ bool tile_sums_rows(uint64_t* se, uint32_t cnt, bool 
   int32_t pre = inc - dd;
 #pragma unroll
   for (int q = 0; q < NW; ++q) pre += q < (int)w ? ss.wd[q][y] : 0;
+  if (t >= (uint32_t)kMergeThreads - 8) ss.last[y] = pre + dd;
   {
     int32_t m0 = nval ? pre + lmin : 0x7FFFFFFF;
 #pragma unroll
@@ -1214,7 +1215,7 @@ __device__ __forceinline__ bool tile_sums_rows(uint64_t* se, uint32_t cnt, bool 
   for (int q = 0; q < NW; ++q) mp = ss.wm[q][y] < mp ? ss.wm[q][y] : mp;
   mp += kLBias;
   // ---- the sums (tau less 2^31)
-  const uint32_t t_mid = (uint32_t)(last_w >> kEvCodeBits) - kTauMid;
+  const uint32_t t_mid = (uint32_t)(last_w >> kEvCodeBits) - (1u << 31);
   int32_t l = pre + kLBias;
   uint64_t s1 = 0;
   uint64_t* acc = &ss.a[w][0][lane];
@@ -1283,15 +1284,12 @@ __device__ __forceinline__ bool tile_sums_rows(uint64_t* se, uint32_t cnt, bool 
       }
       const uint32_t py = px + k - row;
       if (k0 < (uint32_t)NP) {
-        constexpr uint64_t B = (uint64_t)kLBias;
-        uint64_t lx = B, ly = B;  // the counts after the tile's last event
-#pragma unroll
-        for (int q = 0; q < NW; ++q) {
-          lx += (uint64_t)(int64_t)ss.wd[q][px];
-          ly += (uint64_t)(int64_t)ss.wd[q][py];
-        }
-        sum = px == py ? ss.m[px][px] + (s0 - kTauMid) * (B * (B - 1) / 2) + kTauMid * (lx * (lx - 1) / 2)
-                       : ss.m[px][py] + ss.m[py][px] + (s0 - kTauMid) * (B * B) + kTauMid * (lx * ly);
+        constexpr uint32_t B = (uint32_t)kLBias, BB = B * B, BC = B * (B - 1) / 2;
+        // the counts after the tile's last event (at most 2 B: products fit 32 bits)
+        const uint32_t lx = B + (uint32_t)ss.last[px], ly = B + (uint32_t)ss.last[py];
+        const uint32_t f0 = px == py ? BC : BB, f1 = px == py ? lx * (lx - 1) / 2 : lx * ly;
+        sum = px == py ? ss.m[px][px] : ss.m[px][py] + ss.m[py][px];
+        sum += (uint64_t)(uint32_t)s0 * f0 + ((uint64_t)(int64_t)(int32_t)(f1 - f0) << 31);
       } else {
         const uint32_t m = (1u << px) | (1u << py);
 #pragma unroll
@@ -1304,13 +1302,10 @@ __device__ __forceinline__ bool tile_sums_rows(uint64_t* se, uint32_t cnt, bool 
     rec[0] = head;
 #pragma unroll
     for (int x = 0; x < KC; ++x) {
-      int32_t agg = 0, mn = 0x7FFFFFFF;
+      int32_t mn = 0x7FFFFFFF;
 #pragma unroll
-      for (int q = 0; q < NW; ++q) {
-        agg += ss.wd[q][x];
-        mn = ss.wm[q][x] < mn ? ss.wm[q][x] : mn;
-      }
-      rec[1 + x] = (uint64_t)(uint32_t)agg | ((uint64_t)(uint32_t)mn << 32);
+      for (int q = 0; q < NW; ++q) mn = ss.wm[q][x] < mn ? ss.wm[q][x] : mn;
+      rec[1 + x] = (uint64_t)(uint32_t)ss.last[x] | ((uint64_t)(uint32_t)mn << 32);
     }
   }
   return true;
