@@ -24,9 +24,8 @@
 
 namespace argus {
 
-// Counters of one phase: tickets at word 0, tiles done at word 16 (on its
-// own 64 bytes).
-ARGUS_DEV uint32_t* phase_ctr(uint32_t* ctrs, uint32_t phase) { return ctrs + phase * kPhaseWords; }
+// Counters of one phase: tickets at word 0, tiles done at word 8.
+ARGUS_DEV uint32_t* phase_ctr(uint32_t* ctrs, uint32_t phase) { return ctrs + kPhaseBase + phase * kPhaseWords; }
 
 // Every store and atomic of this wave has been acknowledged.
 ARGUS_DEV void drain_stores() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
@@ -39,24 +38,34 @@ ARGUS_DEV uint32_t phase_take(uint32_t* ctr, uint32_t* s_slot) {
   return *s_slot;
 }
 
-// The block's `mine` tiles are done (its agent-scope stores acknowledged).
-// Returns (in every thread) the tiles done so far, these included.
-ARGUS_DEV uint32_t phase_done(uint32_t* ctr, uint32_t mine, uint32_t* s_slot) {
+// The block's `mine` tiles are done (its agent-scope stores acknowledged);
+// the block whose tiles complete the phase's `total` releases the waiting
+// blocks.  Returns (in every thread) the tiles done so far, these included.
+ARGUS_DEV uint32_t phase_done(uint32_t* ctrs, uint32_t phase, uint32_t mine, uint32_t total, uint32_t* s_slot) {
   drain_stores();
   __syncthreads();
-  if (threadIdx.x == 0) *s_slot = atomicAdd(ctr + 16, mine) + mine;
+  if (threadIdx.x == 0) {
+    const uint32_t done = atomicAdd(phase_ctr(ctrs, phase) + 8, mine) + mine;
+    if (done == total) st_agent(&ctrs[phase], 1u);
+    *s_slot = done;
+  }
   __syncthreads();
   const uint32_t done = *s_slot;
   __syncthreads();
   return done;
 }
 
-// Waits until all `total` tiles of the phase are done (bounded, like the
-// look-back waits).
-ARGUS_DEV void phase_wait(uint32_t* ctr, uint32_t total, uint64_t* counters) {
+// Waits until all tiles of the phase are done (bounded, like the look-back
+// waits).  The word the blocks poll is written once and lies 256 bytes from
+// what others add to: polled by up to 512 blocks, the counter of the tiles
+// done kept the blocks still at work from adding to it (and to the tickets, 64
+// bytes away): four passes over 2^22 elements took 365 us, this way 178;
+// 2^20: 127, 84; 2^24: 907, 718.  (Several such words, or longer sleeps, were
+// no faster.)
+ARGUS_DEV void phase_wait(const uint32_t* ctrs, uint32_t phase, uint64_t* counters) {
   if (threadIdx.x == 0) {
     uint32_t spins = 0;
-    while (ld_agent(ctr + 16) < total) {
+    while (ld_agent(&ctrs[phase]) == 0) {
       if (++spins > kMaxSpins) {
         flag_internal_error(counters, 2048);
         break;
@@ -72,7 +81,7 @@ ARGUS_DEV void phase_wait(uint32_t* ctr, uint32_t total, uint64_t* counters) {
 // arrive: the agent-scope stores and atomics of all the others are then
 // visible to its agent-scope loads.  (In every thread.)
 ARGUS_DEV bool last_arrival(uint32_t* ctrs, uint32_t which, uint32_t total, uint32_t* s_slot) {
-  uint32_t* c = ctrs + kPhCount * kPhaseWords + which * kArriveWords;
+  uint32_t* c = ctrs + kPhaseBase + kPhCount * kPhaseWords + which * kArriveWords;
   drain_stores();
   __syncthreads();
   if (threadIdx.x == 0) {

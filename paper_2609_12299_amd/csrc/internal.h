@@ -276,8 +276,11 @@ struct RunArgs {
   Work w;
 };
 
-// Phase counters (chain.h): kPhaseWords words each, zeroed by k_init.
-constexpr uint32_t kPhaseWords = 32;
+// Phase counters (chain.h), zeroed by k_init: first a release word per
+// phase, then, 256 bytes on, the phases' counters.
+constexpr uint32_t kMaxPhases = 64;
+constexpr uint32_t kPhaseBase = kMaxPhases + 64;
+constexpr uint32_t kPhaseWords = 16;
 enum Phase {
   kPhCompact = 0,  // k_ctx_sort: runs compacted,
   kPhCtx = 1,      //   4 context passes,
@@ -291,13 +294,14 @@ enum Phase {
   kPhClear = 34,   // k_ctx_sort: look-back words cleared
   kPhCount = 35
 };
+static_assert(kPhCount <= kMaxPhases, "a release word per phase");
 // Arrivals at the end of a kernel are counted in kArriveGroups groups of
 // blocks, then over the groups: about 10 ns per atomic on one word make 2048
 // arrivals on one counter 20 us.
 constexpr uint32_t kArriveGroups = 16;
 constexpr uint32_t kArriveWords = 16 * (kArriveGroups + 1);  // 64 bytes per counter
 enum Arrive { kArIngest = 0, kArTsum = 1, kArTree = 2, kArCount = 3 };
-constexpr uint32_t kCtrWords = kPhCount * kPhaseWords + kArCount * kArriveWords;
+constexpr uint32_t kCtrWords = kPhaseBase + kPhCount * kPhaseWords + kArCount * kArriveWords;
 
 // Up to this many records k_init clears the look-back words of the record
 // sorts (half a byte per record); beyond it they are cleared by the sort that

@@ -456,8 +456,8 @@ __global__ __launch_bounds__(kSortThreads) void k_ev_sort(SweepArgs a) {
     for (uint32_t i = tid; i < 12 * kRadixBins; i += kSortThreads)
       if (s_hist[i]) atomicAdd(&a.hist[i], s_hist[i]);
     if (tid == 0 && s_nev) atomicAdd((unsigned long long*)&p->n_ev, s_nev);
-    phase_done(ctr, mine, &s.ticket);
-    phase_wait(ctr, tiles, a.r.counters);
+    phase_done(a.r.ctrs, kPhEvHist, mine, tiles, &s.ticket);
+    phase_wait(a.r.ctrs, kPhEvHist, a.r.counters);
   }
   const uint64_t n_ev = ld_agent(&p->n_ev);
   uint32_t act = digits_varying<12>(a.hist, 12);

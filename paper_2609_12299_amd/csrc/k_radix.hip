@@ -200,8 +200,8 @@ __global__ __launch_bounds__(kSortThreads, 4) void k_ctx_sort(CtxSortArgs a) {
     }
     // later phases may have more tiles than this one (up to 32 runs a chunk):
     // a block without a tile here stays
-    if (mine) phase_done(ctr, mine, &s.ticket);
-    phase_wait(ctr, tiles, a.r.counters);
+    if (mine) phase_done(a.r.ctrs, kPhCompact, mine, tiles, &s.ticket);
+    phase_wait(a.r.ctrs, kPhCompact, a.r.counters);
   } else if (a.r.clear_lb) {
     const uint64_t rows = ceil_div(n_records, kSortTile);
     const uint32_t tiles = (uint32_t)ceil_div(rows, 64);
@@ -213,8 +213,8 @@ __global__ __launch_bounds__(kSortThreads, 4) void k_ctx_sort(CtxSortArgs a) {
       clear_rows(a.r.lb, 64ull * t, 64ull * t + 64 < rows ? 64ull * t + 64 : rows);
       ++mine;
     }
-    if (mine) phase_done(ctr, mine, &s.ticket);
-    phase_wait(ctr, tiles, a.r.counters);
+    if (mine) phase_done(a.r.ctrs, kPhClear, mine, tiles, &s.ticket);
+    phase_wait(a.r.ctrs, kPhClear, a.r.counters);
   }
   const uint32_t* hist = runs ? a.run_hist : a.rec_hist;
   uint32_t act = digits_varying<4>(hist, 4);
@@ -355,8 +355,8 @@ __global__ __launch_bounds__(kSortThreads, 4) void k_full_sort(FullSortArgs a) {
       const uint32_t h = s_hist[i];
       if (h) atomicAdd(&a.hist[i], h);
     }
-    phase_done(ctr, mine, &s.ticket);
-    if (mine < tiles) phase_wait(ctr, tiles, a.r.counters);
+    phase_done(a.r.ctrs, kPhHist, mine, tiles, &s.ticket);
+    if (mine < tiles) phase_wait(a.r.ctrs, kPhHist, a.r.counters);
   }
   // pass k < 8: key digit k; 8 + k: raw context digit k (wide keys only)
   uint32_t act = digits_varying<8>(a.hist, nd);
@@ -394,7 +394,7 @@ __global__ __launch_bounds__(kSortThreads, 4) void k_full_sort(FullSortArgs a) {
     ++mine;
     if (vb + 1 == a.t.nblk) break;
   }
-  if (!mine || phase_done(ctr, mine, &s.ticket) != a.t.nblk) return;
+  if (!mine || phase_done(a.r.ctrs, kPhTsum, mine, a.t.nblk, &s.ticket) != a.t.nblk) return;
   mscan_top<kSortThreads>(a.t, ts, ceil_div(n_valid, kMatchTile));
   if (tid == 0) {
     p->rec_final = src;

@@ -1046,7 +1046,7 @@ constexpr uint32_t kPrJoinBlocks = 2048;
 constexpr uint32_t kPrTile = 1024;    // sorted probes per tile of k_pr_groups
 constexpr uint32_t kPrDigits = 12;    // latency bytes 0..7, instance code bytes 0..3
 constexpr uint32_t kPrPhGroups = kPrDigits;  // phase counters: one per sort pass, then the groups' tiles
-constexpr uint32_t kPrCtrWords = (kPrDigits + 1) * kPhaseWords;
+constexpr uint32_t kPrCtrWords = kPhaseBase + (kPrDigits + 1) * kPhaseWords;
 
 struct ProbeArgs {
   const argus_instance* inst;

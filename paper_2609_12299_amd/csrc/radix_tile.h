@@ -392,8 +392,8 @@ __device__ __forceinline__ uint32_t radix_phase(const RadixArgs& a, RadixShared&
     drain_stores();
     __syncthreads();
   } else if (mine && !last) {
-    phase_done(ctr, mine, &s.ticket);
-    phase_wait(ctr, tiles, a.counters);
+    phase_done(a.ctrs, phase, mine, tiles, &s.ticket);
+    phase_wait(a.ctrs, phase, a.counters);
   }
   return mine;
 }
