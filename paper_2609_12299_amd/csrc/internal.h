@@ -28,9 +28,8 @@ constexpr int kMatchThreads = 256;
 constexpr int kMatchItems = 8;
 constexpr int kMatchTile = kMatchThreads * kMatchItems;  // 2048 elements
 
-constexpr int kSweepThreads = 512;
-constexpr int kSweepItems = 4;
-constexpr int kSweepTile = kSweepThreads * kSweepItems;  // 2048 events
+constexpr int kSweepThreads = 256;  // of the sweep alone; inside the event sort kSortThreads
+constexpr int kSweepTile = 2048;    // events
 constexpr int kSweepSlots = 8;  // groups of one tile aggregated in LDS
 
 // Ordering overlap events by merging per-context runs (see k_merge.hip).

@@ -40,18 +40,18 @@ struct SweepShared {
   static constexpr int NP = KM * (KM + 1) / 2;
   uint64_t u[kSweepSlots][NP];
   uint64_t q[kSweepSlots][NP];
-  int32_t wd[kSweepThreads / 64][KM];
-  uint32_t wr[kSweepThreads / 64];
+  int32_t wd[kSortThreads / 64][KM];  // (a block has at most these waves)
+  uint32_t wr[kSortThreads / 64];
   int32_t cin[KM];
   uint32_t g0;
 };
 
-// One tile of 2048 sorted events.
-template <int KM>
+// One tile of 2048 sorted events, by NT threads.
+template <int KM, int NT>
 __device__ __forceinline__ void sweep_tile(const SweepArgs& a, SweepShared<KM>& s, const KeySpace& ks,
                                            uint64_t n, uint32_t buf, uint64_t tile) {
   constexpr int NP = KM * (KM + 1) / 2;
-  constexpr int IT = kSweepItems;
+  constexpr int IT = kSweepTile / NT;  // consecutive events per thread
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   auto& s_u = s.u;
   auto& s_q = s.q;
@@ -74,7 +74,7 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs& a, SweepShared<KM>& 
   auto load_one = [&](uint64_t i, uint32_t* g, uint64_t* t, uint32_t* py) {
     decode(gk[i], gp[i], wide ? gc[i] : 0u, g, t, py);
   };
-  for (int i = tid; i < kSweepSlots * NP; i += kSweepThreads) {
+  for (int i = tid; i < kSweepSlots * NP; i += NT) {
     (&s_u[0][0])[i] = 0;
     (&s_q[0][0])[i] = 0;
   }
@@ -204,7 +204,7 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs& a, SweepShared<KM>& 
     int32_t td[KM];
 #pragma unroll
     for (int k = 0; k < KM; ++k) td[k] = 0;
-    for (int qq = 0; qq < kSweepThreads / 64; ++qq) {
+    for (int qq = 0; qq < NT / 64; ++qq) {
       if (s_wr[qq]) {
         tr = 1;
 #pragma unroll
@@ -389,7 +389,7 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs& a, SweepShared<KM>& 
   flush(qg);
   __syncthreads();
   // ---- tile flush of the LDS slots (slot j: group g0 + j)
-  for (uint32_t i = tid; i < (uint32_t)(kSweepSlots * NP); i += kSweepThreads) {
+  for (uint32_t i = tid; i < (uint32_t)(kSweepSlots * NP); i += NT) {
     const uint32_t slot = i / NP, k = i % NP;
     const uint64_t gg = (uint64_t)g0 + slot;
     if (gg >= G) continue;
@@ -400,16 +400,15 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs& a, SweepShared<KM>& 
 }
 
 // Where the events cannot be merged (decided by k_mseg): their digit
-// histograms and number, a radix sort on (group, time offset), the sweep.
-// Event slot e is the begin (even) or end (odd) of instance e / 2.
+// histograms and number, a radix sort on (group, time offset), and the sweep
+// (KM 0: k_ev_sweep follows).  Event slot e is the begin (even) or end (odd) of
+// instance e / 2.
 template <int KM>
-__global__ __launch_bounds__(kSortThreads) void k_ev_sort(SweepArgs a) {
-  static_assert(kSortThreads == kSweepThreads && kSortTile == 2 * kSweepTile, "one block shape");
+__global__ __launch_bounds__(kSortThreads, KM <= 4 ? 4 : 1) void k_ev_sort(SweepArgs a) {
+  static_assert(kSortTile == 2 * kSweepTile, "two sweep tiles per sort tile");
   DevPlan* p = a.r.plan;
   if (p->ev_merge) return;  // merged events are swept by k_merge_sweep
   __shared__ RadixShared s;
-  static_assert(sizeof(SweepShared<KM>) <= sizeof(s.key), "the sweep shares the stage");
-  SweepShared<KM>& sw = *reinterpret_cast<SweepShared<KM>*>(s.key);
   __shared__ unsigned long long s_nev;
   const uint32_t tid = threadIdx.x;
   KeySpace ks = p->rec;
@@ -427,30 +426,50 @@ __global__ __launch_bounds__(kSortThreads) void k_ev_sort(SweepArgs a) {
     // sweep look-back words: at most one event per record
     const uint64_t slb_words = 8 * ceil_div(p->n_records, kSweepTile);
     uint32_t* ctr = phase_ctr(a.r.ctrs, kPhEvHist);
-    uint32_t mine = 0;
+    uint32_t mine = 0, n_ev = 0;
     for (;;) {
       const uint32_t t = phase_take(ctr, &s.ticket);
       if (t >= tiles) break;
       // the look-back words of the sort tile and of its two sweep tiles
       if (tid < (uint32_t)kRadixBins) st_agent(&a.r.lb[(uint64_t)t * kRadixBins + tid], 0ull);
       if (tid < 16 && 16ull * t + tid < slb_words) st_agent(&a.slb[16ull * t + tid], 0ull);
-      uint32_t n_ev = 0;
-      for (int r = 0; r < kSortItems; ++r) {
-        const uint64_t e = (uint64_t)t * kSortTile + (uint32_t)r * kSortThreads + tid;
-        if (e >= slots) continue;
-        const argus_instance x = a.r.inst[e >> 1];
-        const uint64_t g = a.r.shift >= 32 ? 0 : (x.ctx_key >> a.r.shift);
-        if (x.region_id != x.end_region_id || a.r.region_class[x.region_id] >= a.r.K || g >= a.r.G) continue;
-        ++n_ev;
-        const uint64_t t_off = ((e & 1) ? x.t_end : x.t_begin) - ks.ts_min;
-        const uint64_t k = wide ? t_off : ((ks.ts_bits >= 64 ? 0 : (g << ks.ts_bits)) | t_off);
-        for (uint32_t d = 0; d < nd; ++d) atomicAdd(&s_hist[d * kRadixBins + ((uint32_t)(k >> (8 * d)) & 0xFFu)], 1u);
-        if (wide)
-          for (uint32_t d = 0; d < 4; ++d) atomicAdd(&s_hist[(8 + d) * kRadixBins + ((uint32_t)(g >> (8 * d)) & 0xFFu)], 1u);
+      // an instance per lane, both its events; all loads in flight together
+      // (past the end: the last instance again, not counted).  The digits that
+      // a wave's events share (the group, high time digits) are added once:
+      // an add per lane on one address takes the lanes one after another
+      // (2^24 skewed records: 198 us, this way 108).
+      constexpr int kPer = kSortTile / 2 / kSortThreads;
+      const uint64_t i0 = (uint64_t)t * (kSortTile / 2) + tid, nb = slots >> 1;
+      const uint4* inst = reinterpret_cast<const uint4*>(a.r.inst);
+      uint4 h0[kPer], h1[kPer];
+      uint32_t cl[kPer];
+#pragma unroll
+      for (int r = 0; r < kPer; ++r) {
+        const uint64_t i = i0 + (uint32_t)r * kSortThreads, ic = i < nb ? i : nb - 1;
+        h0[r] = inst[2 * ic];
+        h1[r] = inst[2 * ic + 1];
       }
-      if (n_ev) atomicAdd(&s_nev, (unsigned long long)n_ev);
+#pragma unroll
+      for (int r = 0; r < kPer; ++r) cl[r] = a.r.region_class[h1[r].w & 0xFFFFu];
+#pragma unroll
+      for (int r = 0; r < kPer; ++r) {
+        const uint64_t g = a.r.shift >= 32 ? 0 : (h1[r].x >> a.r.shift);
+        const bool ok = i0 + (uint32_t)r * kSortThreads < nb && (h1[r].w & 0xFFFFu) == h1[r].w >> 16 &&
+                        cl[r] < a.r.K && g < a.r.G;
+        n_ev += ok ? 2u : 0u;
+#pragma unroll
+        for (int end = 0; end < 2; ++end) {
+          const uint64_t t_off = (end ? join64(h0[r].z, h0[r].w) : join64(h0[r].x, h0[r].y)) - ks.ts_min;
+          const uint64_t k = wide ? t_off : ((ks.ts_bits >= 64 ? 0 : (g << ks.ts_bits)) | t_off);
+          for (uint32_t d = 0; d < nd; ++d) hist_digit(s_hist + d * kRadixBins, (uint32_t)(k >> (8 * d)) & 0xFFu, ok);
+          if (wide)
+            for (uint32_t d = 0; d < 4; ++d)
+              hist_digit(s_hist + (8 + d) * kRadixBins, (uint32_t)(g >> (8 * d)) & 0xFFu, ok);
+        }
+      }
       ++mine;
     }
+    if (n_ev) atomicAdd(&s_nev, (unsigned long long)n_ev);
     if (!mine) return;  // the blocks with a tile are as many as any later phase has tiles
     __syncthreads();
     for (uint32_t i = tid; i < 12 * kRadixBins; i += kSortThreads)
@@ -474,29 +493,63 @@ __global__ __launch_bounds__(kSortThreads) void k_ev_sort(SweepArgs a) {
     ps.n_out = (uint32_t)n_ev;
     ps.n_elems = src == 2 ? slots : n_ev;
     radix_offsets(s, a.hist + d * kRadixBins);
+    const bool last = (act >> (d + 1)) == 0;
     bool fin;
-    const uint32_t mine = radix_phase<2>(a.r, s, ks, ps, kPhEv + d, false, &fin);
+    const uint32_t mine = radix_phase<2>(a.r, s, ks, ps, kPhEv + d, KM == 0 && last, &fin);
     src = ps.dst;
     if (fin && tid == 0) {
       note_slot(p->es[d], d < 8 ? 4 + d : d - 8, ps);
-      p->ev_slots = slots;
-      p->ev = ks;
+      if (last) {
+        p->ev_slots = slots;
+        p->ev = ks;
+        p->ev_final = src;
+      }
     }
     if (!mine) return;
   }
-  // the sweep reads with plain loads: what this XCD's caches hold of the
-  // buffers is dropped first
-  if (tid < 64) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-  __syncthreads();
-  const uint32_t tiles = (uint32_t)ceil_div(n_ev, kSweepTile);
-  uint32_t* ctr = phase_ctr(a.r.ctrs, kPhSweep);
-  for (;;) {
-    const uint32_t t = phase_take(ctr, &s.ticket);
-    if (t >= tiles) break;
-    sweep_tile<KM>(a, sw, ks, n_ev, src, t);
-    if (t + 1 == tiles && tid == 0) p->ev_final = src;
+  if constexpr (KM > 0) {
+    static_assert(sizeof(SweepShared<KM>) <= sizeof(s.key), "the sweep shares the stage");
+    SweepShared<KM>& sw = *reinterpret_cast<SweepShared<KM>*>(s.key);
+    // the sweep reads with plain loads: what this XCD's caches hold of the
+    // buffers is dropped first
+    if (tid < 64) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    __syncthreads();
+    const uint32_t tiles = (uint32_t)ceil_div(n_ev, kSweepTile);
+    uint32_t* ctr = phase_ctr(a.r.ctrs, kPhSweep);
+    for (;;) {
+      const uint32_t t = phase_take(ctr, &s.ticket);
+      if (t >= tiles) break;
+      sweep_tile<KM, kSortThreads>(a, sw, ks, n_ev, src, t);
+    }
   }
 }
+
+// The sweep alone, after k_ev_sort<0>.
+template <int KM>
+__global__ __launch_bounds__(kSweepThreads) void k_ev_sweep(SweepArgs a) {
+  const DevPlan* p = a.r.plan;
+  if (p->ev_merge) return;
+  __shared__ SweepShared<KM> s;
+  __shared__ uint32_t s_slot;
+  const KeySpace ks = p->ev;
+  const uint64_t n_ev = p->n_ev;
+  const uint32_t tiles = (uint32_t)ceil_div(n_ev, kSweepTile), buf = p->ev_final;
+  uint32_t* ctr = phase_ctr(a.r.ctrs, kPhSweep);
+  for (;;) {
+    const uint32_t t = phase_take(ctr, &s_slot);
+    if (t >= tiles) break;
+    sweep_tile<KM, kSweepThreads>(a, s, ks, n_ev, buf, t);
+  }
+}
+
+// Beyond this many records the sweep is a kernel of its own: inside the sort's
+// it has 512 threads of 4 events, whose pair sums are flushed twice as often as
+// those of 256 threads of 8 events, and its registers leave the sort's passes
+// (8 classes) one block per compute unit instead of two.  Events of 2^22 decode
+// records, 8 classes: 940 us for the run in one kernel, 750 in two; 2^24: 3100,
+// 2300.  Up to there one kernel: the second launch costs every run whose
+// events are merged, which has nothing to sweep here, 1.3 to 2 us of 160.
+constexpr uint64_t kEvSplit = 1ull << 20;
 
 hipError_t launch_ev_sort(const RunArgs& a, hipStream_t s) {
   SweepArgs sa{};
@@ -505,9 +558,19 @@ hipError_t launch_ev_sort(const RunArgs& a, hipStream_t s) {
   sa.slb = a.w.slb;
   sa.ov_u = a.w.ov_mask;
   sa.ov_q = a.w.ov_q;
-  const void* kern = a.K <= 2 ? (const void*)k_ev_sort<2> : a.K <= 4 ? (const void*)k_ev_sort<4> : (const void*)k_ev_sort<8>;
   void* args[] = {&sa};
-  return hipLaunchKernel(kern, dim3(sort_blocks(kern, 2 * a.n)), dim3(kSortThreads), args, 0, s);
+  const bool split = a.n > kEvSplit;
+  const void* kern = split      ? (const void*)k_ev_sort<0>
+                     : a.K <= 2 ? (const void*)k_ev_sort<2>
+                     : a.K <= 4 ? (const void*)k_ev_sort<4>
+                                : (const void*)k_ev_sort<8>;
+  hipError_t e = hipLaunchKernel(kern, dim3(sort_blocks(kern, 2 * a.n)), dim3(kSortThreads), args, 0, s);
+  if (e != hipSuccess || !split) return e;
+  const void* sweep = a.K <= 2   ? (const void*)k_ev_sweep<2>
+                      : a.K <= 4 ? (const void*)k_ev_sweep<4>
+                                 : (const void*)k_ev_sweep<8>;
+  const uint64_t tiles = ceil_div(a.n, kSweepTile), fit = persistent_blocks(sweep, kSweepThreads);
+  return hipLaunchKernel(sweep, dim3((uint32_t)(tiles < fit ? tiles : fit)), dim3(kSweepThreads), args, 0, s);
 }
 
 // ------------------------------------------------------------- finalise

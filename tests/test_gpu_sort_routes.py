@@ -54,6 +54,19 @@ def test_routes(oracle_mod, n, order, wide):
                   what=f"{order} wide={wide}, both sorts forced")
 
 
+@pytest.mark.parametrize("K", [1, 3, 8])
+@pytest.mark.parametrize("n", [1 << 20, (1 << 20) + 1, (1 << 20) + 4096])
+def test_event_sort_split(oracle_mod, n, K):
+    """Up to 2^20 records the events are sorted and swept by one kernel, beyond by two."""
+    rec = _records(n, "late", False, K)
+    p = dict(P, num_classes=K, region_class=np.array([0, 1 % K, 2 % K, 7 % K, 0xFF, K - 1], np.uint8))
+    log(f"[gpu] event sort of {n} records, {K} classes")
+    g = gpu_run(rec, p, force_event=True, with_plan=True)
+    plan = g.pop("_plan")
+    assert plan["ev_merge"] == 0 and plan["n_ev"] > 0
+    assert_parity(g, oracle_run(oracle_mod, rec, p), what=f"n={n} K={K}")
+
+
 @pytest.mark.timeout(400)
 @pytest.mark.parametrize("order,radix", [("in_order", True), ("shuffled", False), ("late", False)])
 def test_beyond_init_clear(oracle_mod, order, radix):
