@@ -306,6 +306,12 @@ constexpr uint32_t kSoMaskShift = 16;         // bits 16..31: the chunk's granul
 constexpr uint32_t kSoGranule = kScTile / 16; // 256 instances
 static_assert(kSoMaxRegions <= 4096 && kScTile <= 4096, "12 bits each in a pending ordinal");
 constexpr uint32_t kSoSeg = 256;   // chunks per segment of the carry scan
+// Up to this many instances the granules are not marked and all are read:
+// marking costs the ordinal pass, whose waves walk a chunk in 64 dependent
+// rounds, 6 us (12 with a region set), and what it saves is less (iterations
+// 0..15, 1024 regions: 2^20 instances 251 us unmarked, 256 marked; 2^22: 298
+// each; 2^23: 362, 354).
+constexpr uint64_t kSoMarkMin = 1ull << 21;
 
 struct ScopeArgs {
   const argus_instance* inst;
@@ -331,6 +337,7 @@ struct ScopeArgs {
   uint32_t* segb;     // [segments][R] segment composites, then the carry entering each
   uint32_t* segm;     // [segments] 1: the segment passes its entering carry on
   uint32_t hslice, hslices, hranges;  // k_sc_hist: regions per slice, slices, ranges of granules
+  uint32_t hper;                      // granules a wave takes at a time (1..64)
 };
 
 // Fill kernel for the outputs that are accumulated.
@@ -543,6 +550,7 @@ __device__ __forceinline__ bool in_scope_ctx(const argus_scope& sc, uint32_t ctx
   return in_range32(ctx & sc.role_mask, sc.role_lo, sc.role_hi) && in_range32(group, sc.group_lo, sc.group_hi);
 }
 
+template <bool MARK>
 __global__ __launch_bounds__(kScThreads) void k_so_local(ScopeArgs a) {
   extern __shared__ uint32_t so_cnt[];  // [4 waves][R]: context start << 16 | count
   const uint64_t n = sb_count(a.s);
@@ -564,7 +572,7 @@ __global__ __launch_bounds__(kScThreads) void k_so_local(ScopeArgs a) {
     uint32_t f = F == L ? kSoWhole : 0u;
     if (base > 0 && ctx_before == F) f |= kSoPcont;
     if (base + cnt < n && ctx_after == L) f |= kSoCont;
-    uint32_t maybe = 0;  // granules that may hold instances in scope
+    uint32_t maybe = MARK ? 0u : 0xFFFFu;  // granules that may hold instances in scope
     for (uint32_t r = lane; r < a.R; r += 64) cr[r] = 0;
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
@@ -620,16 +628,18 @@ __global__ __launch_bounds__(kScThreads) void k_so_local(ScopeArgs a) {
         // the chunk's first context starts at position 0
         const bool pending = ok && (f & kSoPcont) && seg == 0;
         if (in) a.ordinal[base + e] = pending ? (kSoPending | (reg << 12) | local) : local;
-        // (a pending ordinal only grows by its carry)
-        const bool cand = ok && in_scope_ctx(a.sc, ctx) && local <= a.sc.iter_hi &&
-                          (pending || local >= a.sc.iter_lo) && (!a.region_mask || a.region_mask[rc] != 0);
-        if (__ballot(cand)) maybe |= 1u << (r0 / kSoGranule);
+        if (MARK) {
+          // (a pending ordinal only grows by its carry)
+          const bool cand = ok && in_scope_ctx(a.sc, ctx) && local <= a.sc.iter_hi &&
+                            (pending || local >= a.sc.iter_lo) && (!a.region_mask || a.region_mask[rc] != 0);
+          if (__ballot(cand)) maybe |= 1u << (r0 / kSoGranule);
+        }
         }
       }
     }
     if (lane == 0) {
       a.cflag[c] = f | (maybe << kSoMaskShift);
-      a.cneed[c] = 0;
+      a.cneed[c] = MARK ? 0u : 1u;
     }
     if (f & kSoCont) {
       // the last context's counts (its start: the last element's)
@@ -941,9 +951,11 @@ __global__ __launch_bounds__(kScStatThreads) void k_sc_stats(ScopeArgs a) {
 
 // The log2 histograms from the granules' keys: each block covers one slice of
 // regions in LDS over one range of the granules (the slices of a range are 8
-// blocks apart: on one XCD, whose L2 they share).  A wave takes 64 granules at
-// a time and, of those with keys, eight at once: a granule's keys are one
-// 16-byte load per lane.
+// blocks apart: on one XCD, whose L2 they share).  A wave takes up to 64
+// granules at a time (fewer where there are not 64 for each: 2^15 instances
+// took 28 us in the two waves that had any, 8 with one per wave) and,
+// of those with keys, eight at once: a granule's keys are one 16-byte load per
+// lane.
 __global__ __launch_bounds__(kScStatThreads) void k_sc_hist(ScopeArgs a) {
   extern __shared__ __align__(16) uint8_t sc_smem[];
   uint32_t* s_h = reinterpret_cast<uint32_t*>(sc_smem);
@@ -955,9 +967,28 @@ __global__ __launch_bounds__(kScStatThreads) void k_sc_hist(ScopeArgs a) {
   __syncthreads();
   const uint64_t granules = (sb_count(a.s) + kSoGranule - 1) / kSoGranule;
   const uint32_t lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const uint64_t step = (uint64_t)a.hranges * (kScStatThreads / 64) * 64;
-  for (uint64_t g0 = ((uint64_t)w * a.hranges + range) * 64; g0 < granules; g0 += step) {
-    const uint32_t cnt = g0 + lane < granules ? a.gcnt[g0 + lane] : 0u;
+  // four of a granule's n keys, those from 4 lane on
+  auto add = [&](const uint4& v, uint32_t n) {
+    const uint32_t k[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+    for (uint32_t e = 0; e < 4; ++e) {
+      const uint32_t r = k[e] >> 16;
+      if (4 * lane + e >= n || r < r0 || r - r0 >= nr) continue;
+      atomicAdd(&s_h[(r - r0) * 130 + ((k[e] >> 8) & 0xFFu)], 1u);
+      atomicAdd(&s_h[(r - r0) * 130 + 65 + (k[e] & 0xFFu)], 1u);
+    }
+  };
+  const uint4* keys = reinterpret_cast<const uint4*>(a.hkey);
+  const uint64_t step = (uint64_t)a.hranges * (kScStatThreads / 64) * a.hper;
+  for (uint64_t g0 = ((uint64_t)w * a.hranges + range) * a.hper; g0 < granules; g0 += step) {
+    if (a.hper == 1) {
+      // its keys and how many there are, together (the buffer goes on past the
+      // last granule's keys; what lies there is not counted)
+      const uint4 v = keys[g0 * (kSoGranule / 4) + lane];
+      add(v, a.gcnt[g0]);
+      continue;
+    }
+    const uint32_t cnt = lane < a.hper && g0 + lane < granules ? a.gcnt[g0 + lane] : 0u;
     uint64_t left = __ballot(cnt != 0);
     while (left) {
       uint4 v[8];
@@ -970,20 +1001,11 @@ __global__ __launch_bounds__(kScStatThreads) void k_sc_hist(ScopeArgs a) {
           const uint32_t q = (uint32_t)__builtin_ctzll(left);
           left &= left - 1;
           kn[u] = (uint32_t)__builtin_amdgcn_readlane((int)cnt, (int)q);
-          if (4 * lane < kn[u]) v[u] = reinterpret_cast<const uint4*>(a.hkey + (g0 + q) * kSoGranule)[lane];
+          if (4 * lane < kn[u]) v[u] = keys[(g0 + q) * (kSoGranule / 4) + lane];
         }
       }
 #pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        const uint32_t k[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
-#pragma unroll
-        for (uint32_t e = 0; e < 4; ++e) {
-          const uint32_t r = k[e] >> 16;
-          if (4 * lane + e >= kn[u] || r < r0 || r - r0 >= nr) continue;
-          atomicAdd(&s_h[(r - r0) * 130 + ((k[e] >> 8) & 0xFFu)], 1u);
-          atomicAdd(&s_h[(r - r0) * 130 + 65 + (k[e] & 0xFFu)], 1u);
-        }
-      }
+      for (int u = 0; u < 8; ++u) add(v[u], kn[u]);
     }
   }
   __syncthreads();
@@ -2143,13 +2165,13 @@ extern "C" int argus_attr_scope(const argus_scope_config* cfg, const argus_scope
     // four chunks at a time per block (a wave each), each wave with its row
     // of R counters
     const size_t so_lds = (size_t)4 * a.R * sizeof(uint32_t);
-    (void)hipFuncSetAttribute((const void*)k_so_local, hipFuncAttributeMaxDynamicSharedMemorySize,
-                              (int)so_lds);
-    hipLaunchKernelGGL(k_so_local,
-                       dim3((uint32_t)std::min<uint64_t>((chunks + 3) / 4,
-                                                         persistent_blocks((const void*)k_so_local,
-                                                                           kScThreads))),
-                       dim3(kScThreads), so_lds, st, a);
+    const bool mark = io->max_instances > kSoMarkMin;
+    const void* local = mark ? (const void*)k_so_local<true> : (const void*)k_so_local<false>;
+    (void)hipFuncSetAttribute(local, hipFuncAttributeMaxDynamicSharedMemorySize, (int)so_lds);
+    void* largs[] = {&a};
+    if (hipLaunchKernel(local, dim3((uint32_t)std::min<uint64_t>((chunks + 3) / 4, persistent_blocks(local, kScThreads))),
+                        dim3(kScThreads), largs, so_lds, st) != hipSuccess)
+      return ARGUS_E_HIP;
     const uint64_t cells = segs * a.R;
     hipLaunchKernelGGL(k_so_seg, dim3((uint32_t)((cells + kScThreads - 1) / kScThreads)),
                        dim3(kScThreads), 0, st, a);
@@ -2176,9 +2198,12 @@ extern "C" int argus_attr_scope(const argus_scope_config* cfg, const argus_scope
     const size_t lds = rows ? (size_t)a.R * kScCols * sizeof(uint64_t) : 0;
     const void* kern = rows ? (const void*)k_sc_stats<true> : (const void*)k_sc_stats<false>;
     if (rows) (void)hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    // the blocks that fit at once: each flushes its rows once
+    // the blocks that fit at once, a granule per wave: each flushes its rows
+    // once.  While granules are few, fewer per block, so that their adds do not
+    // queue in one compute unit (4096 instances, 3000 regions: one block 31 us,
+    // one per granule 9.5); with rows, which each block flushes, up to four.
     const uint64_t fit = persistent_blocks(kern, kScStatThreads, lds);
-    const uint32_t blocks = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(fit, (waves + 15) / 16));
+    const uint32_t blocks = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(fit, !rows ? waves : std::max<uint64_t>((waves + 15) / 16, std::min<uint64_t>(4, (waves + 3) / 4))));
     if (rows) hipLaunchKernelGGL(k_sc_stats<true>, dim3(blocks), dim3(kScStatThreads), lds, st, a);
     else hipLaunchKernelGGL(k_sc_stats<false>, dim3(blocks), dim3(kScStatThreads), 0, st, a);
     // as few slices of regions as fit, of equal size
@@ -2192,6 +2217,7 @@ extern "C" int argus_attr_scope(const argus_scope_config* cfg, const argus_scope
     // where few granules have keys)
     const uint64_t hfit = ceil_div(persistent_blocks((const void*)k_sc_hist, kScStatThreads, hb), 8ull * slices) * 8;
     a.hranges = (uint32_t)std::min<uint64_t>(hfit, ceil_div(ceil_div(waves, 16 * 64), 8) * 8);
+    a.hper = (uint32_t)std::min<uint64_t>(64, ceil_div(waves, (uint64_t)a.hranges * (kScStatThreads / 64)));
     hipLaunchKernelGGL(k_sc_hist, dim3(a.hranges * slices), dim3(kScStatThreads), hb, st, a);
   } else {
     hipLaunchKernelGGL(k_sc_stats_sorted, dim3(sc_grid(io->max_instances, kScStatThreads, 1024)),

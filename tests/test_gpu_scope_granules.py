@@ -9,7 +9,7 @@ from __future__ import annotations
 import numpy as np
 import pytest
 
-from gpu_util import log
+from gpu_util import gpu_run, log
 from test_gpu_scope import assert_scope_parity, run_both
 
 pytestmark = pytest.mark.gpu
@@ -51,3 +51,58 @@ def test_windows(oracle_mod, R):
     log(f"[gpu] scope granules R={R}")
     for i, (g, w, nb) in enumerate(run_both(oracle_mod, rec, R, scopes, masks)):
         assert_scope_parity(g, w, nb, f"R={R} scope {scopes[i]}")
+
+
+@pytest.mark.parametrize("cap", [1 << 21, (1 << 21) + 1])
+@pytest.mark.parametrize("R", [3, 1024, 1025, 4096])
+def test_windows_of_a_large_buffer(oracle_mod, R, cap):
+    """Granules are marked only where the buffer holds more than 2^21 instances (whatever their number)."""
+    import torch
+
+    from paper_2609_12299_amd import scope_statistics
+    rec = _trace(R, R)
+    g = gpu_run(rec, dict(num_regions=R))
+    o = oracle_mod.run(rec, R, 0, None, 0, 0)
+    nb = len(g["instances"])
+    inst = torch.zeros((cap, 32), dtype=torch.uint8, device="cuda")
+    inst[:nb] = torch.from_numpy(g["instances"].view(np.uint8).reshape(nb, 32)).to("cuda")
+    excl = torch.zeros(cap, dtype=torch.int64, device="cuda")
+    excl[:nb] = torch.from_numpy(g["instance_excl"].view(np.int64)).to("cuda")
+    count = torch.tensor([nb], dtype=torch.int64, device="cuda")
+    log(f"[gpu] scope granules R={R} in a buffer of {cap}")
+    for lo, hi in WINDOWS:
+        sc = dict(iter_lo=lo, iter_hi=hi, role_mask=7, role_lo=0, role_hi=3)
+        got = scope_statistics(inst, excl, count, R, **sc)
+        torch.cuda.synchronize()
+        got = {k: v.cpu().numpy() for k, v in got.items() if not k.startswith("_")}
+        assert_scope_parity(got, oracle_mod.scope(o["instances"], o["instance_excl"], R, **sc), nb, f"R={R} {sc}")
+
+
+@pytest.mark.parametrize("R", [1024, 1025])
+@pytest.mark.parametrize("n", [256, 257, 1024, 4096, 4097, 32768, 33024, 300000])
+def test_few_granules(oracle_mod, n, R):
+    """Blocks and granules per wave follow the number of granules: one, a few, one per wave, more."""
+    rng = np.random.default_rng(n)
+    r = np.zeros((n, 2), DTYPE)
+    r["ts"] = np.arange(2 * n).reshape(n, 2) * 3
+    r["ctx"] = (np.arange(n) // 700)[:, None]
+    r["region"] = rng.integers(0, R, n)[:, None]
+    r["kind"] = [1, 2]
+    rec = r.reshape(-1).view(np.uint8).reshape(2 * n, 16)
+    scopes = [dict(), dict(iter_lo=0, iter_hi=0), dict(group_shift=1, group_lo=1, group_hi=2)]
+    log(f"[gpu] scope of {n} instances, R={R}")
+    # (a buffer of n instances: half of the records')
+    import torch
+
+    from paper_2609_12299_amd import scope_statistics
+    g = gpu_run(rec, dict(num_regions=R))
+    o = oracle_mod.run(rec, R, 0, None, 0, 0)
+    assert len(g["instances"]) == n
+    inst = torch.from_numpy(g["instances"].view(np.uint8).reshape(n, 32)).to("cuda")
+    excl = torch.from_numpy(g["instance_excl"].view(np.int64)).to("cuda")
+    count = torch.tensor([n], dtype=torch.int64, device="cuda")
+    for sc in scopes:
+        got = scope_statistics(inst, excl, count, R, **sc)
+        torch.cuda.synchronize()
+        got = {k: v.cpu().numpy() for k, v in got.items() if not k.startswith("_")}
+        assert_scope_parity(got, oracle_mod.scope(o["instances"], o["instance_excl"], R, **sc), n, f"R={R} {sc}")
