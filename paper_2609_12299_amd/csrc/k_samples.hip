@@ -56,8 +56,12 @@ struct SampArgs {
 constexpr int kSampThreads = 256;
 // The join's blocks: 16 waves, so that few blocks add to the counters (adds
 // to one line of memory take 5 ns each, one after another: six counters from
-// each of 4096 blocks of 4 waves were 0.1 ms).
+// each of 4096 blocks of 4 waves were 0.1 ms).  Up to kJoinSmall samples, 4
+// waves: the searches are spread over more compute units, and at most 512
+// blocks add (2^18 instances, 177 regions, whole calls with 16 and 4 waves:
+// 1000 samples 50 and 37 us, 10^5 58 and 54, 2 10^5 59 and 63, 10^6 95 and 119).
 constexpr int kJoinThreads = 1024;
+constexpr uint64_t kJoinSmall = 1ull << 17;
 constexpr int kPcRegs = 4;  // rows of up to 256 regions held in registers (k_s_pc)
 constexpr uint32_t kTotalRegions = 64 * kPcRegs;  // up to here k_s_pc also takes the regions' totals
 
@@ -73,12 +77,13 @@ __global__ __launch_bounds__(kSampThreads) void k_s_clear(SampArgs a) {
     for (uint64_t i = (uint64_t)blockIdx.x * kSampThreads + threadIdx.x; i < a.R; i += stride) a.region_total[i] = 0;
 }
 
-__global__ __launch_bounds__(kJoinThreads) void k_s_join(SampArgs a) {
+template <int NT>
+__global__ __launch_bounds__(NT) void k_s_join(SampArgs a) {
   const uint64_t avail = *a.n_inst;
   const uint64_t ni = avail < a.max_inst ? avail : a.max_inst;
   const uint4* inst = reinterpret_cast<const uint4*>(a.inst);  // two uint4 per instance
   uint64_t bad = 0, wt = 0, watt = 0, wun = 0, winner = 0, wbadi = 0;
-  const uint64_t stride = (uint64_t)gridDim.x * kJoinThreads;
+  const uint64_t stride = (uint64_t)gridDim.x * NT;
   // blocks go to the 8 XCDs round-robin: give each XCD a contiguous eighth
   // of the block indices (when the grid divides by 8), so that neighbouring
   // samples, whose searches end in the same lines, share one L2
@@ -129,7 +134,7 @@ __global__ __launch_bounds__(kJoinThreads) void k_s_join(SampArgs a) {
   // twice the requests in flight.  The search finds the first instance whose
   // (context, begin time) exceeds the sample's; the key is compared with
   // bitwise operators, so that a level's two loads go out together.
-  for (uint64_t i = (uint64_t)bid * kJoinThreads + threadIdx.x; i < a.ns; i += 2 * stride) {
+  for (uint64_t i = (uint64_t)bid * NT + threadIdx.x; i < a.ns; i += 2 * stride) {
     const uint64_t i1 = i + stride;
     const bool has1 = i1 < a.ns;
     const uint4 s0 = a.smp[i], s1 = a.smp[has1 ? i1 : i];
@@ -169,7 +174,7 @@ __global__ __launch_bounds__(kJoinThreads) void k_s_join(SampArgs a) {
     if (ok1) finish(lo1, ts1, ctx1, pc1, w1);
   }
   // the block's sums, added by six lanes of one wave in one request
-  constexpr int kWaves = kJoinThreads / 64;
+  constexpr int kWaves = NT / 64;
   __shared__ uint64_t s_part[6][kWaves];
   const uint64_t v[6] = {bad, wt, watt, wun, winner, wbadi};
 #pragma unroll
@@ -477,10 +482,15 @@ extern "C" int argus_attr_samples(const argus_samples_config* cfg, const argus_s
   hipStream_t s = (hipStream_t)stream_v;
   hipLaunchKernelGGL(k_s_clear, dim3(grid_for(P * R, kSampThreads, 4096)), dim3(kSampThreads), 0,
                      s, a);
-  // (the blocks that fit at once, two per compute unit)
-  hipLaunchKernelGGL(k_s_join, dim3(grid_for(a.ns, kJoinThreads, 512)), dim3(kJoinThreads), 0, s, a);
-  // few enough blocks that their adds to the totals do not queue
-  hipLaunchKernelGGL(k_s_pc, dim3(grid_for(P, kSampThreads / 64, 2048)), dim3(kSampThreads), 0, s, a);
+  if (a.ns <= kJoinSmall)
+    hipLaunchKernelGGL(k_s_join<kSampThreads>, dim3(grid_for(a.ns, kSampThreads, 4096)), dim3(kSampThreads), 0, s, a);
+  else  // (the blocks that fit at once, two per compute unit)
+    hipLaunchKernelGGL(k_s_join<kJoinThreads>, dim3(grid_for(a.ns, kJoinThreads, 512)), dim3(kJoinThreads), 0, s, a);
+  // Where the blocks add to the regions' totals, few enough that the adds do
+  // not queue; else twice as many (65536 PCs of 257 regions, 1000 samples: 282 us
+  // against 322 for the call).
+  const uint32_t pc_blocks = R <= kTotalRegions ? 2048u : 4096u;
+  hipLaunchKernelGGL(k_s_pc, dim3(grid_for(P, kSampThreads / 64, pc_blocks)), dim3(kSampThreads), 0, s, a);
   const uint32_t lift_y = M > 0 ? (uint32_t)((M + kLiftMetrics - 1) / kLiftMetrics) : 1u;
   if (M > 0 || R > kTotalRegions) hipLaunchKernelGGL(k_s_region, dim3(8 * (uint32_t)((R + 7) / 8), lift_y), dim3(kLiftStrands), 0, s,
                      a);
