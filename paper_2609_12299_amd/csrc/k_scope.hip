@@ -1536,7 +1536,14 @@ __global__ __launch_bounds__(kScThreads) void k_pr_groups(ProbeArgs a) {
 
 constexpr uint32_t kHoMaxCompact = 4096;  // compaction blocks
 constexpr uint32_t kHoThreads = 1024;
-constexpr uint32_t kHoTile = kHoThreads * kScRounds;  // instances per compaction tile
+// Instances per compaction tile of NT threads, and up to which capacity of the
+// instance buffer the compaction has 256 threads: tiles of 1024 threads are
+// faster (33 M instances 0.31 -> 0.27 ms), but while they are fewer than 96,
+// many compute units have none (whole calls, decode, level 1, buffers half
+// full, with tiles of 4096 and of 16384: capacity 2^16 34 and 41 us, 2^20 53 and
+// 58, 2^21 67 and 65, 2^22 92 and 81).
+constexpr uint32_t ho_tile(uint32_t nt) { return nt * kScRounds; }
+constexpr uint64_t kHoSmall = 3ull << 19;
 
 struct HandoffArgs {
   const argus_instance* inst;
@@ -1573,7 +1580,7 @@ __global__ __launch_bounds__(kScThreads) void k_ho_init(HandoffArgs a) {
     for (uint64_t i = first; i < a.max_inst; i += stride) a.parent_gap[i] = 0;
   if (first < 65) a.hist[first] = 0;
   if (first < ARGUS_HO_NUM_COUNTERS) a.counters[first] = 0;
-  const uint64_t tiles = (a.max_inst + kHoTile - 1) / kHoTile;
+  const uint64_t tiles = ceil_div(a.max_inst, ho_tile(kScThreads));  // (of either size at most)
   for (uint64_t i = first; i < tiles; i += stride) a.status[i] = 0;
   if (first == 0) {
     *a.tctr = 0;
@@ -1582,15 +1589,17 @@ __global__ __launch_bounds__(kScThreads) void k_ho_init(HandoffArgs a) {
 }
 
 // The instances of level <= L compacted in canonical order, in one pass:
-// blocks take tiles of 16384 instances in order (a counter; a block takes its
+// blocks take tiles of 4096 or 16384 instances in order (a counter; a block takes its
 // next tile once this one's loads are on their way, so that the counter's
 // round trip is hidden: nothing waits for a tile that comes after one still
 // in work), count the tile's qualifying instances (a ballot per round of 64,
 // the waves' counts through LDS), publish the count, find the count before
 // the tile by decoupled look-back, 64 tiles a step, and write the indices.
 // The tile holding the last instance records the total.
-__global__ __launch_bounds__(kHoThreads) void k_ho_compact(HandoffArgs a) {
-  __shared__ uint32_t s_tile, s_w[kHoThreads / 64];
+template <int NT>
+__global__ __launch_bounds__(NT) void k_ho_compact(HandoffArgs a) {
+  constexpr uint32_t kHoTile = ho_tile(NT);
+  __shared__ uint32_t s_tile, s_w[NT / 64];
   __shared__ uint64_t s_base;
   const uint64_t n = ho_count(a);
   const uint64_t T = (n + kHoTile - 1) / kHoTile;
@@ -1630,7 +1639,7 @@ __global__ __launch_bounds__(kHoThreads) void k_ho_compact(HandoffArgs a) {
     __syncthreads();
     uint32_t wpre = 0, cnt = 0;
 #pragma unroll
-    for (int q = 0; q < kHoThreads / 64; ++q) {
+    for (int q = 0; q < NT / 64; ++q) {
       wpre += q < (int)w ? s_w[q] : 0u;
       cnt += s_w[q];
     }
@@ -1684,7 +1693,7 @@ __global__ __launch_bounds__(kHoThreads) void k_ho_compact(HandoffArgs a) {
   __syncthreads();
   if (tid == 0) {
     uint32_t t = 0;
-    for (uint32_t q = 0; q < kHoThreads / 64; ++q) t += s_w[q];
+    for (uint32_t q = 0; q < NT / 64; ++q) t += s_w[q];
     a.atl[blockIdx.x] = t;
   }
 }
@@ -2377,10 +2386,13 @@ extern "C" int argus_attr_handoffs(const argus_handoffs_config* cfg, const argus
   if (io->max_instances > 0) {
     const uint32_t g = sc_grid(io->max_instances, kScThreads, 4096);
     // resident blocks only: they take the tiles in order
+    const bool small = io->max_instances <= kHoSmall;
+    const void* compact = small ? (const void*)k_ho_compact<kScThreads> : (const void*)k_ho_compact<kHoThreads>;
+    const uint32_t nt = small ? (uint32_t)kScThreads : kHoThreads;
     a.cblocks = (uint32_t)std::min<uint64_t>(
-        std::min<uint64_t>(ceil_div(io->max_instances, kHoTile), persistent_blocks((const void*)k_ho_compact, kHoThreads)),
-        kHoMaxCompact);
-    hipLaunchKernelGGL(k_ho_compact, dim3(a.cblocks), dim3(kHoThreads), 0, st, a);
+        std::min<uint64_t>(ceil_div(io->max_instances, ho_tile(nt)), persistent_blocks(compact, (int)nt)), kHoMaxCompact);
+    void* cargs[] = {&a};
+    if (hipLaunchKernel(compact, dim3(a.cblocks), dim3(nt), cargs, 0, st) != hipSuccess) return ARGUS_E_HIP;
     // resident blocks only (one per compute unit): each stores its table once
     a.dumps = (uint32_t)std::min<uint64_t>(
         std::min<uint64_t>(g, persistent_blocks((const void*)k_ho_pairs, kHoThreads)), kHoMaxDumps);

@@ -73,3 +73,36 @@ def test_decode_megakernel_steps(oracle_mod, tracegen_mod):
                             cls=d["region_class"], shift=d["group_shift"], G=d["num_groups"]):
         assert int(o["counters"][1]) > 0
         assert_parity(g, o, f"config 3 L={L}")
+
+
+@pytest.mark.parametrize("cap", [1, 4096, 4097, 16384, 16385, 3 << 19, (3 << 19) + 1])
+def test_compaction_tiles(oracle_mod, cap):
+    """The compaction's tiles hold 4096 instances in buffers of up to 3 2^19, beyond 16384: edges of both,
+    with the buffer full and with one that holds fewer."""
+    import torch
+
+    from paper_2609_12299_amd import INSTANCE_DTYPE, phase_handoffs
+    rng = np.random.default_rng(cap)
+    R = 9
+    # steps (level 0) of four phases (level 1) each, some phases with a child (level 2), one left open
+    x = np.zeros(cap, INSTANCE_DTYPE)
+    at = np.arange(cap)
+    k = at % 7
+    x["level"] = np.array([0, 1, 1, 2, 1, 2, 1])[k]
+    x["parent"] = np.where(k == 0, 0xFFFFFFFF, np.where(x["level"] == 1, at - k, at - 1)).astype(np.uint32)
+    x["ctx_key"] = at // 700
+    x["region_id"] = rng.integers(0, R, cap)
+    x["end_region_id"] = x["region_id"]
+    x["t_begin"] = 10 * at
+    x["t_end"] = 10 * at + rng.integers(1, 9, cap)
+    x["end_region_id"][cap // 2] = 0xFFFF
+    x["t_end"][cap // 2] = 0xFFFFFFFFFFFFFFFF
+    inst = torch.from_numpy(x.view(np.uint8).reshape(cap, 32)).to("cuda")
+    log(f"[gpu] handoffs of a buffer of {cap}")
+    for n in sorted({cap, max(1, cap - 5000)}):
+        count = torch.tensor([n], dtype=torch.int64, device="cuda")
+        for L in (0, 1, 2):
+            g = phase_handoffs(inst, count, R, level=L)
+            torch.cuda.synchronize()
+            g = {k: v.cpu().numpy() for k, v in g.items() if not k.startswith("_")}
+            assert_parity(g, oracle_mod.handoffs(x[:n], R, L), f"cap={cap} n={n} L={L}")
