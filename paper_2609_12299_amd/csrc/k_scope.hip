@@ -306,12 +306,12 @@ constexpr uint32_t kSoMaskShift = 16;         // bits 16..31: the chunk's granul
 constexpr uint32_t kSoGranule = kScTile / 16; // 256 instances
 static_assert(kSoMaxRegions <= 4096 && kScTile <= 4096, "12 bits each in a pending ordinal");
 constexpr uint32_t kSoSeg = 256;   // chunks per segment of the carry scan
-// Up to this many instances the granules are not marked and all are read:
-// marking costs the ordinal pass, whose waves walk a chunk in 64 dependent
-// rounds, 6 us (12 with a region set), and what it saves is less (iterations
-// 0..15, 1024 regions: 2^20 instances 251 us unmarked, 256 marked; 2^22: 298
-// each; 2^23: 362, 354).
-constexpr uint64_t kSoMarkMin = 1ull << 21;
+// Up to this capacity of the instance buffer the granules are not marked and
+// all are read: marking costs the ordinal pass, whose waves walk a chunk in 64
+// dependent rounds, 6 us (12 with a region set), and what it saves is less
+// (iterations 0..15, 1024 regions, buffers half full: capacity 2^21 251 us
+// unmarked, 256 marked; 2^22 278, 282; 2^23 298 each; 2^24 362, 354).
+constexpr uint64_t kSoMarkMin = 1ull << 22;
 
 struct ScopeArgs {
   const argus_instance* inst;

@@ -53,10 +53,10 @@ def test_windows(oracle_mod, R):
         assert_scope_parity(g, w, nb, f"R={R} scope {scopes[i]}")
 
 
-@pytest.mark.parametrize("cap", [1 << 21, (1 << 21) + 1])
+@pytest.mark.parametrize("cap", [1 << 22, (1 << 22) + 1])
 @pytest.mark.parametrize("R", [3, 1024, 1025, 4096])
 def test_windows_of_a_large_buffer(oracle_mod, R, cap):
-    """Granules are marked only where the buffer holds more than 2^21 instances (whatever their number)."""
+    """Granules are marked only where the buffer has room for more than 2^22 instances (whatever their number)."""
     import torch
 
     from paper_2609_12299_amd import scope_statistics
