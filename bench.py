@@ -70,6 +70,8 @@ def byte_model(name: str, c: dict, plan: dict, R: int, K: int, G: int, flags: in
         return b
 
     elem = 12.0 + (4.0 if wide else 0.0)
+    if plan["early"] and name in ("ctx_sort", "runs_scatter", "tile_sums"):
+        return 0.0  # they return at once: the full sort starts from the input
     if name == "ctx_sort":
         # context passes over the records, or over runs: run counts and lists in, run keys, ids
         # and lengths out, the passes, then ids, keys and lengths in and positions out

@@ -45,7 +45,7 @@ PLAN_BYTES = 1728
 PLAN_FIELDS = {
     "n_records": (0, "<u8"), "n_valid": (8, "<u8"), "n_begin": (16, "<u8"),
     "rec_ts_bits": (48, "<u4"), "rec_ctx_bits": (52, "<u4"), "rec_wide": (56, "<u4"),
-    "unsorted": (104, "<u4"), "n_ev": (128, "<u8"), "rec_slots": (144, "slots"),
+    "unsorted": (104, "<u4"), "early": (124, "<u4"), "n_ev": (128, "<u8"), "rec_slots": (144, "slots"),
     "ev_slots": (784, "slots"), "ev_merge": (1432, "<u4"), "merge_rounds": (1440, "<u4"),
     "merge_end": (1448, "<u8"), "runs": (1712, "<u4"), "n_runs": (1720, "<u8"),
 }

@@ -159,6 +159,7 @@ static_assert(offsetof(DevPlan, rec.ts_bits) == 48, "DevPlan layout");
 static_assert(offsetof(DevPlan, rec.ctx_bits) == 52, "DevPlan layout");
 static_assert(offsetof(DevPlan, rec.wide) == 56, "DevPlan layout");
 static_assert(offsetof(DevPlan, unsorted) == 104, "DevPlan layout");
+static_assert(offsetof(DevPlan, early) == 124, "DevPlan layout");
 static_assert(offsetof(DevPlan, n_ev) == 128, "DevPlan layout");
 static_assert(offsetof(DevPlan, rs) == 144, "DevPlan layout");
 static_assert(offsetof(DevPlan, es) == 784, "DevPlan layout");
