@@ -58,7 +58,7 @@ struct Layout {
   size_t inst, excl, hist_key, agg_part, ov_mask, ov_q;
   size_t push_pos, pop_pos, ctx_list, seg_run, seg_tile0, seg_samp0, part;
   size_t total;
-  uint64_t lb_words, tree_leaves, match_tiles, pool_cap, ctx_cap, tiles_cap, chunks, run_cap, scan_words;
+  uint64_t tree_leaves, match_tiles, ctx_cap, tiles_cap, chunks, run_cap, scan_words;
 };
 
 Layout make_layout(const argus_attr_config& c, uint64_t n, bool own_instances) {
@@ -81,8 +81,7 @@ Layout make_layout(const argus_attr_config& c, uint64_t n, bool own_instances) {
     L.ctxw[b] = take(sizeof(uint32_t) * nn);
   }
   // The first event pass reads 2 * n_begin <= 2 * n slots.
-  L.lb_words = ceil_div(2 * nn, kSortTile) * kRadixBins;
-  L.lb = take(sizeof(uint64_t) * L.lb_words);
+  L.lb = take(sizeof(uint64_t) * ceil_div(2 * nn, kSortTile) * kRadixBins);
   L.match_tiles = ceil_div(nn, kMatchTile);
   L.tsum = take(sizeof(uint64_t) * L.match_tiles);
   L.carry = take(sizeof(TileCarry) * L.match_tiles);
@@ -103,12 +102,12 @@ Layout make_layout(const argus_attr_config& c, uint64_t n, bool own_instances) {
   while (leaves < L.match_tiles) leaves <<= 1;
   L.tree_leaves = leaves;
   L.tree = take(sizeof(int64_t) * 2 * leaves);
-  L.pool_cap = L.match_tiles * (uint64_t)kMatchTile;
-  L.pop_ts = take(sizeof(uint64_t) * L.pool_cap);
-  L.pop_reg = take(sizeof(uint32_t) * L.pool_cap);
-  L.pushes = take(sizeof(uint32_t) * L.pool_cap);
-  L.op_parent = take(sizeof(uint32_t) * L.pool_cap);
-  L.op_sum = take(sizeof(uint64_t) * L.pool_cap);
+  const uint64_t pool_cap = L.match_tiles * (uint64_t)kMatchTile;
+  L.pop_ts = take(sizeof(uint64_t) * pool_cap);
+  L.pop_reg = take(sizeof(uint32_t) * pool_cap);
+  L.pushes = take(sizeof(uint32_t) * pool_cap);
+  L.op_parent = take(sizeof(uint32_t) * pool_cap);
+  L.op_sum = take(sizeof(uint64_t) * pool_cap);
   L.inst = own_instances ? take(sizeof(argus_instance) * nn) : 0;
   L.excl = take(sizeof(uint64_t) * nn);
   L.hist_key = take(sizeof(uint32_t) * nn);
@@ -122,8 +121,8 @@ Layout make_layout(const argus_attr_config& c, uint64_t n, bool own_instances) {
   // a segment of L events takes at most ceil(L / 4096) tiles in a two-way
   // pass and (L / 127 + 4) / 28 + 1 in a four-way one
   L.tiles_cap = ev ? ceil_div(nn, kSampStride * kSampPerTile) + L.ctx_cap + ceil_div(L.ctx_cap, 2) : 0;
-  L.push_pos = take(ev ? sizeof(uint32_t) * L.pool_cap : 0);
-  L.pop_pos = take(ev ? sizeof(uint32_t) * L.pool_cap : 0);
+  L.push_pos = take(ev ? sizeof(uint32_t) * pool_cap : 0);
+  L.pop_pos = take(ev ? sizeof(uint32_t) * pool_cap : 0);
   L.ctx_list = take(sizeof(uint2) * L.ctx_cap);
   // segment arrays of every merge pass, ctx_cap + 1 entries per pass
   const uint64_t segs = ev ? kMaxMergePasses * (L.ctx_cap + 1) : 0;
@@ -339,10 +338,8 @@ int enqueue_run(argus_attr* h, const argus_record* d_records, uint64_t n, char* 
   w.part = (uint32_t*)(base + L.part);
   w.ctx_cap = L.ctx_cap;
   w.tiles_cap = L.tiles_cap;
-  w.lb_words = L.lb_words;
   w.tree_leaves = L.tree_leaves;
   w.match_tiles = L.match_tiles;
-  w.pool_cap = L.pool_cap;
 
   // Timing events (one per launch, recorded on the run's stream).
   argus_attr::TimedRun* tr = nullptr;

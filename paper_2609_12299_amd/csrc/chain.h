@@ -102,7 +102,8 @@ ARGUS_DEV bool last_arrival(uint32_t* ctrs, uint32_t which, uint32_t total, uint
 // one wave: the tile's word is published with its own total, then the
 // wave reads 64 predecessors per round trip, nearest first, until one holds
 // its inclusive prefix.  Totals stay below 2^32.  The words start at zero.
-ARGUS_DEV uint64_t scan_lookback(uint64_t* words, uint32_t tile, uint32_t tot, uint64_t* counters) {
+// A wait that gives up sets `code` in *error.
+ARGUS_DEV uint64_t scan_lookback(uint64_t* words, uint32_t tile, uint32_t tot, uint64_t* error, uint64_t code) {
   const uint32_t lane = lane_id();
   if (tile == 0) {
     if (lane == 0) st_agent(&words[0], kFlagIncl | tot);
@@ -126,7 +127,7 @@ ARGUS_DEV uint64_t scan_lookback(uint64_t* words, uint32_t tile, uint32_t tot, u
     top -= jn;
     if (jn == 0) {
       if (++spins > kMaxSpins) {
-        if (lane == 0) flag_internal_error(counters, 2048);
+        if (lane == 0) atomicOr((unsigned long long*)error, (unsigned long long)code);
         break;
       }
       backoff();

@@ -14,6 +14,9 @@
 namespace argus {
 
 // ------------------------------------------------------------------ sizes
+// 512 threads of 8 elements, not 256 of 16: with the LDS for two blocks per
+// compute unit, twice the waves (four passes over 2^12 elements 38 us against
+// 47, 2^20 84 and 91, 2^24 720 and 743, 2^26 2793 and 2857).
 constexpr int kSortThreads = 512;
 constexpr int kSortItems = 8;
 constexpr int kSortWaves = kSortThreads / 64;
@@ -77,9 +80,6 @@ constexpr uint32_t kParentPending = 0x80000000u;  // | tile: parent lies in an e
 constexpr uint16_t kNoEnd = 0xFFFF;
 constexpr uint64_t kU64Max = ~0ull;
 
-// Source of the elements read by a sort pass.
-enum SrcKind : uint32_t { kSrcPacked = 0, kSrcRecords = 1, kSrcInstances = 2 };
-
 // How packed sort keys are laid out.  key = (ctx_rel << ts_bits) | ts_off
 // when ctx_bits + ts_bits <= 64, else ("wide") key = ts_off and ctx_rel lives
 // in a separate 32-bit array.  ts_off = ts - ts_min, ctx_rel = ctx - ctx_min.
@@ -98,7 +98,7 @@ struct SlotPlan {
   uint32_t pos;    // digit position: 0..3 context digit, 4..11 timestamp digit
   uint32_t src;    // buffer index 0/1, or 2 = raw source
   uint32_t dst;    // buffer index 0/1
-  uint32_t lb;     // look-back status array used (0/1)
+  uint32_t lb;     // unused (keeps the layout)
   uint32_t n_out;  // valid elements written (destination bound)
   uint64_t n_elems;  // elements read (raw sources include the invalid ones)
   uint64_t tiles;
@@ -125,7 +125,7 @@ struct DevPlan {
   uint32_t force_full;   // ARGUS_FORCE_FULL_SORT
   uint32_t rec_final;    // buffer holding the sorted records
   uint32_t ev_final;     // buffer holding the sorted events
-  uint32_t rec_active;   // active record passes so far (look-back parity)
+  uint32_t pad0;         // unused (keeps the layout)
   uint32_t early;        // the ingest saw a context out of time order (or the full sort is forced):
                          // no context sort, the full sort starts from the input
   uint64_t n_ev;         // valid overlap events
@@ -259,10 +259,8 @@ struct Work {
   uint32_t* part;       // [tiles_cap] merge tasks, 48 B each (k_merge.hip)
   uint64_t ctx_cap;
   uint64_t tiles_cap;
-  uint64_t lb_words;    // capacity of lb in words
   uint64_t tree_leaves; // power of two >= max match tiles
   uint64_t match_tiles; // upper bound (from n_records)
-  uint64_t pool_cap;
 };
 
 // Run parameters shared by all launches.
@@ -305,7 +303,10 @@ constexpr uint32_t kCtrWords = kPhaseBase + kPhCount * kPhaseWords + kArCount * 
 
 // Up to this many records k_init clears the look-back words of the record
 // sorts (half a byte per record); beyond it they are cleared by the sort that
-// needs them (2^28 records sorted as runs use 2 of 128 MiB: 20 us less).
+// needs them, so that what is not used is not cleared: 2^28 records sorted as
+// 2^20 runs use 0.5 of 128 MiB, 20 us less.  Cleared by the sort, 2^22
+// interleaved records took 295 us instead of 287 and 2^25 1479 instead of 1467;
+// sorted as runs, 2^25 took 925 us either way.
 constexpr uint64_t kInitClearMax = 1ull << 25;
 constexpr uint32_t kChunksPerTile = 1024;  // chunks per tile of k_ctx_sort's compaction
 
@@ -334,8 +335,10 @@ constexpr uint32_t kChunkCountBits = 9;
 constexpr uint32_t kRunPosMask = 0x7FFFFFFFu;
 // The ingest's grid for n records (four waves per block): a chunk per wave
 // up to 256 blocks, so that short traces do not wait for four chunks in a
-// row, then four chunks per wave (each block ends with up to 1024 atomics on
-// the same histogram), up to 1024 blocks.
+// row (statistics alone of 2^12 to 2^16 records 75 to 108 us, with four chunks
+// per wave 76 to 112; equal at 2^17; 2^18 109 and 105), then four chunks per
+// wave (each block ends with up to 1024 atomics on the same histogram), up to
+// 1024 blocks.
 __host__ __device__ inline uint32_t ingest_blocks(uint64_t n) {
   uint64_t blocks = (n + 256 * 4 - 1) / (256 * 4);
   if (blocks > 256) {
@@ -542,12 +545,6 @@ template <int CTRL, int ROWS = 0xF>
 ARGUS_DEV Fn dpp_fn(const Fn& f) {
   return Fn{dpp32<CTRL, ROWS>(f.reset), (int32_t)dpp32<CTRL, ROWS>((uint32_t)f.a),
             (int32_t)dpp32<CTRL, ROWS>((uint32_t)f.c)};
-}
-ARGUS_DEV Fn shfl_down_fn(const Fn& f, int o) {
-  return Fn{(uint32_t)__shfl_down((int)f.reset, o), __shfl_down(f.a, o), __shfl_down(f.c, o)};
-}
-ARGUS_DEV Fn shfl_fn(const Fn& f, int src) {
-  return Fn{(uint32_t)__shfl((int)f.reset, src), __shfl(f.a, src), __shfl(f.c, src)};
 }
 // Inclusive scan of the maps over the wave (lane order = record order).
 ARGUS_DEV Fn wave_scan_fn(Fn x) {

@@ -340,7 +340,9 @@ uint64_t agg_part_words(uint64_t n, uint32_t R) {
   uint32_t rl, hl;
   size_t bytes;
   agg_sizes(R, &rl, &hl, &bytes);
-  // few blocks add their rows directly: no second launch
+  // few blocks add their rows directly: no second launch (statistics alone of
+  // 2^12 to 2^16 records 9 us less with few regions, the same with 1024; up to
+  // 64 blocks the adds queue with many: 2^19 records, 1024 regions 155 -> 178 us)
   if (!rl || agg_grid(n) <= 8) return 0;
   const uint64_t words = agg_grid(n) * kAggFields * rl;
   return words * sizeof(uint64_t) <= kAggPartBytes ? words : 0;

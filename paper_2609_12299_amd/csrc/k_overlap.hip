@@ -470,7 +470,9 @@ __global__ __launch_bounds__(kSortThreads, KM <= 4 ? 4 : 1) void k_ev_sort(Sweep
       ++mine;
     }
     if (n_ev) atomicAdd(&s_nev, (unsigned long long)n_ev);
-    if (!mine) return;  // the blocks with a tile are as many as any later phase has tiles
+    // a block without a tile leaves: the passes have no more tiles than this
+    // phase (the sweep has up to two per tile: each block takes several)
+    if (!mine) return;
     __syncthreads();
     for (uint32_t i = tid; i < 12 * kRadixBins; i += kSortThreads)
       if (s_hist[i]) atomicAdd(&a.hist[i], s_hist[i]);

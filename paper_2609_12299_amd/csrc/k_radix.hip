@@ -62,7 +62,7 @@ __device__ __forceinline__ void runs_compact_tile(const CtxSortArgs& a, RadixSha
     pre += cnt[q];
   }
   if (w == 0) {
-    const uint32_t ex = (uint32_t)scan_lookback(a.scan0, tile, total, a.r.counters);
+    const uint32_t ex = (uint32_t)scan_lookback(a.scan0, tile, total, &a.r.counters[31], 2048);
     if (lane == 0) s.total = ex;
   }
   __syncthreads();
@@ -142,7 +142,7 @@ __device__ __forceinline__ void runs_pos_tile(const CtxSortArgs& a, RadixShared&
   uint32_t total;
   uint32_t pre = sort_excl_scan(sum, s.scr, &total);
   if (w == 0) {
-    const uint32_t ex = (uint32_t)scan_lookback(a.scan1, tile, total, a.r.counters);
+    const uint32_t ex = (uint32_t)scan_lookback(a.scan1, tile, total, &a.r.counters[31], 2048);
     if (lane == 0) s.total = ex;
   }
   __syncthreads();
@@ -219,7 +219,7 @@ __global__ __launch_bounds__(kSortThreads, 4) void k_ctx_sort(CtxSortArgs a) {
   const uint32_t* hist = runs ? a.run_hist : a.rec_hist;
   uint32_t act = digits_varying<4>(hist, 4);
   if (!runs && !act) act = 1;  // one pass packs the records
-  uint32_t src = runs ? 0u : 2u, ran = 0;
+  uint32_t src = runs ? 0u : 2u;
   for (uint32_t pos = 0; pos < 4; ++pos) {
     if (!((act >> pos) & 1u)) continue;
     RadixPass ps;
@@ -235,15 +235,12 @@ __global__ __launch_bounds__(kSortThreads, 4) void k_ctx_sort(CtxSortArgs a) {
     bool fin;
     const uint32_t mine = radix_phase<1>(a.r, s, ks, ps, kPhCtx + pos, last, &fin);
     src = ps.dst;
-    ++ran;
     if (fin && tid == 0) {
       note_slot(p->rs[pos], pos, ps);
       // the last pass only: the block of an earlier one's last tile may come
-      // here after a later pass has ended
-      if ((act >> (pos + 1)) == 0) {
-        p->rec_active = ran;
-        if (!runs) p->rec_final = ps.dst;  // over runs: the scatter writes buffer 0
-      }
+      // here after a later pass has ended (over runs: the scatter writes
+      // buffer 0)
+      if (!runs && (act >> (pos + 1)) == 0) p->rec_final = ps.dst;
     }
     if (!mine) return;
   }
@@ -301,7 +298,6 @@ __global__ __launch_bounds__(kSortThreads, 4) void k_full_sort(FullSortArgs a) {
   const uint64_t n_valid = p->n_valid, n_records = p->n_records;
   const uint32_t tid = threadIdx.x;
   const uint32_t src0 = p->early ? 2u : p->rec_final;
-  const uint32_t ran0 = p->early ? 0u : p->rec_active;
   const uint32_t key_bits = wide ? ks.ts_bits : ks.ts_bits + ks.ctx_bits;
   const uint32_t nd = (key_bits + 7) / 8;  // key digits (at most 8)
   {  // histograms of the key digits
@@ -349,7 +345,9 @@ __global__ __launch_bounds__(kSortThreads, 4) void k_full_sort(FullSortArgs a) {
       ++mine;
       if (t + 1 == tiles) break;
     }
-    if (!mine) return;  // the blocks with a tile are as many as any later phase has tiles
+    // a block without a tile leaves: the passes have no more tiles than this
+    // phase (the tile sums have up to two per tile: each block takes several)
+    if (!mine) return;
     __syncthreads();
     for (uint32_t i = tid; i < nd * kRadixBins; i += kSortThreads) {
       const uint32_t h = s_hist[i];
@@ -362,7 +360,7 @@ __global__ __launch_bounds__(kSortThreads, 4) void k_full_sort(FullSortArgs a) {
   uint32_t act = digits_varying<8>(a.hist, nd);
   if (wide) act |= digits_varying<4>(a.ctx_hist, 4) << 8;
   if (!act && src0 == 2) act = nd ? 1u : 1u << 8;  // one pass packs the records
-  uint32_t src = src0, ran = ran0;
+  uint32_t src = src0;
   for (uint32_t d = 0; d < 12; ++d) {
     if (!((act >> d) & 1u)) continue;
     RadixPass ps;
@@ -377,7 +375,6 @@ __global__ __launch_bounds__(kSortThreads, 4) void k_full_sort(FullSortArgs a) {
     bool fin;
     const uint32_t mine = radix_phase<1>(a.r, s, ks, ps, kPhFull + d, false, &fin);
     src = ps.dst;
-    ++ran;
     if (fin && tid == 0) note_slot(p->rs[kPhase2Slot + d], d < 8 ? 4 + d : d - 8, ps);
     if (!mine) return;
   }
@@ -396,10 +393,7 @@ __global__ __launch_bounds__(kSortThreads, 4) void k_full_sort(FullSortArgs a) {
   }
   if (!mine || phase_done(a.r.ctrs, kPhTsum, mine, a.t.nblk, &s.ticket) != a.t.nblk) return;
   mscan_top<kSortThreads>(a.t, ts, ceil_div(n_valid, kMatchTile));
-  if (tid == 0) {
-    p->rec_final = src;
-    p->rec_active = ran;
-  }
+  if (tid == 0) p->rec_final = src;
 }
 
 hipError_t launch_full_sort(const RunArgs& a, hipStream_t s) {

@@ -749,7 +749,7 @@ __global__ __launch_bounds__(kScThreads) void k_so_down(ScopeArgs a) {
 // granules that may hold instances in scope (and the carry scan the chunks
 // inside one context whose ordinals reach the iteration window); elsewhere
 // only the ordinals are completed, from the 4-byte words that hold what is
-// needed for it, and the 32-byte instances are not read: 0.88 -> 0.38 ms on 67 M
+// needed for it, and the 32-byte instances are not read: 0.68 -> 0.38 ms on 67 M
 // instances (iterations 0..15 of half the groups).
 constexpr uint32_t kScLdsRegions = 1024;  // 12 x 8 B x 1024 = 96 KiB of LDS
 constexpr int kScStatThreads = 1024;
@@ -1018,7 +1018,9 @@ __global__ __launch_bounds__(kScStatThreads) void k_sc_hist(ScopeArgs a) {
 }
 
 // More than kSoMaxRegions regions: the ordinals are final, and every
-// instance is read; one histogram key each.
+// instance is read; one histogram key each.  (With the next
+// instances loaded ahead and counters per wave the call took 530 us on 2^19
+// instances of 20000 regions, this way 340.)
 __global__ __launch_bounds__(kScStatThreads) void k_sc_stats_sorted(ScopeArgs a) {
   const uint64_t n = sb_count(a.s);
   const uint4* inst = reinterpret_cast<const uint4*>(a.inst);
@@ -1460,7 +1462,7 @@ __global__ __launch_bounds__(kScThreads) void k_pr_groups(ProbeArgs a) {
       total += s_w[q];
     }
     if (w == 0) {
-      const uint32_t ex = (uint32_t)scan_lookback(a.scan, tile, total, a.r.counters);
+      const uint32_t ex = (uint32_t)scan_lookback(a.scan, tile, total, &a.r.counters[31], 2048);
       if (lane == 0) s_ex = ex;
     }
     __syncthreads();
@@ -1644,33 +1646,8 @@ __global__ __launch_bounds__(NT) void k_ho_compact(HandoffArgs a) {
       cnt += s_w[q];
     }
     if (w == 0) {
-      // the tile of one wave: 64 predecessors per round trip, nearest first
-      uint64_t excl = 0;
-      if (lane == 0) st_agent(&a.status[tile], (tile == 0 ? kFlagIncl : kFlagAgg) | cnt);
-      int64_t top = (int64_t)tile - 1;
-      uint32_t spins = 0;
-      while (top >= 0) {
-        const int64_t q = top - (int64_t)lane;
-        const uint64_t v = q >= 0 ? ld_agent(&a.status[q]) : kFlagIncl;
-        const uint64_t f = v & ~kValMask;
-        const uint64_t mi = __ballot(f == kFlagIncl), mn = __ballot(f == 0);
-        const uint32_t ji = mi ? (uint32_t)__builtin_ctzll(mi) : 64u;  // nearest inclusive
-        const uint32_t jn = mn ? (uint32_t)__builtin_ctzll(mn) : 64u;  // nearest not published
-        const bool found = ji < jn;
-        const uint32_t use = found ? ji + 1 : jn;  // lanes [0, use) are summed
-        excl += rows_sum64(row_sum64(lane < use ? (v & kValMask) : 0ull));
-        if (found) break;
-        top -= jn;
-        if (jn == 0) {
-          if (++spins > kMaxSpins) {
-            if (lane == 0) atomicOr((unsigned long long*)&a.counters[ARGUS_HO_INTERNAL], 1ull);
-            break;
-          }
-          backoff();
-        }
-      }
+      const uint64_t excl = scan_lookback(a.status, (uint32_t)tile, cnt, &a.counters[ARGUS_HO_INTERNAL], 1);
       if (lane == 0) {
-        if (tile != 0) st_agent(&a.status[tile], kFlagIncl | (excl + cnt));
         s_base = excl;
         if (tile == T - 1) *a.mtot = excl + cnt;
       }

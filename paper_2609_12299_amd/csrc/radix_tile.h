@@ -140,7 +140,7 @@ ARGUS_DEV void clear_rows(uint64_t* lb, uint64_t r0, uint64_t r1) {
 }
 
 // Records (RAW 1) or overlap events of instances (RAW 2) as the raw source;
-// RAW 0: packed buffers only; RAW 3: packed buffers without payloads.
+// RAW 3: packed buffers only, without payloads.
 template <int RAW>
 __device__ __forceinline__ void radix_tile(const RadixArgs& a, RadixShared& s, const KeySpace& ks,
                                            const RadixPass& ps, uint64_t tile) {
@@ -167,7 +167,7 @@ __device__ __forceinline__ void radix_tile(const RadixArgs& a, RadixShared& s, c
     const uint64_t rel = wide ? c : (ks.ts_bits >= 64 ? 0ull : (k >> ks.ts_bits));
     return (uint32_t)((ks.ctx_min + rel) >> ps.shift) & 0xFFu;
   };
-  if (RAW == 0 || RAW == 3 || ps.src < 2) {
+  if (RAW == 3 || ps.src < 2) {
     const uint64_t* ksrc = ps.src ? a.key[1] : a.key[0];
     const uint32_t* psrc = ps.src ? a.pay[1] : a.pay[0];
     const uint32_t* csrc = ps.src ? a.ctxw[1] : a.ctxw[0];
