@@ -1,5 +1,5 @@
-"""Scoped statistics read only the 256-instance granules that may hold instances
-in scope, as marked by the ordinal pass, and the chunks inside one context whose
+"""Scoped statistics are taken by granules of 256 instances and, in large buffers,
+read only those that may hold instances in scope, as marked by the ordinal pass, and the chunks inside one context whose
 ordinals reach the iteration window, as found by the carry scan; histogram keys
 are kept per granule.  Windows at and around chunk (4096) and granule edges, in
 the first, inner and last chunks of a context, beyond every ordinal, for one
