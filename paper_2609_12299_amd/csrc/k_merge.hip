@@ -1139,7 +1139,7 @@ struct MsRows {
 // tile_sums for five to eight classes.  Pair sums per thread would take
 // K(K+1)/2 multiply-adds and as many activity tests per event (at eight
 // classes 202 registers, one block per compute unit: the pass took 2.0 ms over
-// 2^26 records, this way 1.07), so a group of 8 lanes takes an event together,
+// 2^26 records, this way 1.08), so a group of 8 lanes takes an event together,
 // lane y holding class y's count.  Summed by parts, with tau the time from an
 // event to the tile's end,
 //   sum gap l'_x l'_y = tau_first B^2 + sum over events of x of s tau l'_y
